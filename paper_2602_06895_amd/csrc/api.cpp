@@ -205,8 +205,8 @@ msx_status sample_device(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uin
     MSX_HIP(ctx,
             launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, d_call, C,
                           ctx->all_slots, ctx->all_inv, ctx->all_kinds, ctx->mixed, ctx->lds_max, seed, stream_id,
-                          counter_offset, 0, ctx->max_np, capacity, p, x1x2, w, chan, d_tile, ctx->d_stats, grid, s,
-                          d_vtiles, ctx->vstride, ctx->d_hist_off, ctx->hist_total, ctx->d_hist, jit_of(ctx)),
+                          counter_offset, 0, ctx->max_np, capacity, p, x1x2, w, chan, d_tile, max_tiles, ctx->d_stats,
+                          grid, s, d_vtiles, ctx->vstride, ctx->d_hist_off, ctx->hist_total, ctx->d_hist, jit_of(ctx)),
             "sample launch");
     if (advance) MSX_HIP(ctx, launch_advance_counter(d_call, const_cast<uint64_t*>(counter_offset), s), "counter");
     return MSX_OK;
@@ -571,7 +571,7 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
             launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, ctx->d_call, C,
                           max_slots, max_inv, kinds, ctx->mixed, ctx->lds_max, seed, stream_id, nullptr,
                           counter_offset, ctx->max_np, N, p, x1x2, w, chan, noalloc ? ctx->d_noalloc : ctx->d_tile,
-                          ctx->d_stats, grid, s, acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off,
+                          tiles, ctx->d_stats, grid, s, acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off,
                           ctx->hist_total, ctx->d_hist, jit_of(ctx)),
             "sample launch");
     return MSX_OK;
@@ -1151,8 +1151,8 @@ msx_status sample_with_flows(msx_ctx* ctx, const int64_t* counts, uint64_t seed,
         MSX_HIP(ctx,
                 launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, ctx->d_call,
                               C, max_slots, max_inv, kinds, ctx->mixed, ctx->lds_max, seed, stream_id, nullptr,
-                              counter_offset, ctx->max_np, N, p, x1x2, w, chan, ctx->d_tile, ctx->d_stats, grid, s,
-                              acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off, ctx->hist_total,
+                              counter_offset, ctx->max_np, N, p, x1x2, w, chan, ctx->d_tile, tiles,
+                              ctx->d_stats, grid, s, acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off, ctx->hist_total,
                               ctx->d_hist, jit_of(ctx)),
                 "sample launch");
     }

@@ -61,15 +61,13 @@ __global__ __launch_bounds__(kBlock) void k_weight(const ChannelTab* __restrict_
     if (alpha) alpha[e] = av;
 }
 
-// Reduce the tiles of each channel in order and add to the accumulators
-// stats[c] = (sum w, sum w^2, n, n(w == 0), max w).
-__global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __restrict__ call,
-                                                        const double* __restrict__ tile_stats,
-                                                        double* __restrict__ stats) {
-    const int c = blockIdx.x;
-    __shared__ double red[4][kWaves];
-    if (c >= call->n_chan || ((call->skip_mask >> c) & 1)) return;
-    const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
+// Sum of the statistics of tiles [t0, t1) over a workgroup, in a fixed order;
+// the result is valid in thread 0.
+struct TileSum {
+    double s1, s2, zeros, wmax;
+};
+__device__ __forceinline__ TileSum sum_tiles(const double* tile_stats, int64_t t0, int64_t t1,
+                                             double (&red)[4][kWaves]) {
     double a[4] = {0.0, 0.0, 0.0, 0.0};
     for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
         a[0] += tile_stats[t * 4 + 0];
@@ -86,20 +84,75 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __rest
         red[3][wave] = r3;
     }
     __syncthreads();
+    TileSum r{red[0][0], red[1][0], red[2][0], red[3][0]};
+    for (int v = 1; v < kWaves; ++v) {
+        r.s1 += red[0][v];
+        r.s2 += red[1][v];
+        r.zeros += red[2][v];
+        r.wmax = fmax(r.wmax, red[3][v]);
+    }
+    return r;
+}
+
+// A channel with more than kStatTiles tiles is reduced in two passes: first
+// kStatSlices workgroups sum a contiguous run of its tiles each, in place
+// (into the run's first entry), then k_stats_final adds the runs.  One
+// workgroup per channel walking all its tiles is bound by the latency of its
+// loads: 147 us for the 78125 tiles of 2e7 t tbar events, 11 us in two
+// passes; up to 2048 tiles (eight loads a thread) the second launch would
+// cost more than it saves.
+constexpr int kStatTiles = 2048, kStatSlices = 64;
+
+__global__ __launch_bounds__(kBlock) void k_stats_slices(const SampleCall* __restrict__ call, double* tile_stats) {
+    const int c = blockIdx.y;
+    __shared__ double red[4][kWaves];
+    if (c >= call->n_chan || ((call->skip_mask >> c) & 1)) return;
+    const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
+    if (t1 - t0 <= kStatTiles) return;
+    const int64_t per = (t1 - t0 + kStatSlices - 1) / kStatSlices;
+    const int64_t b = t0 + blockIdx.x * per, e = min(t1, b + per);
+    if (b >= e) return;
+    const TileSum r = sum_tiles(tile_stats, b, e, red);
     if (threadIdx.x == 0) {
-        double s0 = red[0][0], s1 = red[1][0], s2 = red[2][0], mx = red[3][0];
-        for (int v = 1; v < kWaves; ++v) {
-            s0 += red[0][v];
-            s1 += red[1][v];
-            s2 += red[2][v];
-            mx = fmax(mx, red[3][v]);
+        tile_stats[b * 4 + 0] = r.s1;
+        tile_stats[b * 4 + 1] = r.s2;
+        tile_stats[b * 4 + 2] = r.zeros;
+        tile_stats[b * 4 + 3] = r.wmax;
+    }
+}
+
+// Reduce the tiles of each channel and add to the accumulators
+// stats[c] = (sum w, sum w^2, n, n(w == 0), max w).
+__global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __restrict__ call,
+                                                        const double* __restrict__ tile_stats,
+                                                        double* __restrict__ stats) {
+    const int c = blockIdx.x;
+    __shared__ double red[4][kWaves];
+    if (c >= call->n_chan || ((call->skip_mask >> c) & 1)) return;
+    const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
+    TileSum r;
+    if (t1 - t0 <= kStatTiles) {
+        r = sum_tiles(tile_stats, t0, t1, red);
+    } else {
+        // the runs' sums sit in the first entry of each run
+        const int64_t per = (t1 - t0 + kStatSlices - 1) / kStatSlices;
+        const int64_t t = t0 + threadIdx.x * per;
+        if (threadIdx.x < 64) {
+            static_assert(kStatSlices == 64, "one lane per run");
+            const bool has = t < t1;
+            r.s1 = wave_sum(has ? tile_stats[t * 4 + 0] : 0.0);
+            r.s2 = wave_sum(has ? tile_stats[t * 4 + 1] : 0.0);
+            r.zeros = wave_sum(has ? tile_stats[t * 4 + 2] : 0.0);
+            r.wmax = wave_max(has ? tile_stats[t * 4 + 3] : 0.0);
         }
+    }
+    if (threadIdx.x == 0) {
         double* st = stats + 5 * c;
-        st[0] += s0;
-        st[1] += s1;
+        st[0] += r.s1;
+        st[1] += r.s2;
         st[2] += (double)(call->ev_start[c + 1] - call->ev_start[c]);
-        st[3] += s2;
-        st[4] = fmax(st[4], mx);
+        st[3] += r.zeros;
+        st[4] = fmax(st[4], r.wmax);
     }
 }
 
@@ -807,8 +860,8 @@ hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const dou
                          const int32_t* chan_nb, const SampleCall* call, int n_chan, int max_slots, int max_inv,
                          int kinds, int mixed, size_t lds_bytes, uint64_t seed, uint64_t sid, const uint64_t* ctr_dev,
                          uint64_t ctr_off, int np, int64_t ld, double* p, double* x1x2, double* w, int32_t* chan,
-                         double* tile_stats, double* stats, int grid, hipStream_t s, double* vpart, int vstride,
-                         const int64_t* hist_off, int64_t hist_total, double* hist, const JitSampleSet* jit) {
+                         double* tile_stats, int64_t max_tiles, double* stats, int grid, hipStream_t s,
+                         double* vpart, int vstride, const int64_t* hist_off, int64_t hist_total, double* hist, const JitSampleSet* jit) {
     if (jit && jit->n > 0) {
         int grid_doubles = (int)(lds_bytes / sizeof(double));
         void* args[] = {&cts, &pts, &grids, &grid_off, &chan_nb, &call, &seed, &sid, &ctr_dev, &ctr_off, &np, &ld,
@@ -848,6 +901,8 @@ hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const dou
         hipError_t err = launch_chain(reg_class(max_slots, max_inv), kind_class(kinds), mixed, a);
         if (err != hipSuccess) return err;
     }
+    if (max_tiles > kStatTiles)
+        k_stats_slices<<<dim3(kStatSlices, (unsigned)n_chan), kBlock, 0, s>>>(call, tile_stats);
     k_stats_final<<<n_chan, kBlock, 0, s>>>(call, tile_stats, stats);
     if (vpart && hist_total > 0) {
         const int64_t g = (hist_total + 63) / 64;

@@ -121,8 +121,8 @@ hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const dou
                          const int32_t* chan_nb, const SampleCall* call, int n_chan, int max_slots, int max_inv,
                          int kinds, int mixed, size_t lds_bytes, uint64_t seed, uint64_t sid, const uint64_t* ctr_dev,
                          uint64_t ctr_off, int np, int64_t ld, double* p, double* x1x2, double* w, int32_t* chan,
-                         double* tile_stats, double* stats, int grid, hipStream_t s, double* vpart = nullptr,
-                         int vstride = 0, const int64_t* hist_off = nullptr, int64_t hist_total = 0,
+                         double* tile_stats, int64_t max_tiles, double* stats, int grid, hipStream_t s,
+                         double* vpart = nullptr, int vstride = 0, const int64_t* hist_off = nullptr, int64_t hist_total = 0,
                          double* hist = nullptr, const JitSampleSet* jit = nullptr);
 // Dynamic LDS bytes of a sample launch with VEGAS accumulation (grid area
 // lds_bytes, vstride doubles per wave histogram) for the register class of

@@ -71,3 +71,31 @@ def test_sample_repeats_its_bits(torch, case, mixed):
             ref = ref or bits
             assert all(torch.equal(a, b) for a, b in zip(bits, ref))
     ctx.close()
+
+
+@pytest.mark.parametrize("tiles", [1, 2047, 2048, 2049, 64 * 40, 64 * 40 + 1])
+def test_statistics_of_many_tiles(torch, tiles):
+    """One pass up to 2048 tiles of a channel, two beyond (full and ragged
+    runs); beside a channel of one tile.  Relative error of a sum of n
+    non-negative terms: at most n times the unit roundoff."""
+    from paper_2602_06895_amd import Context
+
+    desc = {"processes": [W.c1_ee_mumu(), W.c1_ee_mumu()]}
+    ctx = Context(desc)
+    counts = [256 * (tiles - 1) + 3, 100]
+    out = ctx.sample(counts, seed=9, stream_id=1, counter_offset=5)
+    st = ctx.stats()
+    ctx.sample(counts, seed=9, stream_id=1, counter_offset=5)
+    twice = ctx.stats()
+    w = out["w"].cpu().numpy()
+    off = 0
+    for c, n in enumerate(counts):
+        v = w[off:off + n]
+        off += n
+        tol = n * 2.0 ** -52
+        for k, want in ((0, v.sum()), (1, (v * v).sum())):
+            assert abs(st[c, k] - want) <= tol * want
+            assert abs(twice[c, k] - 2.0 * want) <= 2.0 * tol * want
+        assert st[c, 2] == n and st[c, 3] == (v == 0).sum() and st[c, 4] == v.max()
+        assert twice[c, 2] == 2 * n and twice[c, 4] == v.max()
+    ctx.close()
