@@ -1008,106 +1008,166 @@ static_assert(kUnwBuckets == kUnwMaxBuckets, "bucket count");
 // a bucket has the bucket's binary exponent (the buckets of every pass lie
 // within one exponent), so its value is m 2^(e - 1075) with the integer
 // significand m < 2^53, and the bucket sum is kept exactly as the sums of
-// m's upper 27 and lower 26 bits (each < 2^63 for n < 2^36 weights).
-__global__ __launch_bounds__(256) void k_unw_hist(int64_t n, const double* __restrict__ w, int shift, int width,
-                                                  const UnwState* __restrict__ st, int first,
-                                                  unsigned long long* __restrict__ counts,
-                                                  unsigned long long* __restrict__ sum_hi,
-                                                  unsigned long long* __restrict__ sum_lo) {
+// m's upper 27 and lower 26 bits (each < 2^63 for n < 2^36 weights).  In LDS
+// the count rides in the upper sum's word, above bit 45 (a workgroup sees at
+// most 2^17 weights, so that sum stays below 2^44).
+//
+// Eight weights are in flight per thread: with one the pass over 1e7 weights
+// took 38 us (2.1 TB/s), bound by the latency of its loads.
+constexpr int kUnwThreads = 512, kUnwFlight = 8;
+constexpr int64_t kUnwPerBlock = 1 << 17;
+__global__ __launch_bounds__(kUnwThreads) void k_unw_hist(int64_t n, int64_t chunk, const double* __restrict__ w,
+                                                          int shift, int width, const UnwState* __restrict__ st,
+                                                          int first, unsigned long long* __restrict__ counts,
+                                                          unsigned long long* __restrict__ sum_hi,
+                                                          unsigned long long* __restrict__ sum_lo) {
     const uint64_t prefix = st->prefix;
-    __shared__ unsigned int c_l[kUnwBuckets];
     __shared__ unsigned long long h_l[kUnwBuckets];
     __shared__ unsigned long long l_l[kUnwBuckets];
     const int nbk = 1 << width;
-    for (int i = threadIdx.x; i < nbk; i += blockDim.x) {
-        c_l[i] = 0u;
+    for (int i = threadIdx.x; i < nbk; i += kUnwThreads) {
         h_l[i] = 0ull;
         l_l[i] = 0ull;
     }
     __syncthreads();
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        double v = w[e];
-        if (!(v > 0.0)) continue;  // zero weights carry no excess
-        uint64_t bits = (uint64_t)__double_as_longlong(v);
-        if (!first && (bits >> (shift + width)) != prefix) continue;
-        int b = (int)((bits >> shift) & (uint64_t)(nbk - 1));
-        const uint64_t ex = bits >> 52;
-        const uint64_t m = (bits & ((1ull << 52) - 1)) | (ex ? (1ull << 52) : 0ull);
-        atomicAdd(&c_l[b], 1u);
-        atomicAdd(&h_l[b], (unsigned long long)(m >> 26));
-        atomicAdd(&l_l[b], (unsigned long long)(m & ((1ull << 26) - 1)));
+    const int64_t e0 = blockIdx.x * chunk, e1 = min(n, e0 + chunk);
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += kUnwThreads * kUnwFlight) {
+        double v[kUnwFlight];
+#pragma unroll
+        for (int u = 0; u < kUnwFlight; ++u) {
+            const int64_t i = e + u * kUnwThreads;
+            v[u] = i < e1 ? w[i] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnwFlight; ++u) {
+            if (!(v[u] > 0.0)) continue;  // zero weights carry no excess
+            const uint64_t bits = (uint64_t)__double_as_longlong(v[u]);
+            if (!first && (bits >> (shift + width)) != prefix) continue;
+            const int b = (int)((bits >> shift) & (uint64_t)(nbk - 1));
+            const uint64_t ex = bits >> 52;
+            const uint64_t m = (bits & ((1ull << 52) - 1)) | (ex ? (1ull << 52) : 0ull);
+            atomicAdd(&h_l[b], (unsigned long long)((m >> 26) | (1ull << 45)));
+            atomicAdd(&l_l[b], (unsigned long long)(m & ((1ull << 26) - 1)));
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < nbk; i += blockDim.x) {
-        if (c_l[i]) {
-            atomicAdd(&counts[i], (unsigned long long)c_l[i]);
-            atomicAdd(&sum_hi[i], h_l[i]);
+    for (int i = threadIdx.x; i < nbk; i += kUnwThreads) {
+        const unsigned long long h = h_l[i];
+        if (h) {
+            atomicAdd(&counts[i], h >> 45);
+            atomicAdd(&sum_hi[i], h & ((1ull << 45) - 1));
             atomicAdd(&sum_lo[i], l_l[i]);
         }
     }
 }
 
-// The crossing bucket of one pass: the workgroup converts the bucket sums
-// and counts into LDS, then one thread scans from the top bucket down (the
-// order and arithmetic of a sequential scan): the excess at the lower edge
-// L_b of bucket b, S - L_b N over the weights in buckets >= b and above the
-// earlier passes' crossing buckets, reaches the target first at the crossing
-// bucket; st gets the extended prefix and the sums above it.  The bucket
-// arrays are cleared for the next pass.
-__global__ __launch_bounds__(256) void k_unw_search(int shift, int width, double overweight,
+constexpr int kUnwScanWaves = 16;
+
+// Running sums of S and N over the workgroup's threads (inclusive), in a
+// fixed order.
+__device__ __forceinline__ void scan_pairs(double& S, double& N, double (&red)[2][kUnwScanWaves]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double s = __shfl_up(S, o, 64), c = __shfl_up(N, o, 64);
+        if (lane >= o) {
+            S += s;
+            N += c;
+        }
+    }
+    if (lane == 63) {
+        red[0][wave] = S;
+        red[1][wave] = N;
+    }
+    __syncthreads();
+    for (int v = 0; v < wave; ++v) {
+        S += red[0][v];
+        N += red[1][v];
+    }
+}
+
+// The crossing bucket of one pass: the excess at the lower edge L_b of bucket
+// b, S - L_b N over the weights in buckets >= b and above the earlier passes'
+// crossing buckets, reaches the target first, from the top bucket down, at
+// the crossing bucket; st gets the extended prefix and the sums above it.
+// Every thread converts and sums a run of four buckets, the runs' sums are
+// scanned over the workgroup, and each thread then looks for the crossing in
+// its own run (a single thread walking the 4096 buckets took 155 us a pass,
+// this way 10).  The bucket arrays are cleared for the next pass.
+__global__ __launch_bounds__(64 * kUnwScanWaves) void k_unw_search(int shift, int width, double overweight,
                                                     const double* __restrict__ tot, UnwState* __restrict__ st,
                                                     unsigned long long* __restrict__ counts,
                                                     unsigned long long* __restrict__ sum_hi,
                                                     unsigned long long* __restrict__ sum_lo) {
-    __shared__ double s_b[kUnwBuckets];
-    __shared__ double n_b[kUnwBuckets];
+    constexpr int kRun = kUnwBuckets / (64 * kUnwScanWaves);
+    __shared__ double red[2][kUnwScanWaves];
+    __shared__ int first;
     const int nbk = 1 << width;
     const uint64_t prefix = st->prefix;
-    // every bucket's sum (its significand sum times 2^(e - 1075), e its
-    // biased exponent; 1 - 1075 for subnormals) and count, in parallel
-    for (int b = threadIdx.x; b < nbk; b += blockDim.x) {
-        const uint64_t lb_bits = ((prefix << width) | (uint64_t)b) << shift;
-        const int ex = (int)(lb_bits >> 52);
-        s_b[b] = ldexp((double)sum_hi[b] * 67108864.0 + (double)sum_lo[b], (ex ? ex : 1) - 1075);
-        n_b[b] = (double)counts[b];
+    const double S_up = st->S_up, N_up = st->N_up;
+    const double target = overweight * tot[0];
+    if (threadIdx.x == 0) first = kUnwBuckets;
+    // position q = 0, 1, ... from the top bucket down: bucket nbk - 1 - q
+    const int q0 = threadIdx.x * kRun;
+    double sv[kRun], nv[kRun], S = 0.0, N = 0.0;
+#pragma unroll
+    for (int u = 0; u < kRun; ++u) {
+        const int b = nbk - 1 - (q0 + u);
+        sv[u] = nv[u] = 0.0;
+        if (b >= 0) {
+            // the bucket's significand sum times 2^(e - 1075), e its biased
+            // exponent (1 - 1075 for subnormals)
+            const uint64_t lb_bits = ((prefix << width) | (uint64_t)b) << shift;
+            const int ex = (int)(lb_bits >> 52);
+            sv[u] = ldexp((double)sum_hi[b] * 67108864.0 + (double)sum_lo[b], (ex ? ex : 1) - 1075);
+            nv[u] = (double)counts[b];
+            counts[b] = 0ull;
+            sum_hi[b] = 0ull;
+            sum_lo[b] = 0ull;
+        }
+        S += sv[u];
+        N += nv[u];
+    }
+    double Si = S, Ni = N;
+    scan_pairs(Si, Ni, red);
+    // the sums above this thread's run: the runs before it, added up the same
+    // way on every thread
+    double Sa = __shfl_up(Si, 1, 64), Na = __shfl_up(Ni, 1, 64);
+    if ((threadIdx.x & 63) == 0) {
+        Sa = Na = 0.0;
+        for (int v = 0; v < (int)(threadIdx.x >> 6); ++v) {
+            Sa += red[0][v];
+            Na += red[1][v];
+        }
+    }
+    Sa += S_up;
+    Na += N_up;
+    int found = kUnwBuckets;
+    double S_above = 0.0, N_above = 0.0;
+#pragma unroll
+    for (int u = 0; u < kRun; ++u) {
+        const int b = nbk - 1 - (q0 + u);
+        if (b >= 0 && found == kUnwBuckets) {
+            const uint64_t lb_bits = ((prefix << width) | (uint64_t)b) << shift;
+            const double Sn = Sa + sv[u], Nn = Na + nv[u];
+            // the last bucket stands in when none crosses: W then lies below
+            // every positive weight
+            if (Sn - __longlong_as_double((long long)lb_bits) * Nn >= target || b == 0) {
+                found = q0 + u;
+                S_above = Sa;
+                N_above = Na;
+            }
+            Sa = Sn;
+            Na = Nn;
+        }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const double target = overweight * tot[0];
-        double S = st->S_up, N = st->N_up;
-        double S_above = S, N_above = N;
-        int found = -1;
-        // eight buckets per step, their LDS reads issued before the
-        // sequential additions (the scan is otherwise bound by LDS latency)
-        for (int b0 = nbk - 1; b0 >= 0 && found < 0; b0 -= 8) {
-            double sv[8], nv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                sv[u] = b0 - u >= 0 ? s_b[b0 - u] : 0.0;
-                nv[u] = b0 - u >= 0 ? n_b[b0 - u] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int b = b0 - u;
-                if (b < 0 || found >= 0) break;
-                S_above = S;
-                N_above = N;
-                S += sv[u];
-                N += nv[u];
-                const uint64_t lb_bits = ((prefix << width) | (uint64_t)b) << shift;
-                if (S - __longlong_as_double((long long)lb_bits) * N >= target) found = b;
-            }
-        }
-        if (found < 0) found = 0;  // only the zero bucket: W lies below every positive weight
+    if (found < kUnwBuckets) atomicMin(&first, found);
+    __syncthreads();
+    if (found == first && found < kUnwBuckets) {
         st->S_up = S_above;
         st->N_up = N_above;
-        st->prefix = (prefix << width) | (uint64_t)found;
-    }
-    for (int i = threadIdx.x; i < kUnwBuckets; i += blockDim.x) {
-        counts[i] = 0ull;
-        sum_hi[i] = 0ull;
-        sum_lo[i] = 0ull;
+        st->prefix = (prefix << width) | (uint64_t)(nbk - 1 - found);
     }
 }
 
@@ -1137,15 +1197,24 @@ __global__ __launch_bounds__(256) void k_sum_max(int64_t n, const double* __rest
     }
 }
 
-__global__ void k_sum_max_final(int nblk, const double* __restrict__ part, double* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ __launch_bounds__(256) void k_sum_max_final(int nblk, const double* __restrict__ part,
+                                                       double* __restrict__ out) {
     double a = 0.0, b = 0.0;
-    for (int i = 0; i < nblk; ++i) {
+    for (int i = threadIdx.x; i < nblk; i += 256) {
         a += part[2 * i];
         b = fmax(b, part[2 * i + 1]);
     }
-    out[0] = a;
-    out[1] = b;
+    __shared__ double rs[4], rm[4];
+    const double ws = wave_sum(a), wm = wave_max(b);
+    if ((threadIdx.x & 63) == 0) {
+        rs[threadIdx.x >> 6] = ws;
+        rm[threadIdx.x >> 6] = wm;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        out[0] = ((rs[0] + rs[1]) + rs[2]) + rs[3];
+        out[1] = fmax(fmax(rm[0], rm[1]), fmax(rm[2], rm[3]));
+    }
 }
 
 // Moments of a weight array: block b reduces its grid-stride share into
@@ -1236,11 +1305,15 @@ hipError_t launch_unw_search(int64_t n, const double* w, double overweight, cons
     // bits, the last pass 3
     const int shifts[6] = {51, 39, 27, 15, 3, 0};
     const int widths[6] = {12, 12, 12, 12, 12, 3};
-    const int g = grid_for(n, cu_count * 4);
+    // contiguous chunks of at most kUnwPerBlock weights; two workgroups fill a
+    // compute unit's LDS
+    const int64_t g = std::max<int64_t>((n + kUnwPerBlock - 1) / kUnwPerBlock,
+                                        std::min<int64_t>(2 * cu_count, (n + kUnwThreads - 1) / kUnwThreads));
+    const int64_t chunk = (n + g - 1) / g;
     for (int pass = 0; pass < 6; ++pass) {
-        k_unw_hist<<<g, 256, 0, s>>>(n, w, shifts[pass], widths[pass], st, pass == 0, (unsigned long long*)counts,
+        k_unw_hist<<<(unsigned)g, kUnwThreads, 0, s>>>(n, chunk, w, shifts[pass], widths[pass], st, pass == 0, (unsigned long long*)counts,
                                      (unsigned long long*)sum_hi, (unsigned long long*)sum_lo);
-        k_unw_search<<<1, 256, 0, s>>>(shifts[pass], widths[pass], overweight, tot, st, (unsigned long long*)counts,
+        k_unw_search<<<1, 64 * kUnwScanWaves, 0, s>>>(shifts[pass], widths[pass], overweight, tot, st, (unsigned long long*)counts,
                                        (unsigned long long*)sum_hi, (unsigned long long*)sum_lo);
     }
     return hipGetLastError();
@@ -1250,7 +1323,7 @@ hipError_t launch_sum_max(int64_t n, const double* w, double* out, double* part,
     k_sum_max<<<nblk, 256, 0, s>>>(n, w, part);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    k_sum_max_final<<<1, 64, 0, s>>>(nblk, part, out);
+    k_sum_max_final<<<1, 256, 0, s>>>(nblk, part, out);
     return hipGetLastError();
 }
 

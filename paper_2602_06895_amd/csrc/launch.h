@@ -175,7 +175,7 @@ namespace msx {
 // (2^width - 1) of the positive weights whose higher bits equal the prefix
 // found so far (counts, and the bucket's significand sum as the sums of
 // m >> 26 and m & (2^26 - 1), the weight being m 2^(e - 1075); integer
-// atomics only), then a one-thread scan for the crossing bucket.  On return
+// atomics only), then a scan for the crossing bucket.  On return
 // (stream order) st holds the crossing value's bit pattern in prefix and the
 // sums above it.  st must start at zero, the bucket arrays (kUnwMaxBuckets
 // words each) too; they are zero again afterwards.  No host round trip.

@@ -99,3 +99,28 @@ def test_statistics_of_many_tiles(torch, tiles):
         assert st[c, 2] == n and st[c, 3] == (v == 0).sum() and st[c, 4] == v.max()
         assert twice[c, 2] == 2 * n and twice[c, 4] == v.max()
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["spread", "equal", "one", "ties"])
+@pytest.mark.parametrize("n", [1, 2, 511, 4097, 512 * 512 + 1, 700_001])
+def test_unweighting_efficiency_search(torch, kind, n):
+    """The threshold against its definition on the sorted weights, the same
+    bits on a second call.  The excess is linear in W between two weights, so
+    W carries the relative error of the sums over the weights above it divided
+    by their share of the total (1e-3): n times the unit roundoff times 1e3."""
+    from paper_2602_06895_amd import Context
+
+    rng = np.random.default_rng(n)
+    w = {"spread": lambda: np.exp(rng.normal(0.0, 3.0, n)) * (rng.random(n) < 0.7),
+         "equal": lambda: np.full(n, 0.37),
+         "one": lambda: np.where(np.arange(n) == n // 2, 2.5, 0.0),
+         "ties": lambda: rng.choice([1.0, 1.0 + 2.0 ** -52, 7.0, 1e-300], n)}[kind]()
+    w[0] = max(w[0], 1e-3)
+    ctx = Context(W.c1_ee_mumu())
+    t = torch.from_numpy(w).cuda()
+    got = [ctx.unweight_eff(t) for _ in range(2)]
+    assert got[0] == got[1]
+    eff, w_max = oracle.unweighting_efficiency(w)
+    tol = 1e-12 + n * 2.0 ** -52 * 1e3
+    assert abs(got[0][1] - w_max) <= tol * w_max and abs(got[0][0] - eff) <= tol * eff
+    ctx.close()
