@@ -124,3 +124,27 @@ def test_unweighting_efficiency_search(torch, kind, n):
     tol = 1e-12 + n * 2.0 ** -52 * 1e3
     assert abs(got[0][1] - w_max) <= tol * w_max and abs(got[0][0] - eff) <= tol * eff
     ctx.close()
+
+
+@pytest.mark.parametrize("bins", [1, 2, 63, 64, 65, 512, 513, 4096])
+@pytest.mark.parametrize("n", [0, 1, 63, 2049, 2048 * 2048 + 77])
+def test_histogram_shapes(torch, bins, n):
+    """One and four waves per workgroup, one bin, more bins than events, all
+    events in one bin, values on the ends of the range; the same bits on a
+    second call.  Sums of non-negative terms: n times the unit roundoff."""
+    from paper_2602_06895_amd import Context
+
+    rng = np.random.default_rng(n + bins)
+    x = rng.normal(0.4, 0.3, n)
+    w = np.exp(rng.normal(0.0, 1.0, n)) * (rng.random(n) < 0.6)
+    if n > 8:
+        x[:4] = [0.0, 1.0, np.nan, -0.0]
+        x[n // 2:n // 2 + n // 4] = 0.5
+        w[:4] = 1.0
+    ctx = Context(W.c1_ee_mumu())
+    tx, tw = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    a, b = (ctx.histogram(tx, tw, bins, 0.0, 1.0).cpu().numpy() for _ in range(2))
+    assert np.array_equal(a, b)
+    want = oracle.histogram(x, w, bins, 0.0, 1.0)
+    assert np.all(np.abs(a - want) <= max(n, 1) * 2.0 ** -52 * want)
+    ctx.close()
