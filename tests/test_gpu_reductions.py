@@ -148,3 +148,32 @@ def test_histogram_shapes(torch, bins, n):
     want = oracle.histogram(x, w, bins, 0.0, 1.0)
     assert np.all(np.abs(a - want) <= max(n, 1) * 2.0 ** -52 * want)
     ctx.close()
+
+
+@pytest.mark.parametrize("nf", range(2, 9))
+def test_observables_of_every_particle_count(torch, nf):
+    """Every kind on full and partial sets, at every number of final-state
+    particles, against the oracle.  Both sum the same doubles in the same order
+    and differ by the rounding of a few library functions (1e-13 relative);
+    the mass, whose E^2 - p^2 cancels, by u E^2 / M."""
+    from paper_2602_06895_amd import (OBS_DR_HARDEST, OBS_E, OBS_ETA, OBS_M, OBS_PHI, OBS_PT, OBS_PT_RANK, Context)
+
+    rng = np.random.default_rng(nf)
+    n = 1003
+    p = rng.normal(0.0, 50.0, (4, nf + 2, n))
+    p[0] = np.sqrt((p[1:] ** 2).sum(0))
+    p[1:, 3, :7] = p[1:, 2, :7]  # equal transverse momenta
+    every, some = list(range(nf)), [0, nf - 1]
+    spec = [(OBS_M, every, 0), (OBS_PT_RANK, every, nf - 1), (OBS_DR_HARDEST, every, 0), (OBS_ETA, [nf - 1], 0),
+            (OBS_PHI, some, 0), (OBS_PT, every, 0), (OBS_E, some, 0), (OBS_PT_RANK, some, 1)]
+    ctx = Context(W.volume_process(nf) if nf > 2 else W.c1_ee_mumu())
+    got = ctx.observables(0, torch.from_numpy(p).cuda(), spec).cpu().numpy()
+    want = oracle.observables(p, spec)
+    scale = np.abs(want) + 1e-3  # angles and separations near zero: absolute
+    scale[0] = want[0] + p[0, 2:].sum(0) ** 2 / np.maximum(want[0], 1e-3) * 1e-2
+    assert np.all(np.abs(got - want) <= 1e-12 * scale)
+    # a list that needs no energies and one that needs nothing but a sum of them
+    for part in ([spec[2]], [spec[6]], [spec[4], spec[1]]):
+        assert np.array_equal(ctx.observables(0, torch.from_numpy(p).cuda(), part).cpu().numpy(),
+                              got[[spec.index(s) for s in part]])
+    ctx.close()
