@@ -1009,7 +1009,7 @@ msx_status msx_unweight(msx_ctx* ctx, const double* w, int64_t n, double w_max, 
     if (n > 0 && (!w || !keep)) return fail(ctx, MSX_ERR_ARG, "w and keep are required");
     if (!(w_max > 0.0) || !std::isfinite(w_max)) return fail(ctx, MSX_ERR_ARG, "w_max must be finite and > 0");
     if (msx_status st = set_device(ctx)) return st;
-    const int64_t nb = std::max<int64_t>(1, unweight_blocks(n));
+    const int64_t nb = std::max<int64_t>(1, unweight_words(n));
     if (nb > ctx->ublk_cap) {
         // the previous scratch may still be read by work in flight
         MSX_HIP(ctx, hipDeviceSynchronize(), "synchronize");

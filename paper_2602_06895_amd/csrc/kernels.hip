@@ -160,31 +160,38 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __rest
 // estimated maximum weight): event i is kept when u_i w_max < w_i, u_i the
 // Philox uniform of event id e0 + i (dimension 0, as msx_uniform), and
 // carries the unit weight max(1, w_i / w_max) (overweight events above 1).
-// Pass 1 counts the kept events of every block of kUnwPer events; a one-
+// Pass 1 decides: every wave writes its decisions as one 64-bit mask per 64
+// events, and the kept events of every block of kUnwPer are counted; a one-
 // workgroup scan turns the counts into offsets; pass 2 writes the kept
-// indices in increasing order (ranks within a block from wave ballots).
-constexpr int kUnwPer = kBlock * 4;  // events per block
-
-__device__ __forceinline__ bool unw_keep(const double* __restrict__ w, int64_t i, double w_max, uint64_t seed,
-                                         uint64_t sid, uint64_t e0) {
-    uint64_t c0 = e0 + (uint64_t)i, c1 = 0, c2 = 0, c3 = 0;
-    philox4x64_10(c0, c1, c2, c3, seed, sid);
-    return to_unit(c0) * w_max < w[i];
-}
+// indices in increasing order from the masks (ranks are bit counts).  The
+// generator is most of the work, so it runs once: deciding again in pass 2
+// made that pass as long as the first (59 us each for 1e7 weights; now 55
+// and 8, and the scan 23 -> 13 with its 1024 run totals added by waves).
+constexpr int kUnwPer = kBlock * 4;          // events per block
+constexpr int kUnwMasks = kUnwPer / 64;      // masks per block
 
 __global__ __launch_bounds__(kBlock) void k_unw_count(const double* __restrict__ w, int64_t n, double w_max,
                                                       uint64_t seed, uint64_t sid, uint64_t e0,
-                                                      int64_t* __restrict__ blk) {
+                                                      int64_t* __restrict__ blk, uint64_t* __restrict__ masks) {
     __shared__ int red[kWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kUnwPer;
+    double wv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int64_t i = base + q * kBlock + threadIdx.x;
+        wv[q] = i < n ? w[i] : 0.0;
+    }
     int c = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int64_t i = (int64_t)blockIdx.x * kUnwPer + q * kBlock + threadIdx.x;
-        if (i < n && unw_keep(w, i, w_max, seed, sid, e0)) ++c;
+        const int64_t i = base + q * kBlock + threadIdx.x;
+        uint64_t c0 = e0 + (uint64_t)i, c1 = 0, c2 = 0, c3 = 0;
+        philox4x64_10(c0, c1, c2, c3, seed, sid);
+        const uint64_t bal = __ballot(i < n && to_unit(c0) * w_max < wv[q]);
+        if (lane == 0) masks[(int64_t)blockIdx.x * kUnwMasks + q * kWaves + wave] = bal;
+        c += __popcll(bal);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
     if (lane == 0) red[wave] = c;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -195,27 +202,26 @@ __global__ __launch_bounds__(kBlock) void k_unw_count(const double* __restrict__
 }
 
 // Exclusive scan of nb block counts in place (one workgroup: every thread
-// sums a contiguous run, the run totals are scanned in LDS); total to *count.
+// sums a contiguous run, the run totals are scanned by waves); total to
+// *count.
 __global__ __launch_bounds__(1024) void k_unw_scan(int64_t* __restrict__ blk, int64_t nb, int64_t* __restrict__ count) {
-    __shared__ int64_t tot[1024];
-    const int t = threadIdx.x;
+    __shared__ int64_t tot[16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t per = (nb + 1023) / 1024;
     const int64_t b0 = t * per, b1 = min(nb, b0 + per);
     int64_t s = 0;
     for (int64_t b = b0; b < b1; ++b) s += blk[b];
-    tot[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        int64_t acc = 0;
-        for (int v = 0; v < 1024; ++v) {
-            const int64_t x = tot[v];
-            tot[v] = acc;
-            acc += x;
-        }
-        *count = acc;
+    int64_t run = s;  // inclusive over the wave
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t x = __shfl_up(run, o, 64);
+        if (lane >= o) run += x;
     }
+    if (lane == 63) tot[wave] = run;
     __syncthreads();
-    int64_t acc = tot[t];
+    int64_t acc = run - s;
+    for (int v = 0; v < wave; ++v) acc += tot[v];
+    if (t == 1023) *count = acc + s;
     for (int64_t b = b0; b < b1; ++b) {
         const int64_t x = blk[b];
         blk[b] = acc;
@@ -223,33 +229,32 @@ __global__ __launch_bounds__(1024) void k_unw_scan(int64_t* __restrict__ blk, in
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_unw_write(const double* __restrict__ w, int64_t n, double w_max,
-                                                      uint64_t seed, uint64_t sid, uint64_t e0,
-                                                      const int64_t* __restrict__ blk, int64_t* __restrict__ keep,
+__global__ __launch_bounds__(kBlock) void k_unw_write(const double* __restrict__ w, double w_max,
+                                                      const int64_t* __restrict__ blk,
+                                                      const uint64_t* __restrict__ masks, int64_t* __restrict__ keep,
                                                       double* __restrict__ uw) {
-    __shared__ int wcnt[kWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t* m = masks + (int64_t)blockIdx.x * kUnwMasks;
     int64_t base = blk[blockIdx.x];
-#pragma unroll 1
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int64_t i = (int64_t)blockIdx.x * kUnwPer + q * kBlock + threadIdx.x;
-        const bool k = i < n && unw_keep(w, i, w_max, seed, sid, e0);
-        const uint64_t bal = __ballot(k);
-        if (lane == 0) wcnt[wave] = __popcll(bal);
-        __syncthreads();
         int off = 0, all = 0;
+        uint64_t mine = 0;
 #pragma unroll
         for (int v = 0; v < kWaves; ++v) {
-            off += v < wave ? wcnt[v] : 0;
-            all += wcnt[v];
+            const uint64_t x = m[q * kWaves + v];
+            const int c = __popcll(x);
+            off += v < wave ? c : 0;
+            all += c;
+            mine = v == wave ? x : mine;
         }
-        if (k) {
-            const int64_t pos = base + off + __popcll(bal & ((1ull << lane) - 1));
+        if ((mine >> lane) & 1) {
+            const int64_t i = (int64_t)blockIdx.x * kUnwPer + q * kBlock + threadIdx.x;
+            const int64_t pos = base + off + __popcll(mine & ((1ull << lane) - 1));
             keep[pos] = i;
             if (uw) uw[pos] = fmax(1.0, w[i] / w_max);
         }
         base += all;
-        __syncthreads();
     }
 }
 
@@ -822,7 +827,8 @@ hipError_t launch_histogram(const double* x, const double* w, int64_t n, int nb,
     return hipGetLastError();
 }
 
-int64_t unweight_blocks(int64_t n) { return (n + kUnwPer - 1) / kUnwPer; }
+static int64_t unweight_blocks(int64_t n) { return (n + kUnwPer - 1) / kUnwPer; }
+int64_t unweight_words(int64_t n) { return unweight_blocks(n) * (1 + kUnwMasks); }
 
 hipError_t launch_unweight(const double* w, int64_t n, double w_max, uint64_t seed, uint64_t sid, uint64_t e0,
                            int64_t* blk, int64_t* keep, double* uw, int64_t* count, hipStream_t s) {
@@ -831,12 +837,13 @@ hipError_t launch_unweight(const double* w, int64_t n, double w_max, uint64_t se
         k_unw_scan<<<1, 1024, 0, s>>>(blk, 0, count);
         return hipGetLastError();
     }
-    k_unw_count<<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(w, n, w_max, seed, sid, e0, blk);
+    uint64_t* masks = (uint64_t*)(blk + nb);
+    k_unw_count<<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(w, n, w_max, seed, sid, e0, blk, masks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_unw_scan<<<1, 1024, 0, s>>>(blk, nb, count);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_unw_write<<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(w, n, w_max, seed, sid, e0, blk, keep, uw);
+    k_unw_write<<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(w, w_max, blk, masks, keep, uw);
     return hipGetLastError();
 }
 

@@ -77,8 +77,8 @@ hipError_t launch_histogram(const double* x, const double* w, int64_t n, int nb,
 
 // Hit-or-miss unweighting: kept indices (increasing) to keep, unit weights
 // max(1, w / w_max) to uw (optional), the number kept to count (device);
-// blk: scratch of unweight_blocks(n) (at least 1) int64.
-int64_t unweight_blocks(int64_t n);
+// blk: scratch of unweight_words(n) (at least 1) 64-bit words.
+int64_t unweight_words(int64_t n);
 hipError_t launch_unweight(const double* w, int64_t n, double w_max, uint64_t seed, uint64_t sid, uint64_t e0,
                            int64_t* blk, int64_t* keep, double* uw, int64_t* count, hipStream_t s);
 

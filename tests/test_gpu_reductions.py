@@ -177,3 +177,21 @@ def test_observables_of_every_particle_count(torch, nf):
         assert np.array_equal(ctx.observables(0, torch.from_numpy(p).cuda(), part).cpu().numpy(),
                               got[[spec.index(s) for s in part]])
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1024, 1024 * 1024, 1024 * 1024 + 1, 1024 * 2049 + 5])
+def test_unweighting_of_many_blocks(torch, n):
+    """Runs of one, two and three blocks per thread of the offset scan: kept
+    indices, unit weights and count equal to the oracle's."""
+    from paper_2602_06895_amd import Context
+
+    rng = np.random.default_rng(n)
+    w = np.exp(rng.normal(0.0, 1.5, n)) * (rng.random(n) < 0.4)
+    ctx = Context(W.c1_ee_mumu())
+    out = ctx.unweight(torch.from_numpy(w).cuda(), 6.0, seed=3, stream_id=8, counter_offset=19)
+    ref = oracle.unweight(w, 6.0, W.philox_uniforms(3, 8, 19, n, 1)[0])
+    k = int(out["count"])
+    assert k == len(ref["keep"])
+    assert np.array_equal(out["keep"][:k].cpu().numpy(), ref["keep"])
+    assert np.array_equal(out["uw"][:k].cpu().numpy(), ref["uw"])
+    ctx.close()
