@@ -17,6 +17,7 @@ using namespace msx;
 
 struct msx_flow {
     int device = 0;
+    int cu_count = 256;
     int d = 0, L = 0, K = 0, H = 0, type = FT_BF16;
     int nh = 0, n_out = 0;
     int64_t per_layer = 0, P = 0;
@@ -219,7 +220,19 @@ msx_status bias_grad(msx_flow* f, const void* X, int64_t n, int N, float* out, h
     return MSX_OK;
 }
 
-// The one-kernel coupling layer covers BF16 conditioners of hidden width 128
+FlowNet net_of(const msx_flow* f) {
+    FlowNet n{};
+    n.wt = f->params_t;
+    n.p = f->params;
+    n.per_t = (int32_t)f->per_layer_t;
+    n.per = (int32_t)f->per_layer;
+    for (int i = 0; i < 8; ++i) n.off[i] = (int32_t)f->off[i];
+    n.nh = f->nh;
+    n.K = f->K;
+    return n;
+}
+
+// The fused coupling layers cover BF16 conditioners of hidden width 128
 // with up to 16 bins.
 bool fused_ok(const msx_flow* f) {
     return f->type == FT_BF16 && f->H == kFusedHidden && f->K <= kFusedMaxBins;
@@ -309,6 +322,27 @@ msx_status gradient(msx_flow* f, int64_t n, const float* y, const double* wfj, c
     return MSX_OK;
 }
 
+// All layers, forward or inverse, from `in` to `out` (which may be the same
+// buffer): one kernel where the shape allows it, which needs no work buffers.
+msx_status pass(msx_flow* f, bool inverse, int64_t n, const float* in, float* out, float* logdet, hipStream_t s) {
+    if (fused_ok(f)) {
+        FlowRun run{in, out, 0, logdet, n, inverse ? f->L - 1 : 0, inverse ? -1 : 1, f->L};
+        FHIP(f, launch_flow_layers(inverse, net_of(f), run, f->cu_count, s), "flow layers");
+        return MSX_OK;
+    }
+    if (msx_status st = ensure_work(f, n)) return st;
+    if (out != in)
+        FHIP(f, hipMemcpyAsync(out, in, sizeof(float) * (size_t)f->d * n, hipMemcpyDeviceToDevice, s), "flow copy");
+    FHIP(f, hipMemsetAsync(logdet, 0, sizeof(float) * n, s), "flow clear");
+    for (int i = 0; i < f->L; ++i) {
+        const int l = inverse ? f->L - 1 - i : i;
+        if (msx_status st = run_mlp(f, l, out, n, f->x0, f->h, f->theta, s)) return st;
+        FHIP(f, launch_spline(inverse, out, n, f->theta, f->n_out, f->nh, f->trans[l].data(), f->K, logdet, f->ldp, s),
+             "flow spline");
+    }
+    return MSX_OK;
+}
+
 msx_status check_events(msx_flow* f, int64_t n) {
     if (n < 0) return ffail(f, MSX_ERR_ARG, "n < 0");
     if (n > (int64_t)INT32_MAX) return ffail(f, MSX_ERR_ARG, "n exceeds 2^31 - 1 events per call");
@@ -337,6 +371,9 @@ msx_status msx_flow_create(int32_t dims, int32_t layers, int32_t bins, int32_t h
     if (hipSetDevice(device) != hipSuccess) return ffail(nullptr, MSX_ERR_DEVICE, "hipSetDevice failed");
     msx_flow* f = new msx_flow();
     f->device = device;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
+        f->cu_count = cus;
     f->d = dims;
     f->L = layers;
     f->K = bins;
@@ -509,28 +546,7 @@ msx_status msx_flow_forward(msx_flow* f, int64_t n, const float* u, float* y, fl
     if (!u || !y || !logdet) return ffail(f, MSX_ERR_ARG, "u, y and logdet are required");
     hipStream_t s = (hipStream_t)stream;
     FHIP(f, hipSetDevice(f->device), "hipSetDevice");
-    // whole layers in one kernel where the shape allows it (BF16, hidden 128,
-    // <= 16 bins, 16-byte aligned layer blocks); no work buffers then
-    const bool fused = fused_ok(f);
-    if (!fused)
-        if (msx_status st = ensure_work(f, n)) return st;
-    if (y != u) FHIP(f, hipMemcpyAsync(y, u, sizeof(float) * (size_t)f->d * n, hipMemcpyDeviceToDevice, s), "flow copy");
-    FHIP(f, hipMemsetAsync(logdet, 0, sizeof(float) * n, s), "flow clear");
-    for (int l = 0; l < f->L; ++l) {
-        if (fused) {
-            const int64_t base = l * f->per_layer;
-            FHIP(f,
-                 launch_flow_layer(false, y, n, tptr(f, f->params_t, l * f->per_layer_t), f->params + base, f->off,
-                                   f->nh, f->trans[l].data(), f->cond[l].data(), f->K, logdet, nullptr, nullptr,
-                                   nullptr, s),
-                 "flow layer");
-            continue;
-        }
-        if (msx_status st = run_mlp(f, l, y, n, f->x0, f->h, f->theta, s)) return st;
-        FHIP(f, launch_spline(false, y, n, f->theta, f->n_out, f->nh, f->trans[l].data(), f->K, logdet, f->ldp, s),
-             "flow spline");
-    }
-    return MSX_OK;
+    return pass(f, false, n, u, y, logdet, s);
 }
 
 msx_status msx_flow_inverse(msx_flow* f, int64_t n, const float* y, float* u, float* logq, void* stream) {
@@ -540,25 +556,7 @@ msx_status msx_flow_inverse(msx_flow* f, int64_t n, const float* y, float* u, fl
     if (!u || !y || !logq) return ffail(f, MSX_ERR_ARG, "y, u and logq are required");
     hipStream_t s = (hipStream_t)stream;
     FHIP(f, hipSetDevice(f->device), "hipSetDevice");
-    const bool fused = fused_ok(f);
-    if (!fused)
-        if (msx_status st = ensure_work(f, n)) return st;
-    if (y != u) FHIP(f, hipMemcpyAsync(u, y, sizeof(float) * (size_t)f->d * n, hipMemcpyDeviceToDevice, s), "flow copy");
-    FHIP(f, hipMemsetAsync(logq, 0, sizeof(float) * n, s), "flow clear");
-    for (int l = f->L - 1; l >= 0; --l) {
-        if (fused) {
-            FHIP(f,
-                 launch_flow_layer(true, u, n, tptr(f, f->params_t, l * f->per_layer_t),
-                                   f->params + (int64_t)l * f->per_layer, f->off, f->nh, f->trans[l].data(),
-                                   f->cond[l].data(), f->K, logq, nullptr, nullptr, nullptr, s),
-                 "flow layer");
-            continue;
-        }
-        if (msx_status st = run_mlp(f, l, u, n, f->x0, f->h, f->theta, s)) return st;
-        FHIP(f, launch_spline(true, u, n, f->theta, f->n_out, f->nh, f->trans[l].data(), f->K, logq, f->ldp, s),
-             "flow spline");
-    }
-    return MSX_OK;
+    return pass(f, true, n, y, u, logq, s);
 }
 
 msx_status msx_flow_gradient(msx_flow* f, int64_t n, const float* y, const double* wfj, const float* logq_old,

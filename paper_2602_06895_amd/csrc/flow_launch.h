@@ -55,6 +55,30 @@ hipError_t launch_flow_layer(bool inverse, float* z, int64_t n, const void* para
 constexpr int kFusedHidden = 128;
 constexpr int kFusedMaxBins = 16;
 
+// Parameters of a flow with such layers: the BF16 operand copy (layer blocks
+// of per_t elements, 16-byte aligned), the FP32 parameters (blocks of per),
+// and the offsets of W1 b1 W2 b2 W3 b3 W4 b4 in both.
+struct FlowNet {
+    const void* wt;
+    const float* p;
+    int32_t per_t, per;
+    int32_t off[8];
+    int32_t nh, K;
+};
+// A pass over `count` layers first, first + dir, ...: n events [d][n] from
+// zin; the i-th layer of the pass leaves its result in zout + i zstep (zstep
+// 0: one buffer, which may be zin).  logdet [n] receives the sum of the
+// layers' log-determinants.
+struct FlowRun {
+    const float* zin;
+    float* zout;
+    int64_t zstep;
+    float* logdet;
+    int64_t n;
+    int first, dir, count;
+};
+hipError_t launch_flow_layers(bool inverse, const FlowNet& fn, const FlowRun& run, int cu_count, hipStream_t s);
+
 // out[m][n] = sum_z part[z][m][n] in z order (out has leading dimension ldo).
 hipError_t launch_reduce_partials(const float* part, int splits, int M, int N, float* out, int64_t ldo,
                                   hipStream_t s);

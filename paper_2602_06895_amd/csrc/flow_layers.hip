@@ -1,0 +1,246 @@
+// Fused coupling layers of the flow on gfx950: conditioner on the matrix
+// cores and spline in one kernel, for all layers of a pass.
+#include <algorithm>
+
+#include "flow_layers.h"
+
+namespace msx {
+
+namespace {
+
+using namespace flow;
+
+// LDS of a workgroup with tiles of EV = 16 NT events: the output layer's
+// weights of `kept` coordinates, two activation tiles, two tiles of the
+// conditioning inputs and of the d coordinates, the log-determinant terms of
+// a tile.
+template <int NT>
+constexpr size_t layers_lds(int d, int kept) {
+    return sizeof(__bf16) * ((size_t)kept * kOutElems + 2 * 16 * NT * (kHid + kCond)) +
+           sizeof(float) * 16 * NT * (2 * (size_t)d + kWaves);
+}
+
+// One 128 -> 128 layer: the wave's 16 features of every event of the tile.
+template <int NT>
+__device__ __forceinline__ void hidden_layer(const bf16x8 (&w)[4], const floatx4& bias, const __bf16* in, __bf16* out,
+                                             int wave, int lane) {
+    bf16x8 x[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) load_act(in, 16 * t, lane, x[t]);
+    floatx4 acc[NT];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = mfma(w[s], x[t][s], s ? acc[t] : zero4());
+#pragma unroll
+    for (int t = 0; t < NT; ++t) store_act(acc[t], bias, out, 16 * t, wave, lane);
+}
+
+// All coupling layers of a pass, forward (sampling) or inverse (densities,
+// and the first half of training).  Workgroup b owns tiles b, b + grid, ...
+// of every layer and runs the layers one after the other over them, so the
+// events never meet another workgroup and one launch does the whole flow;
+// between layers z stays in memory (it comes back from the cache), within a
+// layer the weights stay on chip: the hidden layers' in registers, the output
+// layer's in LDS (KEEP: up to eight transformed coordinates).  A tile's
+// coordinates are in flight a tile earlier, its running log-determinant from
+// its start.
+//
+// What bounds it: per 64 events and layer each of the two waves of a SIMD
+// issues 690 vector instructions, most of them in the splines (32
+// exponentials, sums and knots per event and coordinate), and 100 MFMAs, a
+// quarter of them for the padding of 49 parameters to 64 rows; the vector
+// units are busy 60% of the time, the matrix units 27%, and what is left is
+// the latency of the three barriers and the LDS reads behind them.  Before, a
+// wave read every weight of a layer from L2 for its own 64 events and walked
+// each spline through LDS: 4583 us for eight layers of 2^20 events of 16
+// dimensions, now 2531 us; 1000 events of 10 dimensions 299 -> 66 us.  (Tried
+// and slower: the output weights in registers, 2850 us; two workgroups of
+// four waves per compute unit, 4240 us, and the splines of a tile interleaved
+// with the next tile's hidden layers, 2840 us, which both spill.)
+template <bool INV, int NT, bool KEEP, bool K16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_flow_layers(FlowNet fn,
+                                                                                                 FlowRun run) {
+    constexpr int EV = 16 * NT;
+    constexpr int ZR = 2;  // coordinates in flight per thread (all of a tile of 64 events up to 16 dimensions)
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int nh = fn.nh, d = 2 * nh, K = fn.K, P = 3 * K + 1;
+    __bf16* const w4 = (__bf16*)smem;                   // KEEP: [nh][kOutElems]
+    __bf16* const act = w4 + (KEEP ? nh * kOutElems : 0);  // [2][EV][kHid]
+    __bf16* const cond = act + 2 * EV * kHid;           // [2][EV][kCond]
+    float* const zs = (float*)(cond + 2 * EV * kCond);  // [2][d][EV]
+    float* const lds_ld = zs + 2 * d * EV;              // [kWaves][EV]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int e16 = lane & 15, q = lane >> 4;
+    const int ev = lane & (EV - 1);        // this lane's event of a tile in the splines
+    const bool mine = EV >= 64 || lane < EV;
+    const int64_t n = run.n, step = gridDim.x;
+    const int64_t tiles = (n + EV - 1) / EV;
+
+    for (int i = tid; i < 2 * EV * kCond; i += kThreads) cond[i] = (__bf16)0.0f;
+
+    for (int li = 0; li < run.count; ++li) {
+        const int layer = run.first + li * run.dir;
+        const Mask mk = mask_of(layer, nh);
+        const float* const zi = li == 0 ? run.zin : run.zout + (li - 1) * run.zstep;
+        float* const zo = run.zout + li * run.zstep;
+        const HidW hw = load_hidden(fn, layer, wave, lane);
+        const __bf16* const w4g = (const __bf16*)fn.wt + layer * fn.per_t + fn.off[6];
+        OutBias ob;
+        if (KEEP) {
+            ob = load_out_bias(fn, layer, min(wave, nh - 1), lane);
+            __syncthreads();  // the previous layer's readers of w4
+            load_out(fn, layer, w4, tid);
+        }
+        // staging of a tile: 64 / EV coordinates per wave and step, the lane's
+        // event (the last one again beyond the end)
+        float zr[ZR];
+        auto row_of = [&](int i) { return (wave + i * kWaves) * (64 / EV) + (EV < 64 ? lane / EV : 0); };
+        auto coord = [&](int i, uint32_t e) { return zi[(int64_t)min(row_of(i), d - 1) * n + e]; };
+        auto event_of = [&](int64_t tile) { return (uint32_t)min(tile * EV + ev, n - 1); };
+        auto put = [&](int buf, int i, float v) {
+            const int c = row_of(i), k = cond_index(mk, nh, c);
+            if (c >= d) return;
+            zs[(buf * d + c) * EV + ev] = v;
+            if (k >= 0) cond[cond_chunk(buf * EV + ev, k >> 3) + (k & 7)] = (__bf16)v;
+        };
+        auto fetch = [&](int64_t tile) {
+            const uint32_t e = event_of(tile);
+#pragma unroll
+            for (int i = 0; i < ZR; ++i) zr[i] = coord(i, e);
+        };
+        auto stage = [&](int buf, int64_t tile) {
+#pragma unroll
+            for (int i = 0; i < ZR; ++i) put(buf, i, zr[i]);
+            for (int i = ZR; i * kWaves * (64 / EV) < d; ++i) put(buf, i, coord(i, event_of(tile)));
+        };
+        // log-determinants: the sum over the layers before, and the new sum with
+        // the coordinates' terms added in order
+        auto before = [&](int64_t tile) {
+            return li > 0 && tid < EV ? run.logdet[min(tile * EV + tid, n - 1)] : 0.0f;
+        };
+        auto flush = [&](int64_t tile, float old) {
+            if (tid < EV && tile * EV + tid < n) {
+                float s = 0.0f;
+                for (int w = 0; w < min(kWaves, nh); ++w) s += lds_ld[w * EV + tid];
+                run.logdet[tile * EV + tid] = old + s;
+            }
+        };
+        // the spline parameters of coordinate j from the last activation
+        auto output = [&](const __bf16* a, int j) {
+            floatx4 acc[NT][4];
+            bf16x8 x[NT][4];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) load_act(a, 16 * t, lane, x[t]);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int row = j * P + param_row(m, e16, K);
+                bf16x8 w[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    w[s] = KEEP ? out_fragment(w4, j, m, s, lane)
+                                : *(const bf16x8*)&w4g[row * kHid + 32 * s + 8 * q];
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[t][m] = mfma(w[s], x[t][s], s ? acc[t][m] : zero4());
+            }
+            if (!KEEP) ob = load_out_bias(fn, layer, j, lane);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) acc[t][m] += ob.b[m];
+            return gather_theta<NT>(acc);
+        };
+        // the previous layer's stores to z, and its last readers of LDS
+        __syncthreads();
+        fetch(blockIdx.x);
+        stage(0, blockIdx.x);
+        fetch(blockIdx.x + step);
+        __syncthreads();
+        int buf = 0, pa = 0;
+        int64_t prev = -1;
+        float old = 0.0f;
+        for (int64_t tile = blockIdx.x; tile < tiles; tile += step) {
+            const float* zt = zs + buf * d * EV;
+            __bf16* const a0 = act + pa * EV * kHid;
+            __bf16* const a1 = act + (pa ^ 1) * EV * kHid;
+            const float old_next = before(tile);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                store_act(mfma(hw.w1, *(const bf16x8*)&cond[cond_chunk(buf * EV + 16 * t + e16, q)], zero4()),
+                          hw.b1, a0, 16 * t, wave, lane);
+            __syncthreads();
+            if (prev >= 0) flush(prev, old);
+            old = old_next;
+            hidden_layer<NT>(hw.w2, hw.b2, a0, a1, wave, lane);
+            __syncthreads();
+            hidden_layer<NT>(hw.w3, hw.b3, a1, a0, wave, lane);
+            stage(buf ^ 1, tile + step);
+            fetch(tile + 2 * step);
+            __syncthreads();
+            float ld_sum = 0.0f;
+            for (int j = wave; j < nh; j += KEEP ? 2 * kFlowMaxHalf : kWaves) {
+                const int tj = mk.t0 + mk.ts * j;
+                Theta th = output(a0, j);
+                const float vin = zt[tj * EV + ev];
+                float sw, sh, ld;
+                spline_exp<K16>(th, K, sw, sh);
+                Bin b = spline_find<INV, K16>(th, K, vin, sw, sh);
+                spline_slopes(b);
+                const float v = spline_value<INV>(b, vin, ld);
+                const int64_t e = tile * EV + ev;
+                if (mine && e < n) zo[(int64_t)tj * n + e] = v;
+                ld_sum += ld;
+            }
+            if (mine) lds_ld[wave * EV + ev] = ld_sum;
+            if (zi != zo) {
+                // a new buffer: the conditioning coordinates go along
+                const int64_t ec = tile * EV + ev;
+                for (int i = 0; i * kWaves * (64 / EV) < nh; ++i) {
+                    const int c = mk.c0 + mk.cs * row_of(i);
+                    if (row_of(i) < nh && ec < n) zo[(int64_t)c * n + ec] = zt[c * EV + ev];
+                }
+            }
+            prev = tile;
+            buf ^= 1;
+            pa ^= 1;
+        }
+        __syncthreads();
+        flush(prev, old);
+    }
+}
+
+template <bool INV, int NT>
+hipError_t launch_layers(const FlowNet& fn, const FlowRun& run, int64_t grid, hipStream_t s) {
+    const bool keep = fn.nh <= kWaves;  // then W4 fits in LDS: at most 98 KiB
+    const size_t lds = layers_lds<NT>(2 * fn.nh, keep ? fn.nh : 0);
+    const dim3 g((unsigned)grid), t(kThreads);
+    if (keep && fn.K == 16)
+        k_flow_layers<INV, NT, true, true><<<g, t, lds, s>>>(fn, run);
+    else if (keep)
+        k_flow_layers<INV, NT, true, false><<<g, t, lds, s>>>(fn, run);
+    else if (fn.K == 16)
+        k_flow_layers<INV, NT, false, true><<<g, t, lds, s>>>(fn, run);
+    else
+        k_flow_layers<INV, NT, false, false><<<g, t, lds, s>>>(fn, run);
+    return hipGetLastError();
+}
+
+template <bool INV>
+hipError_t launch_pass(const FlowNet& fn, const FlowRun& run, int cu_count, hipStream_t s) {
+    const int64_t t16 = (run.n + 15) / 16;
+    // up to one tile of 16 events for every compute unit the time is the
+    // latency of a tile through the layers, which grows with the tile
+    if (t16 <= cu_count) return launch_layers<INV, 1>(fn, run, t16, s);
+    return launch_layers<INV, 4>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
+}
+
+}  // namespace
+
+hipError_t launch_flow_layers(bool inverse, const FlowNet& fn, const FlowRun& run, int cu_count, hipStream_t s) {
+    if (run.n == 0) return hipSuccess;
+    return inverse ? launch_pass<true>(fn, run, cu_count, s) : launch_pass<false>(fn, run, cu_count, s);
+}
+
+}  // namespace msx

@@ -1,0 +1,73 @@
+"""The fused coupling layers (BF16, hidden width 128, up to 16 bins) over the
+shapes where their split of the work changes: event counts around a tile of 16
+and of 64 events and around one tile per compute unit, one to 32 transformed
+coordinates (fewer than, as many as, and more than a workgroup's waves), bin
+counts with and without padding."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import flow as F
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+
+    if not t.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return t
+
+
+def _pair(d, layers, bins, seed, scale=0.05):
+    import torch as t
+
+    from paper_2602_06895_amd import FLOW_BF16, Flow
+
+    params = W.flow_params(seed, d, layers, bins, 128, last_scale=scale)
+    f = Flow(d, layers, bins, 128, mlp=FLOW_BF16)
+    f.set_params(params)
+    return f, F.Flow(d, layers, bins, 128, params=t.as_tensor(params.astype(np.float64)), bf16_mlp=True)
+
+
+SHAPES = [(16, 5, 16, 1), (16, 4, 16, 15), (16, 4, 16, 16), (16, 4, 16, 17), (10, 4, 16, 1000), (16, 2, 16, 4096),
+          (16, 2, 16, 4097), (14, 2, 16, 16385), (2, 3, 16, 100), (18, 2, 16, 4200), (64, 2, 16, 300),
+          (64, 2, 12, 4160), (16, 4, 1, 70), (16, 2, 2, 5000), (10, 2, 15, 70), (18, 2, 5, 90)]
+
+
+@pytest.mark.parametrize("d,layers,bins,n", SHAPES)
+def test_passes_match_oracle(torch, d, layers, bins, n):
+    """Forward and inverse against the oracle with BF16 conditioner roundings;
+    bounds: one BF16 rounding decision taken the other way on an FP32
+    accumulator, as for the full-size flows."""
+    f, orc = _pair(d, layers, bins, 10 * d + bins)
+    u = W.philox_uniforms_f32(3, d, 0, n, d)
+    t = torch.from_numpy(u).cuda()
+    y, ld = f.forward(t)
+    x, lq = f.inverse(t)
+    torch.cuda.synchronize()
+    ref = torch.from_numpy(u.T.astype(np.float64))
+    for got, gl, (want, wl) in ((y, ld, orc.forward(ref)), (x, lq, orc.inverse(ref))):
+        assert np.abs(got.cpu().numpy().T - want.numpy()).max() < 2e-3
+        assert np.abs(gl.cpu().numpy() - wl.numpy()).max() < 2e-2
+    f.close()
+
+
+@pytest.mark.parametrize("d,n", [(16, 100), (16, 9001), (24, 5000)])
+def test_passes_in_place_and_split(torch, d, n):
+    """A pass over its own buffer, and over the two halves of a batch: the same
+    bits (no event meets another)."""
+    f, _ = _pair(d, 5, 16, 77)
+    u = torch.from_numpy(W.philox_uniforms_f32(4, 1, 0, n, d)).cuda()
+    for name in ("forward", "inverse"):
+        v, ld = getattr(f, name)(u)
+        w, lw = u.clone(), torch.empty(n, dtype=torch.float32, device="cuda")
+        f._check(getattr(f.L, "msx_flow_" + name)(f.h, n, w.data_ptr(), w.data_ptr(), lw.data_ptr(), f._stream()))
+        assert torch.equal(w, v) and torch.equal(lw, ld)
+        k = n // 2 + 3
+        parts = [getattr(f, name)(p.contiguous()) for p in (u[:, :k], u[:, k:])]
+        assert torch.equal(torch.cat([p[0] for p in parts], 1), v)
+        assert torch.equal(torch.cat([p[1] for p in parts]), ld)
+    f.close()
