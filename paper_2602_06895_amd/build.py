@@ -14,7 +14,8 @@ LIB = os.path.join(HERE, "libmsx.so")
 # the six chain_*.hip units (register class x precision) are the slow ones and
 # compile in parallel with the rest
 SOURCES = ["chain_f64_l.hip", "chain_f64_m.hip", "chain_f64_s.hip", "chain_mix_l.hip", "chain_mix_m.hip",
-           "chain_mix_s.hip", "kernels.hip", "flow_kernels.hip", "flow_layers.hip", "api.cpp", "flow_api.cpp", "compiler.cpp",
+           "chain_mix_s.hip", "kernels.hip", "flow_kernels.hip", "flow_layers.hip", "flow_train.hip",
+           "api.cpp", "flow_api.cpp", "compiler.cpp",
            "json.cpp", "jit.cpp", "inverse_s.hip", "inverse_m.hip", "inverse_l.hip"]
 # headers of the fused sample kernel, compiled again at run time for a
 # context's channels (jit.cpp); their text goes into the library

@@ -32,7 +32,7 @@ struct msx_flow {
     int64_t adam_t = 0;
     // work buffers, grown on demand
     int64_t cap = 0;
-    float* z = nullptr;      // [(L + 1)][d][cap]
+    float* z = nullptr;      // [(L + 1)][d][cap]; fused layers: [L][d][cap], last layer's output first
     void* x0 = nullptr;      // [L][cap][nh]
     void* h = nullptr;       // [L][3][cap][H]
     float* theta = nullptr;  // [L][cap][n_out]
@@ -44,6 +44,14 @@ struct msx_flow {
     float* dx0 = nullptr;    // [cap][nh]
     float* adj = nullptr;    // [d][cap]
     float* ldp = nullptr;    // [nh][cap] per-coordinate log-det terms
+    // reverse mode of fused layers (one layer at a time, see FlowRev); these
+    // take the place of x0, h, theta, dtheta, dha, dhb, dx0 and ldp
+    __bf16* rx0 = nullptr;
+    __bf16* rh = nullptr;
+    __bf16* rd = nullptr;
+    __bf16* rdh = nullptr;
+    __bf16* wt_t = nullptr;  // [L][flow_transposed_elems]
+    uint16_t* ron = nullptr;
     float* part = nullptr;   // split-K partials
     int64_t part_cap = 0;
     double* lpart = nullptr;  // loss partials (1024) + loss (1)
@@ -101,6 +109,14 @@ void free_work(msx_flow* f) {
     ffree(f->dx0);
     ffree(f->adj);
     ffree(f->ldp);
+    ffree(f->rx0);
+    ffree(f->rh);
+    ffree(f->rd);
+    ffree(f->rdh);
+    ffree(f->wt_t);
+    ffree(f->ron);
+    f->rx0 = f->rh = f->rd = f->rdh = f->wt_t = nullptr;
+    f->ron = nullptr;
     f->ldp = nullptr;
     f->z = nullptr;
     f->x0 = f->h = f->dtheta = f->dha = f->dhb = nullptr;
@@ -108,12 +124,34 @@ void free_work(msx_flow* f) {
     f->cap = 0;
 }
 
-// Work buffers for n events (all layers kept, as the reverse pass needs them).
+// The fused coupling layers cover BF16 conditioners of hidden width 128
+// with up to 16 bins.
+bool fused_ok(const msx_flow* f) {
+    return f->type == FT_BF16 && f->H == kFusedHidden && f->K <= kFusedMaxBins;
+}
+
+// Work buffers for n events: the intermediates of all layers, which the reverse
+// pass needs; of fused layers only their coordinates, the rest is recomputed.
 msx_status ensure_work(msx_flow* f, int64_t n) {
     if (n <= f->cap) return MSX_OK;
     free_work(f);
     const size_t ts = tsize(f->type);
     const size_t N = (size_t)n;
+    if (fused_ok(f)) {
+        const size_t tiles = (N + 63) / 64, block = 2 * 32 * sizeof(__bf16);  // bytes per row and tile
+        FHIP(f, fmalloc(&f->z, sizeof(float) * (size_t)f->L * f->d * N), "flow work");
+        FHIP(f, fmalloc(&f->logq, sizeof(float) * N), "flow work");
+        FHIP(f, fmalloc(&f->G, sizeof(float) * N), "flow work");
+        FHIP(f, fmalloc(&f->adj, sizeof(float) * (size_t)f->d * N), "flow work");
+        FHIP(f, fmalloc(&f->rx0, block * 32 * tiles), "flow work");
+        FHIP(f, fmalloc(&f->rh, block * 3 * f->H * tiles), "flow work");
+        FHIP(f, fmalloc(&f->rd, block * flow_grad_rows(f->nh, f->K) * tiles), "flow work");
+        FHIP(f, fmalloc(&f->rdh, block * 3 * f->H * tiles), "flow work");
+        FHIP(f, fmalloc(&f->ron, sizeof(uint16_t) * 3 * 512 * tiles), "flow work");
+        FHIP(f, fmalloc(&f->wt_t, sizeof(__bf16) * f->L * flow_transposed_elems(f->nh)), "flow work");
+        f->cap = n;
+        return MSX_OK;
+    }
     FHIP(f, fmalloc(&f->z, sizeof(float) * (size_t)(f->L + 1) * f->d * N), "flow work");
     FHIP(f, fmalloc(&f->x0, ts * (size_t)f->L * N * f->nh), "flow work");
     FHIP(f, fmalloc(&f->h, ts * (size_t)f->L * 3 * N * f->H), "flow work");
@@ -232,12 +270,6 @@ FlowNet net_of(const msx_flow* f) {
     return n;
 }
 
-// The fused coupling layers cover BF16 conditioners of hidden width 128
-// with up to 16 bins.
-bool fused_ok(const msx_flow* f) {
-    return f->type == FT_BF16 && f->H == kFusedHidden && f->K <= kFusedMaxBins;
-}
-
 // Inverse pass over all layers keeping every intermediate: z[L] = y, z[l] =
 // layer l inverted from z[l + 1]; logq accumulates log |du/dy|.
 msx_status inverse_saving(msx_flow* f, int64_t n, const float* y, hipStream_t s) {
@@ -251,15 +283,6 @@ msx_status inverse_saving(msx_flow* f, int64_t n, const float* y, hipStream_t s)
         void* x0 = tptr(f, f->x0, (int64_t)l * n * f->nh);
         void* h = tptr(f, f->h, (int64_t)l * 3 * n * f->H);
         float* th = f->theta + (size_t)l * n * f->n_out;
-        if (fused_ok(f)) {
-            FHIP(f, hipMemcpyAsync(zout, zin, sizeof(float) * zs, hipMemcpyDeviceToDevice, s), "flow copy");
-            FHIP(f,
-                 launch_flow_layer(true, zout, n, tptr(f, f->params_t, l * f->per_layer_t),
-                                   f->params + (int64_t)l * f->per_layer, f->off, f->nh, f->trans[l].data(),
-                                   f->cond[l].data(), f->K, f->logq, x0, h, th, s),
-                 "flow layer");
-            continue;
-        }
         if (msx_status st = run_mlp(f, l, zin, n, x0, h, th, s)) return st;
         FHIP(f, hipMemcpyAsync(zout, zin, sizeof(float) * zs, hipMemcpyDeviceToDevice, s), "flow copy");
         FHIP(f, launch_spline(true, zout, n, th, f->n_out, f->nh, f->trans[l].data(), f->K, f->logq, f->ldp, s),
@@ -268,10 +291,45 @@ msx_status inverse_saving(msx_flow* f, int64_t n, const float* y, hipStream_t s)
     return MSX_OK;
 }
 
+// The gradient through fused layers: the inverse pass keeps the coordinates
+// after every layer, and the reverse pass recomputes the rest layer by layer.
+msx_status gradient_fused(msx_flow* f, int64_t n, const float* y, const double* wfj, const float* logq_old,
+                          float* grad, double* loss, bool log_loss, hipStream_t s) {
+    const FlowNet fn = net_of(f);
+    const int64_t zs = (int64_t)f->d * n;
+    const int splits = flow_wgrad_splits(n);
+    if (msx_status st = ensure_part(f, splits * f->per_layer)) return st;
+    FHIP(f, launch_flow_layers(true, fn, FlowRun{y, f->z, zs, f->logq, n, f->L - 1, -1, f->L}, f->cu_count, s),
+         "flow layers");
+    FHIP(f, launch_flow_loss(n, wfj, f->logq, logq_old, f->G, f->lpart, loss, log_loss, s), "flow loss");
+    FHIP(f, launch_flow_transpose(fn, f->L, f->wt_t, s), "flow transpose");
+    FlowRev r{};
+    r.adj = f->adj;
+    r.G = f->G;
+    r.x0 = f->rx0;
+    r.h = f->rh;
+    r.on = f->ron;
+    r.d = f->rd;
+    r.dh = f->rdh;
+    r.n = n;
+    for (int l = 0; l < f->L; ++l) {
+        r.zin = l == f->L - 1 ? y : f->z + (f->L - 2 - l) * zs;
+        r.layer = l;
+        r.first = l == 0;
+        FHIP(f, launch_flow_spline_reverse(fn, r, f->cu_count, s), "flow spline reverse");
+        FHIP(f, launch_flow_mlp_reverse(fn, r, f->wt_t, f->cu_count, s), "flow conditioner reverse");
+        FHIP(f, launch_flow_wgrad(fn, r, splits, f->part, s), "flow weight gradients");
+        FHIP(f, launch_reduce_partials(f->part, splits, 1, (int)f->per_layer, grad + l * f->per_layer, f->per_layer, s),
+             "flow reduce");
+    }
+    return MSX_OK;
+}
+
 msx_status gradient(msx_flow* f, int64_t n, const float* y, const double* wfj, const float* logq_old, float* grad,
                     double* loss, bool log_loss, hipStream_t s) {
     if (msx_status st = ensure_work(f, n)) return st;
     if (!f->lpart) FHIP(f, fmalloc(&f->lpart, sizeof(double) * 1025), "flow loss partials");
+    if (fused_ok(f)) return gradient_fused(f, n, y, wfj, logq_old, grad, loss ? loss : f->lpart + 1024, log_loss, s);
     if (msx_status st = inverse_saving(f, n, y, s)) return st;
     FHIP(f, launch_flow_loss(n, wfj, f->logq, logq_old, f->G, f->lpart, loss ? loss : f->lpart + 1024, log_loss, s),
          "flow loss");

@@ -14,6 +14,7 @@
 
 #include "chain.h"
 #include "device_util.h"
+#include "flow_adjoint.h"
 #include "flow_launch.h"
 
 namespace msx {
@@ -512,76 +513,6 @@ __global__ __launch_bounds__(256) void k_ld_add(const float* __restrict__ ldp, i
     logdet[e] += ld;
 }
 
-// Forward-mode dual numbers with 7 tangents: (y, x0, w, y0, h, d0, d1).
-struct D7 {
-    float v;
-    float g[7];
-};
-__device__ __forceinline__ D7 dconst(float v) {
-    D7 r;
-    r.v = v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = 0.0f;
-    return r;
-}
-__device__ __forceinline__ D7 dvar(float v, int i) {
-    D7 r = dconst(v);
-    r.g[i] = 1.0f;
-    return r;
-}
-__device__ __forceinline__ D7 operator+(const D7& a, const D7& b) {
-    D7 r;
-    r.v = a.v + b.v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = a.g[i] + b.g[i];
-    return r;
-}
-__device__ __forceinline__ D7 operator-(const D7& a, const D7& b) {
-    D7 r;
-    r.v = a.v - b.v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = a.g[i] - b.g[i];
-    return r;
-}
-__device__ __forceinline__ D7 operator*(const D7& a, const D7& b) {
-    D7 r;
-    r.v = a.v * b.v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = a.g[i] * b.v + a.v * b.g[i];
-    return r;
-}
-__device__ __forceinline__ D7 operator*(float a, const D7& b) {
-    D7 r;
-    r.v = a * b.v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = a * b.g[i];
-    return r;
-}
-__device__ __forceinline__ D7 operator/(const D7& a, const D7& b) {
-    D7 r;
-    const float ib = 1.0f / b.v;
-    r.v = a.v * ib;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = (a.g[i] - r.v * b.g[i]) * ib;
-    return r;
-}
-__device__ __forceinline__ D7 dsqrt(const D7& a) {
-    D7 r;
-    r.v = sqrtf(a.v);
-    const float c = 0.5f / r.v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = a.g[i] * c;
-    return r;
-}
-__device__ __forceinline__ D7 dlog(const D7& a) {
-    D7 r;
-    r.v = logf(a.v);
-    const float c = 1.0f / a.v;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) r.g[i] = a.g[i] * c;
-    return r;
-}
-
 // Reverse mode through the inverse spline of one layer (see flow_launch.h).
 // The parameter slab comes in through LDS and the parameter gradients go out
 // through a second LDS slab with coalesced stores.
@@ -603,27 +534,8 @@ __device__ __forceinline__ void spline_backward_one(const float* th, int K, floa
     }
     auto pw_of = [&](int i) -> float { return KS > 0 ? ewk[i] / sw : expf(th[i] - mw) / sw; };
     auto ph_of = [&](int i) -> float { return KS > 0 ? ehk[i] / sh : expf(th[K + i] - mh) / sh; };
-    // x = S^-1(y) and ld = log (S^-1)'(y) = -log S'(x) as duals
-    const D7 Y = dvar(v, 0), X0 = dvar(bn.x0, 1), W = dvar(bn.w, 2), Y0 = dvar(bn.y0, 3), H = dvar(bn.h, 4),
-             Dd0 = dvar(bn.d0, 5), Dd1 = dvar(bn.d1, 6);
-    const D7 s = H / W;
-    const D7 dy = Y - Y0;
-    const D7 kap = Dd1 + Dd0 - 2.0f * s;
-    const D7 qa = H * (s - Dd0) + dy * kap;
-    const D7 qb = H * Dd0 - dy * kap;
-    const D7 qc = dconst(0.0f) - s * dy;
-    D7 disc = qb * qb - 4.0f * (qa * qc);
-    disc.v = fmaxf(disc.v, 1e-30f);
-    const D7 xi = (2.0f * qc) / (dconst(0.0f) - qb - dsqrt(disc));
-    const D7 X = X0 + xi * W;
-    const D7 om = xi * (dconst(1.0f) - xi);
-    const D7 den = s + kap * om;
-    const D7 omx = dconst(1.0f) - xi;
-    const D7 num = s * s * (Dd1 * xi * xi + 2.0f * (s * om) + Dd0 * omx * omx);
-    const D7 ld = 2.0f * dlog(den) - dlog(num);
     float gp[7];
-#pragma unroll
-    for (int i = 0; i < 7; ++i) gp[i] = ax * X.g[i] + ge * ld.g[i];
+    spline_inverse_adjoint(v, bn.w, bn.y0, bn.h, bn.d0, bn.d1, ge, ax, gp);
     ax = gp[0];
     // to the unconstrained parameters: softmax of widths / heights, softplus of slopes
     const float Cw = 1.0f - K * kMinW, Ch = 1.0f - K * kMinH;
@@ -639,8 +551,8 @@ __device__ __forceinline__ void spline_backward_one(const float* th, int K, floa
         pwk = pw_of(bn.k);
         phk = ph_of(bn.k);
     }
-    const float sumw = gp[1] * bn.pw + gp[2] * pwk;
-    const float sumh = gp[3] * bn.ph + gp[4] * phk;
+    const float sumw = __builtin_fmaf(gp[1], bn.pw, gp[2] * pwk);
+    const float sumh = __builtin_fmaf(gp[3], bn.ph, gp[4] * phk);
 #pragma unroll
     for (int i = 0; i < (KS > 0 ? KS : K); ++i) {
         const float pwi = pw_of(i), phi = ph_of(i);
@@ -798,228 +710,6 @@ __global__ __launch_bounds__(256) void k_flow_weight(int64_t n, const double* __
     if (logq) logq[i] = -ld;
 }
 
-// ---------------------------------------------------------------------------
-// Fused forward coupling layer (BF16 conditioner of hidden width 128).  Each
-// wave takes 64 events.  Their conditioning coordinates are gathered straight
-// into MFMA operand fragments; the hidden layers run on the matrix cores with
-// the weight fragments read from L2 (about 2 KB per event and layer) and the
-// activations passed through a per-wave LDS tile, which also turns the MFMA
-// output layout (4 rows of one column per lane) into the operand layout (8 k
-// of one row per lane).  The last layer produces the 3K + 1 spline
-// parameters of one transformed coordinate at a time into LDS, where each of
-// the 64 lanes evaluates the spline of its own event.  Per event only z and
-// the log-determinant touch HBM.
-// ---------------------------------------------------------------------------
-constexpr int kFH = 128;                 // hidden width of the fused path
-constexpr int kFW = 2;                   // waves per workgroup
-constexpr int kFRow = kFH + 8;           // LDS row of an activation tile (bf16)
-constexpr int kFStage = 64 * kFRow;      // bf16 elements per wave (>= 64 x 49 floats)
-
-struct FusedW {
-    const __bf16* w1;  // [128][nh]
-    const __bf16* w2;  // [128][128]
-    const __bf16* w3;  // [128][128]
-    const __bf16* w4;  // [n_out][128]
-    const float* b1;
-    const float* b2;
-    const float* b3;
-    const float* b4;
-};
-
-// acc (16 events x 16 columns per tile t) + bias, ReLU, BF16 -> activation tile
-__device__ __forceinline__ void hidden_epilogue(const floatx4 (&acc)[4], const float* __restrict__ b, int c, int lane,
-                                                __bf16* __restrict__ st) {
-    const int r16 = lane & 15, kq = lane >> 4;
-    const float bias = b[16 * c + r16];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            st[(16 * t + 4 * kq + e) * kFRow + 16 * c + r16] = (__bf16)fmaxf(acc[t][e] + bias, 0.0f);
-}
-
-// 128 -> 128 layer from the activation tile in LDS back into it
-__device__ __forceinline__ void hidden_layer(const __bf16* __restrict__ Wl, const float* __restrict__ bl, int lane,
-                                             __bf16* __restrict__ st) {
-    const int r16 = lane & 15, kq = lane >> 4;
-    bf16x8 a[4][4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) a[t][s4] = *(const bf16x8*)&st[(16 * t + r16) * kFRow + 32 * s4 + 8 * kq];
-    __syncthreads();  // the tile is overwritten below
-    // weight fragments of the next column tile are in flight while this
-    // tile's MFMAs run
-    bf16x8 bn[4];
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) bn[s4] = *(const bf16x8*)&Wl[r16 * kFH + 32 * s4 + 8 * kq];
-#pragma unroll 2
-    for (int c = 0; c < kFH / 16; ++c) {
-        bf16x8 b[4];
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) b[s4] = bn[s4];
-        if (c + 1 < kFH / 16) {
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4)
-                bn[s4] = *(const bf16x8*)&Wl[(16 * (c + 1) + r16) * kFH + 32 * s4 + 8 * kq];
-        }
-        floatx4 acc[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            acc[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][s4], b[s4], acc[t], 0, 0, 0);
-        }
-        hidden_epilogue(acc, bl, c, lane, st);
-    }
-    __syncthreads();
-}
-
-// What the reverse pass of training reads, written by the fused inverse
-// layer when the pointers are set: the BF16 conditioning inputs x0 [n][nh],
-// the hidden activations h [3][n][128] and the spline parameters theta
-// [n][n_out] (FP32), the same values the unfused path stores.
-struct FusedSave {
-    __bf16* x0;
-    __bf16* h;
-    float* theta;
-};
-
-// Copy a wave's 64 x 128 activation tile to h[e0 ..][128] (16-byte stores).
-__device__ __forceinline__ void save_tile(const __bf16* __restrict__ st, __bf16* __restrict__ h, int64_t e0,
-                                          int64_t n, int lane) {
-#pragma unroll
-    for (int it = 0; it < 16; ++it) {
-        const int idx = it * 64 + lane;        // 16-byte chunk: row idx / 16, column block idx % 16
-        const int r = idx >> 4, cb = (idx & 15) * 8;
-        if (e0 + r < n) *(uint4*)&h[(e0 + r) * kFH + cb] = *(const uint4*)&st[r * kFRow + cb];
-    }
-}
-
-template <bool INV, bool SAVE>
-__global__ __launch_bounds__(64 * kFW) void k_flow_layer(float* __restrict__ z, int64_t n, FusedW fw, int nh,
-                                                         Idx trans, Idx cond, int K, float* __restrict__ logdet,
-                                                         FusedSave sv) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char fsm[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r16 = lane & 15, kq = lane >> 4;
-    __bf16* st = (__bf16*)fsm + (size_t)wave * kFStage;
-    float* th = (float*)st;
-    const int64_t e0 = ((int64_t)blockIdx.x * kFW + wave) * 64;
-    const int P = 3 * K + 1;
-    const int n_out = nh * P;
-
-    // layer 1: A fragments = BF16 conditioning coordinates (k = 8 kq + i < nh)
-    bf16x8 a1[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int k = 8 * kq + i;
-        const int ci = kq == 0 ? cond.v[i] : (kq == 1 ? cond.v[8 + i] : (kq == 2 ? cond.v[16 + i] : cond.v[24 + i]));
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int64_t e = e0 + 16 * t + r16;
-            a1[t][i] = (__bf16)((k < nh && e < n) ? z[(int64_t)ci * n + e] : 0.0f);
-            if (SAVE && k < nh && e < n) sv.x0[e * nh + k] = a1[t][i];
-        }
-    }
-#pragma unroll 2
-    for (int c = 0; c < kFH / 16; ++c) {
-        bf16x8 b;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int k = 8 * kq + i;
-            b[i] = k < nh ? fw.w1[(16 * c + r16) * nh + k] : (__bf16)0.0f;
-        }
-        floatx4 acc[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[t], b, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
-        hidden_epilogue(acc, fw.b1, c, lane, st);
-    }
-    __syncthreads();
-    if (SAVE) save_tile(st, sv.h, e0, n, lane);
-    hidden_layer(fw.w2, fw.b2, lane, st);
-    if (SAVE) save_tile(st, sv.h + n * kFH, e0, n, lane);
-    hidden_layer(fw.w3, fw.b3, lane, st);
-    if (SAVE) save_tile(st, sv.h + 2 * n * kFH, e0, n, lane);
-
-    // last layer, one transformed coordinate at a time, then its spline
-    bf16x8 a3[4][4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) a3[t][s4] = *(const bf16x8*)&st[(16 * t + r16) * kFRow + 32 * s4 + 8 * kq];
-    __syncthreads();
-    const int64_t e = e0 + lane;
-    const bool active = e < n;
-    float ld = 0.0f;
-    for (int j = 0; j < nh; ++j) {
-#pragma unroll 2
-        for (int c = 0; c < (P + 15) / 16; ++c) {
-            const int q = 16 * c + r16;          // parameter within the coordinate
-            const int row = j * P + q;           // row of W4 / column of theta
-            const bool ok = q < P && row < n_out;
-            bf16x8 b[4];
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) {
-                if (ok) {
-                    b[s4] = *(const bf16x8*)&fw.w4[(int64_t)row * kFH + 32 * s4 + 8 * kq];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) b[s4][i] = (__bf16)0.0f;
-                }
-            }
-            const float bias = ok ? fw.b4[row] : 0.0f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                floatx4 acc = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int s4 = 0; s4 < 4; ++s4) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3[t][s4], b[s4], acc, 0, 0, 0);
-                if (ok) {
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const int r = 16 * t + 4 * kq + x;
-                        th[r * P + q] = acc[x] + bias;
-                        if (SAVE && e0 + r < n) sv.theta[(e0 + r) * n_out + row] = acc[x] + bias;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (active) {
-            float* zp = z + (int64_t)trans.v[j] * n + e;
-            const float v = *zp;
-            Bin bn;
-            if (K == 16) {
-                bn = spline_bin_k<INV, 16>(th + lane * P, v);
-            } else {
-                float mw, sw, mh, sh;
-                bn = spline_bin<INV>(th + lane * P, K, v, mw, sw, mh, sh);
-            }
-            const float sl = bn.h / bn.w;
-            const float kap = bn.d1 + bn.d0 - 2.0f * sl;
-            if (!INV) {
-                const float xi = (v - bn.x0) / bn.w;
-                const float om = xi * (1.0f - xi);
-                *zp = bn.y0 + bn.h * (sl * xi * xi + bn.d0 * om) / (sl + kap * om);
-                ld += logf(spline_slope(bn, xi));
-            } else {
-                // the same root as the unfused inverse spline
-                const float dy = v - bn.y0;
-                const float qa = bn.h * (sl - bn.d0) + dy * kap;
-                const float qb = bn.h * bn.d0 - dy * kap;
-                const float qc = -sl * dy;
-                const float disc = fmaxf(qb * qb - 4.0f * qa * qc, 0.0f);
-                const float xi = 2.0f * qc / (-qb - sqrtf(disc));
-                *zp = bn.x0 + xi * bn.w;
-                ld += -logf(spline_slope(bn, xi));
-            }
-        }
-        __syncthreads();
-    }
-    if (active) logdet[e] += ld;
-}
-
 unsigned blocks(int64_t n) {
     return (unsigned)std::max<int64_t>(1, (n + 255) / 256);
 }
@@ -1045,36 +735,6 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
         k_gemm<__bf16><<<grid, GT, 0, s>>>(g, kchunk);
     else
         k_gemm<float><<<grid, GT, 0, s>>>(g, kchunk);
-    return hipGetLastError();
-}
-
-hipError_t launch_flow_layer(bool inverse, float* z, int64_t n, const void* params_t, const float* params,
-                             const int64_t* off, int nh, const int32_t* trans_host, const int32_t* cond_host, int K,
-                             float* logdet, void* save_x0, void* save_h, float* save_theta, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    FusedW fw;
-    const __bf16* W = (const __bf16*)params_t;
-    fw.w1 = W + off[0];
-    fw.b1 = params + off[1];
-    fw.w2 = W + off[2];
-    fw.b2 = params + off[3];
-    fw.w3 = W + off[4];
-    fw.b3 = params + off[5];
-    fw.w4 = W + off[6];
-    fw.b4 = params + off[7];
-    const unsigned nb = (unsigned)((n + 64 * kFW - 1) / (64 * kFW));
-    const size_t lds = sizeof(__bf16) * kFStage * kFW;
-    FusedSave sv{(__bf16*)save_x0, (__bf16*)save_h, save_theta};
-    const bool save = save_x0 && save_h && save_theta;
-    const Idx ti = make_idx(trans_host, nh), ci = make_idx(cond_host, nh);
-    if (inverse && save)
-        k_flow_layer<true, true><<<nb, 64 * kFW, lds, s>>>(z, n, fw, nh, ti, ci, K, logdet, sv);
-    else if (inverse)
-        k_flow_layer<true, false><<<nb, 64 * kFW, lds, s>>>(z, n, fw, nh, ti, ci, K, logdet, sv);
-    else if (save)
-        k_flow_layer<false, true><<<nb, 64 * kFW, lds, s>>>(z, n, fw, nh, ti, ci, K, logdet, sv);
-    else
-        k_flow_layer<false, false><<<nb, 64 * kFW, lds, s>>>(z, n, fw, nh, ti, ci, K, logdet, sv);
     return hipGetLastError();
 }
 

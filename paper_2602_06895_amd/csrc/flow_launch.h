@@ -41,17 +41,8 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 
-// One whole coupling layer in one kernel (BF16 operands, hidden width 128,
-// up to 16 bins): conditioner on the matrix cores and spline (forward, or
-// inverse when `inverse`), z updated in place, logdet accumulated.
-// params_t / params: the layer's block of the BF16 operand copy (16-byte
-// aligned) / of the FP32 parameters (biases), with the offsets off[0..7]
-// (W1 b1 W2 b2 W3 b3 W4 b4) in both.  save_x0 [n][nh] BF16, save_h [3][n][128]
-// BF16 and save_theta [n][nh (3K + 1)] FP32, when all three are set, receive
-// the conditioning inputs, hidden activations and spline parameters.
-hipError_t launch_flow_layer(bool inverse, float* z, int64_t n, const void* params_t, const float* params,
-                             const int64_t* off, int nh, const int32_t* trans_host, const int32_t* cond_host, int K,
-                             float* logdet, void* save_x0, void* save_h, float* save_theta, hipStream_t s);
+// Coupling layers of BF16 operands, hidden width 128 and up to 16 bins have
+// kernels of their own: conditioner on the matrix cores and spline together.
 constexpr int kFusedHidden = 128;
 constexpr int kFusedMaxBins = 16;
 
@@ -78,6 +69,41 @@ struct FlowRun {
     int first, dir, count;
 };
 hipError_t launch_flow_layers(bool inverse, const FlowNet& fn, const FlowRun& run, int cu_count, hipStream_t s);
+
+// Reverse mode of one inverse layer of such a flow.  The matrices between its
+// kernels are BF16 in blocks of 32 events, [blocks][rows][32], which is how the
+// weight gradients read them: an operand of 16 rows and 32 events is 1 KiB
+// without gaps.  Whole tiles of 64 events are written; columns beyond n of d
+// and dh are zero.
+struct FlowRev {
+    const float* zin;  // the layer's input [d][n], before inversion
+    float* adj;        // [d][n] adjoint, of the layer's output on entry, of its input on exit
+    const float* G;    // [n] dLoss/dlogq
+    __bf16* x0;        // [blocks][32][32] conditioning inputs (rows beyond nh undefined)
+    __bf16* h;         // [blocks][3 * 128][32] hidden activations
+    uint16_t* on;      // [tiles][3][512] which of them are positive
+    __bf16* d;         // [blocks][flow_grad_rows][32] gradients of the spline parameters
+    __bf16* dh;        // [blocks][3 * 128][32] gradients of the hidden layers before their ReLU
+    int64_t n;
+    int layer;
+    int first;         // adj counts as zero on entry
+};
+// Rows of FlowRev::d (the last ones undefined).
+int flow_grad_rows(int nh, int K);
+// Hidden activations and spline recomputed, spline reversed: fills x0, h, on,
+// d and the transformed coordinates of adj.
+hipError_t launch_flow_spline_reverse(const FlowNet& fn, const FlowRev& r, int cu_count, hipStream_t s);
+// Transposed weights of all layers, for the next call: wt_t holds
+// flow_transposed_elems(nh) BF16 elements per layer.
+int64_t flow_transposed_elems(int nh);
+hipError_t launch_flow_transpose(const FlowNet& fn, int layers, void* wt_t, hipStream_t s);
+// Through the conditioner: fills dh and the conditioning coordinates of adj.
+hipError_t launch_flow_mlp_reverse(const FlowNet& fn, const FlowRev& r, const void* wt_t, int cu_count,
+                                   hipStream_t s);
+// Weight and bias gradients of the layer from d, dh, h, x0: partial sums over
+// `splits` runs of events, part [splits][per], laid out as the parameters.
+int flow_wgrad_splits(int64_t n);
+hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, hipStream_t s);
 
 // out[m][n] = sum_z part[z][m][n] in z order (out has leading dimension ldo).
 hipError_t launch_reduce_partials(const float* part, int splits, int M, int N, float* out, int64_t ldo,

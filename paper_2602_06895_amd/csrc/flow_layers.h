@@ -21,6 +21,7 @@ namespace msx {
 namespace flow {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -147,14 +148,19 @@ __device__ __forceinline__ OutBias load_out_bias(const FlowNet& fn, int layer, i
 }
 
 // The activations of the wave's 16 features for the 16 events from row r0:
-// bias, ReLU, BF16, one 8-byte store per lane.
-__device__ __forceinline__ void store_act(const floatx4& acc, const floatx4& bias, __bf16* __restrict__ act, int r0,
-                                          int wave, int lane) {
+// bias, ReLU, BF16, one 8-byte store per lane.  Returns which are positive.
+__device__ __forceinline__ uint32_t store_act(const floatx4& acc, const floatx4& bias, __bf16* __restrict__ act, int r0,
+                                              int wave, int lane) {
     const int q = lane >> 4;
     bf16x4 v;
+    uint32_t on = 0;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) v[x] = (__bf16)fmaxf(acc[x] + bias[x], 0.0f);
+    for (int x = 0; x < 4; ++x) {
+        v[x] = (__bf16)fmaxf(acc[x] + bias[x], 0.0f);
+        on |= (float)v[x] > 0.0f ? 1u << x : 0u;
+    }
     *(bf16x4*)&act[act_chunk(r0 + (lane & 15), 2 * wave + (q >> 1)) + 4 * (q & 1)] = v;
+    return on;
 }
 
 // The four right-hand fragments (128 features) of the 16 events from row r0.
@@ -211,6 +217,55 @@ __device__ __forceinline__ Theta gather_theta(const floatx4 (&acc)[NT][4]) {
     transpose_rows(r);
     th.s[16] = __uint_as_float(r[0]);
     return th;
+}
+
+// One 128 -> 128 layer: the wave's 16 features of every event of the tile.
+// Returns which are positive, four bits per 16-event tile.
+template <int NT>
+__device__ __forceinline__ uint32_t hidden_layer(const bf16x8 (&w)[4], const floatx4& bias, const __bf16* in, __bf16* out,
+                                             int wave, int lane) {
+    bf16x8 x[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) load_act(in, 16 * t, lane, x[t]);
+    floatx4 acc[NT];
+    uint32_t on = 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = mfma(w[s], x[t][s], s ? acc[t] : zero4());
+#pragma unroll
+    for (int t = 0; t < NT; ++t) on |= store_act(acc[t], bias, out, 16 * t, wave, lane) << (4 * t);
+    return on;
+}
+
+// The spline parameters of coordinate j from the last activation; the output
+// weights from LDS and the biases from registers (KEEP), or both from memory.
+template <int NT, bool KEEP>
+__device__ __forceinline__ Theta output_layer(const FlowNet& fn, int layer, const __bf16* a, const __bf16* w4,
+                                              OutBias ob, int j, int K, int lane) {
+    const __bf16* const w4g = (const __bf16*)fn.wt + layer * fn.per_t + fn.off[6];
+    floatx4 acc[NT][4];
+    bf16x8 x[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) load_act(a, 16 * t, lane, x[t]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int row = j * (3 * K + 1) + param_row(m, lane & 15, K);
+        bf16x8 w[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            w[s] = KEEP ? out_fragment(w4, j, m, s, lane) : *(const bf16x8*)&w4g[row * kHid + 32 * s + 8 * (lane >> 4)];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t][m] = mfma(w[s], x[t][s], s ? acc[t][m] : zero4());
+    }
+    if (!KEEP) ob = load_out_bias(fn, layer, j, lane);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[t][m] += ob.b[m];
+    return gather_theta<NT>(acc);
 }
 
 // softplus(x) = max(x, 0) + log(1 + e^-|x|) through the hardware's exp2 and

@@ -20,22 +20,6 @@ constexpr size_t layers_lds(int d, int kept) {
            sizeof(float) * 16 * NT * (2 * (size_t)d + kWaves);
 }
 
-// One 128 -> 128 layer: the wave's 16 features of every event of the tile.
-template <int NT>
-__device__ __forceinline__ void hidden_layer(const bf16x8 (&w)[4], const floatx4& bias, const __bf16* in, __bf16* out,
-                                             int wave, int lane) {
-    bf16x8 x[NT][4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) load_act(in, 16 * t, lane, x[t]);
-    floatx4 acc[NT];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = mfma(w[s], x[t][s], s ? acc[t] : zero4());
-#pragma unroll
-    for (int t = 0; t < NT; ++t) store_act(acc[t], bias, out, 16 * t, wave, lane);
-}
-
 // All coupling layers of a pass, forward (sampling) or inverse (densities,
 // and the first half of training).  Workgroup b owns tiles b, b + grid, ...
 // of every layer and runs the layers one after the other over them, so the
@@ -85,7 +69,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const float* const zi = li == 0 ? run.zin : run.zout + (li - 1) * run.zstep;
         float* const zo = run.zout + li * run.zstep;
         const HidW hw = load_hidden(fn, layer, wave, lane);
-        const __bf16* const w4g = (const __bf16*)fn.wt + layer * fn.per_t + fn.off[6];
         OutBias ob;
         if (KEEP) {
             ob = load_out_bias(fn, layer, min(wave, nh - 1), lane);
@@ -126,32 +109,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 run.logdet[tile * EV + tid] = old + s;
             }
         };
-        // the spline parameters of coordinate j from the last activation
-        auto output = [&](const __bf16* a, int j) {
-            floatx4 acc[NT][4];
-            bf16x8 x[NT][4];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) load_act(a, 16 * t, lane, x[t]);
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const int row = j * P + param_row(m, e16, K);
-                bf16x8 w[4];
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    w[s] = KEEP ? out_fragment(w4, j, m, s, lane)
-                                : *(const bf16x8*)&w4g[row * kHid + 32 * s + 8 * q];
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) acc[t][m] = mfma(w[s], x[t][s], s ? acc[t][m] : zero4());
-            }
-            if (!KEEP) ob = load_out_bias(fn, layer, j, lane);
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int m = 0; m < 4; ++m) acc[t][m] += ob.b[m];
-            return gather_theta<NT>(acc);
-        };
         // the previous layer's stores to z, and its last readers of LDS
         __syncthreads();
         fetch(blockIdx.x);
@@ -182,7 +139,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             float ld_sum = 0.0f;
             for (int j = wave; j < nh; j += KEEP ? 2 * kFlowMaxHalf : kWaves) {
                 const int tj = mk.t0 + mk.ts * j;
-                Theta th = output(a0, j);
+                Theta th = output_layer<NT, KEEP>(fn, layer, a0, w4, ob, j, K, lane);
                 const float vin = zt[tj * EV + ev];
                 float sw, sh, ld;
                 spline_exp<K16>(th, K, sw, sh);

@@ -71,3 +71,53 @@ def test_passes_in_place_and_split(torch, d, n):
         assert torch.equal(torch.cat([p[0] for p in parts], 1), v)
         assert torch.equal(torch.cat([p[1] for p in parts]), ld)
     f.close()
+
+
+def _batch(torch, d, n, seed):
+    rng = np.random.default_rng(seed)
+    y = rng.uniform(0.02, 0.98, (d, n)).astype(np.float32)
+    wfj = rng.uniform(0.5, 2.0, n)
+    lqo = rng.uniform(-0.5, 0.5, n).astype(np.float32)
+    return y, wfj, lqo, [torch.from_numpy(a).cuda() for a in (y, wfj, lqo)]
+
+
+# one event, around one tile of 64, an odd number of 32-event blocks per run
+# of the weight gradients, a run per 256 events and beyond its largest number
+GRAD_SHAPES = [(16, 4, 16, 1), (16, 4, 16, 63), (16, 3, 16, 65), (10, 4, 16, 513), (2, 3, 16, 200), (16, 2, 16, 2100),
+               (18, 2, 16, 130), (64, 2, 16, 70), (64, 2, 12, 300), (16, 4, 1, 90), (14, 2, 7, 33000), (24, 2, 5, 700)]
+
+
+@pytest.mark.parametrize("d,layers,bins,n", GRAD_SHAPES)
+def test_gradient_matches_oracle(torch, d, layers, bins, n):
+    """The gradient against the oracle with BF16 conditioner roundings.  That
+    oracle differs from the FP64 one by d_bf16; the kernels round the same
+    quantities, but from FP32 sums, and the back-propagated ones too, each worth
+    at most one more such rounding: 2 d_bf16 + 1e-3, as for the full-size flow."""
+    import torch as t
+
+    f, orc = _pair(d, layers, bins, 7 * d + bins)
+    y, wfj, lqo, dev = _batch(torch, d, n, d + n)
+    g, loss = f.gradient(*dev)
+    torch.cuda.synchronize()
+    args = [t.from_numpy(y.T.astype(np.float64)), t.from_numpy(wfj) ** 2, t.from_numpy(lqo.astype(np.float64))]
+    l_bf, g_bf = orc.loss_and_grad(*args)
+    _, g_64 = F.Flow(d, layers, bins, 128, params=orc.params, bf16_mlp=False).loss_and_grad(*args)
+    got, ref, ref64 = g.cpu().numpy().astype(np.float64), g_bf.numpy(), g_64.numpy()
+    bound = 2 * np.linalg.norm(ref - ref64) + 1e-3 * np.linalg.norm(ref)
+    assert np.linalg.norm(got - ref) <= bound
+    assert abs(float(loss.cpu()[0]) - float(l_bf)) <= 1e-3 * abs(float(l_bf))
+    f.close()
+
+
+@pytest.mark.parametrize("d,bins", [(16, 16), (24, 9)])
+def test_gradient_after_a_larger_batch(torch, d, bins):
+    """A batch that is no whole tile, in the buffers of a larger one: the bits of
+    a flow that has seen nothing else."""
+    f, _ = _pair(d, 3, bins, 5)
+    *_, big = _batch(torch, d, 3000, 1)
+    *_, small = _batch(torch, d, 77, 2)
+    want, _ = f.gradient(*small)
+    f.gradient(*big)
+    got, _ = f.gradient(*small)
+    assert torch.equal(got, want)
+    f.close()
