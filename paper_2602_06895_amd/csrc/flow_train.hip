@@ -3,7 +3,7 @@
 // gradients of one layer in three kernels.  A layer of 8 + 8 coordinates and 16
 // bins with 65,536 events took 490 us as 14 kernels (eight products, spline,
 // four column sums over events, ...) with every operand through memory; the
-// three take 63, 45 and 82 us.
+// three take 63, 45 and 40 us.
 #include <algorithm>
 
 #include "flow_adjoint.h"
@@ -337,16 +337,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // Weight gradients of a layer over a run of 32-event blocks: d h3^T, dh3 h2^T,
 // dh2 h1^T, dh1 x0^T, and the row sums of d, dh3, dh2, dh1 (the biases).  A
 // workgroup holds all 84,000 sums in the accumulators of its eight waves (172
-// registers each), so every element of the run is read from memory once; an
-// operand is one gapless 1 KiB load.  blockIdx.y takes eight coordinates' rows
-// of d, its first the hidden layers too.
+// registers each), so every element of the run is read from memory once.  A
+// block's operands come to LDS as they lie in memory (an operand is 1 KiB
+// without gaps), the next block's while this one is multiplied.  One launch
+// (HIDDEN) takes the rows of d of eight coordinates and the hidden layers, a
+// second one with a blockIdx.y for every eight more coordinates their rows.
+// 65,536 events of 16 dimensions: 40 us, 157 MB at 3.9 TB/s (with every wave
+// loading its operands from the caches itself, eight times the traffic and no
+// load ahead of its use, 82 us).  The partial sums of 128 runs are 43 MB: more
+// runs would fill more compute units, but write and add up as much again.
+constexpr int kBlockH = 3 * kHid * 32, kBlockD = 16 * kGradTiles * 32, kBlockX = 32 * 32;  // elements
+constexpr int kBlockElems = 2 * kBlockH + kBlockD + kBlockX;
+
+__device__ __forceinline__ void copy_to_lds(const __bf16* __restrict__ src, __bf16* __restrict__ dst, int chunks, int wave,
+                                            int lane) {
+    for (int c = wave; c < chunks; c += kWaves)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + c * 512 + lane * 8),
+                                         (__attribute__((address_space(3))) void*)(dst + c * 512), 16, 0, 0);
+}
+
+template <bool HIDDEN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_flow_wgrad(
     FlowNet fn, FlowRev r, int64_t blocks, int64_t chunk, float* __restrict__ part) {
+    __shared__ __attribute__((aligned(16))) __bf16 smem[2 * kBlockElems];
     const int nh = fn.nh, P = 3 * fn.K + 1, n_out = nh * P, gr = grad_rows(nh, fn.K);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4;
-    const int row0 = blockIdx.y * 8 * P, rows = min(8 * P, n_out - row0);
-    const bool hidden = blockIdx.y == 0;
+    const int row0 = HIDDEN ? 0 : (blockIdx.y + 1) * 8 * P, rows = min(8 * P, n_out - row0);
     float* const out = part + (int64_t)blockIdx.x * fn.per;
     floatx4 a4[3][8], a24 = zero4(), a3[8], a2[8], a1[2];
     float s4[3] = {0.0f, 0.0f, 0.0f}, s24 = 0.0f, s3 = 0.0f, s2 = 0.0f, s1 = 0.0f;
@@ -359,10 +376,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         return (((float)v[0] + (float)v[1]) + ((float)v[2] + (float)v[3])) +
                (((float)v[4] + (float)v[5]) + ((float)v[6] + (float)v[7]));
     };
-    const int64_t k0 = blockIdx.x * chunk, k1 = min(blocks, k0 + chunk);
-    for (int64_t k = k0; k < k1; ++k) {
-        const __bf16* const h = r.h + k * 3 * kHid * 32;
-        const __bf16* const d = r.d + (k * gr + row0) * 32;
+    auto stage = [&](int64_t k, __bf16* __restrict__ to) {
+        copy_to_lds(r.d + (k * gr + row0) * 32, to, kBlockD / 512, wave, lane);
+        copy_to_lds(r.h + k * kBlockH, to + kBlockD, kBlockH / 512, wave, lane);
+        if (!HIDDEN) return;
+        copy_to_lds(r.dh + k * kBlockH, to + kBlockD + kBlockH, kBlockH / 512, wave, lane);
+        copy_to_lds(r.x0 + k * kBlockX, to + kBlockD + 2 * kBlockH, kBlockX / 512, wave, lane);
+    };
+    // the copies of block k to `next` run under the products of `d`: restrict
+    // tells the compiler that reading the one need not wait for the other
+    auto step = [&](const __bf16* __restrict__ d, __bf16* __restrict__ next, int64_t k) {
+        stage(k, next);
+        const __bf16 *const h = d + kBlockD, *const dh = h + kBlockH, *const x0 = dh + kBlockH;
         bf16x8 b[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) b[c] = frag(h, 2 * kHid + 16 * c);
@@ -377,15 +402,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const bf16x8 al = frag(d, 384);
         s24 += sum8(al);
         a24 = mfma(al, frag(h, 2 * kHid + 16 * wave), a24);
-        if (!hidden) continue;
-        const __bf16* const dh = r.dh + k * 3 * kHid * 32;
-        const __bf16* const x0 = r.x0 + k * 32 * 32;
+        if (!HIDDEN) return;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 8; ++c) b[c] = frag(h, kHid + 16 * c);
         const bf16x8 x3 = frag(dh, 2 * kHid + 16 * wave);
         s3 += sum8(x3);
 #pragma unroll
         for (int c = 0; c < 8; ++c) a3[c] = mfma(x3, b[c], a3[c]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 8; ++c) b[c] = frag(h, 16 * c);
         const bf16x8 x2 = frag(dh, kHid + 16 * wave);
@@ -396,7 +421,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         s1 += sum8(x1);
 #pragma unroll
         for (int c = 0; c < 2; ++c) a1[c] = mfma(x1, frag(x0, 16 * c), a1[c]);
+    };
+    const int64_t k0 = blockIdx.x * chunk, k1 = min(blocks, k0 + chunk);
+    if (k0 < k1) stage(k0, smem);
+    for (int64_t k = k0; k < k1; ++k) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();  // block k is in LDS, the other buffer's readers are done
+        const int cur = (int)(k - k0) & 1;
+        step(smem + cur * kBlockElems, smem + (cur ^ 1) * kBlockElems, min(k + 1, k1 - 1));
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     auto over_q = [](float v) {
         v += __shfl_xor(v, 16, 64);
         return v + __shfl_xor(v, 32, 64);
@@ -421,7 +455,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (384 + 4 * q + x < rows) w4[(384 + 4 * q + x) * kHid + my] = a24[x];
     const float sl = over_q(s24);
     if (wave == 0 && q == 0 && 384 + r16 < rows) b4[384 + r16] = sl;
-    if (!hidden) return;
+    if (!HIDDEN) return;
     s3 = over_q(s3);
     s2 = over_q(s2);
     s1 = over_q(s1);
@@ -485,7 +519,10 @@ int flow_wgrad_splits(int64_t n) { return (int)std::max<int64_t>(1, std::min<int
 
 hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, hipStream_t s) {
     const int64_t blocks = (r.n + 63) / 64 * 2, chunk = (blocks + splits - 1) / splits;
-    k_flow_wgrad<<<dim3((unsigned)splits, (unsigned)out_chunks(fn.nh)), kThreads, 0, s>>>(fn, r, blocks, chunk, part);
+    k_flow_wgrad<true><<<(unsigned)splits, kThreads, 0, s>>>(fn, r, blocks, chunk, part);
+    if (out_chunks(fn.nh) > 1)
+        k_flow_wgrad<false><<<dim3((unsigned)splits, (unsigned)(out_chunks(fn.nh) - 1)), kThreads, 0, s>>>(fn, r, blocks,
+                                                                                                        chunk, part);
     return hipGetLastError();
 }
 
