@@ -46,11 +46,11 @@ struct msx_flow {
     float* ldp = nullptr;    // [nh][cap] per-coordinate log-det terms
     // reverse mode of fused layers (one layer at a time, see FlowRev); these
     // take the place of x0, h, theta, dtheta, dha, dhb, dx0 and ldp
-    __bf16* rx0 = nullptr;
-    __bf16* rh = nullptr;
-    __bf16* rd = nullptr;
-    __bf16* rdh = nullptr;
-    __bf16* wt_t = nullptr;  // [L][flow_transposed_elems]
+    void* rx0 = nullptr;
+    void* rh = nullptr;
+    void* rd = nullptr;
+    void* rdh = nullptr;
+    void* wt_t = nullptr;  // [L][flow_transposed_elems]
     uint16_t* ron = nullptr;
     float* part = nullptr;   // split-K partials
     int64_t part_cap = 0;
@@ -124,10 +124,13 @@ void free_work(msx_flow* f) {
     f->cap = 0;
 }
 
-// The fused coupling layers cover BF16 conditioners of hidden width 128
-// with up to 16 bins.
-bool fused_ok(const msx_flow* f) {
-    return f->type == FT_BF16 && f->H == kFusedHidden && f->K <= kFusedMaxBins;
+// The fused coupling layers cover conditioners of hidden width 128 with up to
+// 16 bins.
+bool fused_ok(const msx_flow* f) { return f->H == kFusedHidden && f->K <= kFusedMaxBins; }
+
+OperandOrder order_of(const msx_flow* f) {
+    if (f->type != FT_F32 || !fused_ok(f)) return {0, 0, 0, 0};
+    return {(int32_t)f->off[2], (int32_t)f->off[4], (int32_t)f->off[6], (int32_t)f->off[7]};
 }
 
 // Work buffers for n events: the intermediates of all layers, which the reverse
@@ -138,7 +141,7 @@ msx_status ensure_work(msx_flow* f, int64_t n) {
     const size_t ts = tsize(f->type);
     const size_t N = (size_t)n;
     if (fused_ok(f)) {
-        const size_t tiles = (N + 63) / 64, block = 2 * 32 * sizeof(__bf16);  // bytes per row and tile
+        const size_t tiles = (N + 63) / 64, block = 64 * tsize(f->type);  // bytes per row and tile
         FHIP(f, fmalloc(&f->z, sizeof(float) * (size_t)f->L * f->d * N), "flow work");
         FHIP(f, fmalloc(&f->logq, sizeof(float) * N), "flow work");
         FHIP(f, fmalloc(&f->G, sizeof(float) * N), "flow work");
@@ -147,8 +150,8 @@ msx_status ensure_work(msx_flow* f, int64_t n) {
         FHIP(f, fmalloc(&f->rh, block * 3 * f->H * tiles), "flow work");
         FHIP(f, fmalloc(&f->rd, block * flow_grad_rows(f->nh, f->K) * tiles), "flow work");
         FHIP(f, fmalloc(&f->rdh, block * 3 * f->H * tiles), "flow work");
-        FHIP(f, fmalloc(&f->ron, sizeof(uint16_t) * 3 * 512 * tiles), "flow work");
-        FHIP(f, fmalloc(&f->wt_t, sizeof(__bf16) * f->L * flow_transposed_elems(f->nh)), "flow work");
+        FHIP(f, fmalloc(&f->ron, sizeof(uint16_t) * 2 * 3 * 512 * tiles), "flow work");
+        FHIP(f, fmalloc(&f->wt_t, tsize(f->type) * f->L * flow_transposed_elems(f->nh)), "flow work");
         f->cap = n;
         return MSX_OK;
     }
@@ -267,6 +270,7 @@ FlowNet net_of(const msx_flow* f) {
     for (int i = 0; i < 8; ++i) n.off[i] = (int32_t)f->off[i];
     n.nh = f->nh;
     n.K = f->K;
+    n.f32 = f->type == FT_F32;
     return n;
 }
 
@@ -297,7 +301,7 @@ msx_status gradient_fused(msx_flow* f, int64_t n, const float* y, const double* 
                           float* grad, double* loss, bool log_loss, hipStream_t s) {
     const FlowNet fn = net_of(f);
     const int64_t zs = (int64_t)f->d * n;
-    const int splits = flow_wgrad_splits(n);
+    const int splits = flow_wgrad_splits(fn, n);
     if (msx_status st = ensure_part(f, splits * f->per_layer)) return st;
     FHIP(f, launch_flow_layers(true, fn, FlowRun{y, f->z, zs, f->logq, n, f->L - 1, -1, f->L}, f->cu_count, s),
          "flow layers");
@@ -512,7 +516,8 @@ msx_status msx_flow_set_params(msx_flow* f, const float* host, int64_t n) {
     FHIP(f, hipMemset(f->m, 0, sizeof(float) * n), "flow clear");
     FHIP(f, hipMemset(f->v, 0, sizeof(float) * n), "flow clear");
     f->adam_t = 0;
-    FHIP(f, launch_cast(n, f->params, f->type, f->params_t, f->per_layer, f->per_layer_t, nullptr), "flow cast");
+    FHIP(f, launch_cast(n, f->params, f->type, f->params_t, f->per_layer, f->per_layer_t, order_of(f),
+                       nullptr), "flow cast");
     FHIP(f, hipDeviceSynchronize(), "flow synchronise");
     return MSX_OK;
 }
@@ -586,7 +591,8 @@ msx_status msx_flow_set_state(msx_flow* f, const void* buf, size_t size) {
     FHIP(f, hipMemcpy(f->m, body + f->P, sizeof(float) * f->P, hipMemcpyHostToDevice), "flow state");
     FHIP(f, hipMemcpy(f->v, body + 2 * f->P, sizeof(float) * f->P, hipMemcpyHostToDevice), "flow state");
     f->adam_t = h.adam_t;
-    FHIP(f, launch_cast(f->P, f->params, f->type, f->params_t, f->per_layer, f->per_layer_t, nullptr), "flow cast");
+    FHIP(f, launch_cast(f->P, f->params, f->type, f->params_t, f->per_layer, f->per_layer_t, order_of(f),
+                       nullptr), "flow cast");
     FHIP(f, hipDeviceSynchronize(), "flow synchronise");
     return MSX_OK;
 }
@@ -642,7 +648,7 @@ msx_status msx_flow_train_step(msx_flow* f, int64_t n, const float* y, const dou
     const double c1 = 1.0 - std::pow(b1, (double)f->adam_t), c2 = 1.0 - std::pow(b2, (double)f->adam_t);
     const float lr_t = (float)(lr * std::sqrt(c2) / c1), eps_t = (float)(eps * std::sqrt(c2));
     FHIP(f, launch_adam(f->P, f->params, f->grad, f->m, f->v, (float)b1, (float)b2, lr_t, eps_t, f->type, f->params_t,
-                        f->per_layer, f->per_layer_t, s),
+                        f->per_layer, f->per_layer_t, order_of(f), s),
          "flow adam");
     return MSX_OK;
 }

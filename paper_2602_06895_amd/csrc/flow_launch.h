@@ -41,20 +41,20 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 
-// Coupling layers of BF16 operands, hidden width 128 and up to 16 bins have
-// kernels of their own: conditioner on the matrix cores and spline together.
+// Coupling layers of hidden width 128 and up to 16 bins have kernels of their
+// own: conditioner on the matrix cores and spline together.
 constexpr int kFusedHidden = 128;
 constexpr int kFusedMaxBins = 16;
 
-// Parameters of a flow with such layers: the BF16 operand copy (layer blocks
-// of per_t elements, 16-byte aligned), the FP32 parameters (blocks of per),
-// and the offsets of W1 b1 W2 b2 W3 b3 W4 b4 in both.
+// Parameters of a flow with such layers: the operand copy (BF16, or FP32 if
+// f32; layer blocks of per_t elements, 16-byte aligned), the FP32 parameters
+// (blocks of per), and the offsets of W1 b1 W2 b2 W3 b3 W4 b4 in both.
 struct FlowNet {
     const void* wt;
     const float* p;
     int32_t per_t, per;
     int32_t off[8];
-    int32_t nh, K;
+    int32_t nh, K, f32;
 };
 // A pass over `count` layers first, first + dir, ...: n events [d][n] from
 // zin; the i-th layer of the pass leaves its result in zout + i zstep (zstep
@@ -71,19 +71,19 @@ struct FlowRun {
 hipError_t launch_flow_layers(bool inverse, const FlowNet& fn, const FlowRun& run, int cu_count, hipStream_t s);
 
 // Reverse mode of one inverse layer of such a flow.  The matrices between its
-// kernels are BF16 in blocks of 32 events, [blocks][rows][32], which is how the
-// weight gradients read them: an operand of 16 rows and 32 events is 1 KiB
-// without gaps.  Whole tiles of 64 events are written; columns beyond n of d
-// and dh are zero.
+// kernels, of the operands' type, are in blocks of 32 events, [blocks][rows][32],
+// which is how the weight gradients read them: an operand of 16 rows and 32
+// events has no gaps.  Whole tiles of up to 64 events are written; columns
+// beyond n of d and dh are zero.
 struct FlowRev {
     const float* zin;  // the layer's input [d][n], before inversion
     float* adj;        // [d][n] adjoint, of the layer's output on entry, of its input on exit
     const float* G;    // [n] dLoss/dlogq
-    __bf16* x0;        // [blocks][32][32] conditioning inputs (rows beyond nh undefined)
-    __bf16* h;         // [blocks][3 * 128][32] hidden activations
-    uint16_t* on;      // [tiles][3][512] which of them are positive
-    __bf16* d;         // [blocks][flow_grad_rows][32] gradients of the spline parameters
-    __bf16* dh;        // [blocks][3 * 128][32] gradients of the hidden layers before their ReLU
+    void* x0;          // [blocks][32][32] conditioning inputs (rows beyond nh undefined)
+    void* h;           // [blocks][3 * 128][32] hidden activations
+    uint16_t* on;      // [tiles of at least 32 events][3][512] which of them are positive
+    void* d;           // [blocks][flow_grad_rows][32] gradients of the spline parameters
+    void* dh;          // [blocks][3 * 128][32] gradients of the hidden layers before their ReLU
     int64_t n;
     int layer;
     int first;         // adj counts as zero on entry
@@ -94,7 +94,7 @@ int flow_grad_rows(int nh, int K);
 // d and the transformed coordinates of adj.
 hipError_t launch_flow_spline_reverse(const FlowNet& fn, const FlowRev& r, int cu_count, hipStream_t s);
 // Transposed weights of all layers, for the next call: wt_t holds
-// flow_transposed_elems(nh) BF16 elements per layer.
+// flow_transposed_elems(nh) elements per layer.
 int64_t flow_transposed_elems(int nh);
 hipError_t launch_flow_transpose(const FlowNet& fn, int layers, void* wt_t, hipStream_t s);
 // Through the conditioner: fills dh and the conditioning coordinates of adj.
@@ -102,7 +102,7 @@ hipError_t launch_flow_mlp_reverse(const FlowNet& fn, const FlowRev& r, const vo
                                    hipStream_t s);
 // Weight and bias gradients of the layer from d, dh, h, x0: partial sums over
 // `splits` runs of events, part [splits][per], laid out as the parameters.
-int flow_wgrad_splits(int64_t n);
+int flow_wgrad_splits(const FlowNet& fn, int64_t n);
 hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, hipStream_t s);
 
 // out[m][n] = sum_z part[z][m][n] in z order (out has leading dimension ldo).
@@ -145,13 +145,25 @@ hipError_t launch_scatter_add(float* adj, const float* dx0, int64_t n, int n_con
 hipError_t launch_flow_loss(int64_t n, const double* wfj, const float* logq, const float* logq_old, float* G,
                             double* part, double* loss, bool log_loss, hipStream_t s);
 
+// Columns of the FP32 operands of the fused layers: lane l of the matrix
+// instruction takes element 4 i + l / 16 of every 32 in its step i, so those
+// eight stand together.
+__host__ __device__ constexpr int32_t f32_operand_index(int32_t k) {
+    return (k & ~31) | ((k & 3) << 3) | ((k >> 2) & 7);
+}
+// Where the operand copy of a layer orders its columns so: the offsets of W2,
+// W3 and W4 and the end of W4 (0: nowhere).
+struct OperandOrder {
+    int32_t w2, w3, w4, end;
+};
 // Adam step on P parameters (bias corrections folded into lr_t, eps_t by the
 // caller), then the operand copy of the parameters in `type`.  The copy pads
 // each layer block of `per` parameters to `per_t` (a multiple of 8).
 hipError_t launch_adam(int64_t P, float* params, const float* grad, float* m, float* v, float b1, float b2,
-                       float lr_t, float eps_t, int type, void* params_t, int64_t per, int64_t per_t, hipStream_t s);
+                       float lr_t, float eps_t, int type, void* params_t, int64_t per, int64_t per_t,
+                       const OperandOrder& order, hipStream_t s);
 hipError_t launch_cast(int64_t P, const float* params, int type, void* params_t, int64_t per, int64_t per_t,
-                       hipStream_t s);
+                       const OperandOrder& order, hipStream_t s);
 
 // u[k][i] = 24-bit Philox uniforms in (0, 1) (same counters as the FP64
 // generator: key (seed, sid), counter (e0 + i, k / 4, 0, 0)).

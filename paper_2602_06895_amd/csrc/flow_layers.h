@@ -1,12 +1,14 @@
-// Device side of the fused coupling layers (BF16 conditioner of hidden width
-// 128, up to 16 spline bins): the layout that the kernels share.
+// Device side of the fused coupling layers (conditioner of hidden width 128 in
+// BF16 or FP32, up to 16 spline bins): the layout that the kernels share.
 //
 // A workgroup of eight waves takes a tile of events.  Every product is formed
 // with the weights as the left MFMA operand and the events as the right one
 // (v_mfma_f32_16x16x32_bf16: lane l holds W[l % 16][8 (l / 16) + 0..7] and
-// X[8 (l / 16) + 0..7][l % 16], and receives D[4 (l / 16) + 0..3][l % 16]),
-// so a lane gets four neighbouring features of one event: an activation goes
-// to LDS as one 8-byte store, and the spline parameters of an event sit in
+// X[8 (l / 16) + 0..7][l % 16], and receives D[4 (l / 16) + 0..3][l % 16]; in
+// FP32 eight v_mfma_f32_16x16x4_f32 take eight elements one by one, the
+// columns of every 32 ordered so that a lane's eight stand together and the
+// sum still runs over the columns in order), so a lane gets four neighbouring features of one event: an activation goes
+// to LDS as one store, and the spline parameters of an event sit in
 // the four lanes that share its column.  Wave w computes features 16 w .. 16 w
 // + 15 of every hidden layer and the splines of transformed coordinates w, w +
 // 8, ...
@@ -20,9 +22,12 @@
 namespace msx {
 namespace flow {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+template <class T>
+using Vec8 = T __attribute__((ext_vector_type(8)));
+template <class T>
+using Vec4 = T __attribute__((ext_vector_type(4)));
+template <class T>
+using Vec2 = T __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;               // waves per workgroup
@@ -30,17 +35,48 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kHid = kFusedHidden;      // hidden width: 16 features per wave
 static_assert(kHid == 16 * kWaves, "one 16-feature tile per wave");
 
-// Activation tile in LDS, [events][128] BF16: the sixteen 16-byte chunks of
-// row r are permuted by chunk ^ (r mod 16), so the 16-byte operand reads (one
-// chunk column of many rows) and the 8-byte stores (chunk halves of sixteen
-// rows) each touch every bank once; with padded rows instead the reads took
-// two passes.
-__device__ __forceinline__ int act_chunk(int row, int chunk) { return row * kHid + ((chunk ^ (row & 15)) << 3); }
-// Conditioning inputs, [events][kCond] BF16 (zero beyond nh): four chunks.
-constexpr int kCond = kFlowMaxHalf;
-__device__ __forceinline__ int cond_chunk(int row, int chunk) {
-    return row * kCond + ((chunk ^ ((row >> 2) & 3)) << 3);
+// Where column k of an operand stands.
+template <class T>
+__device__ __forceinline__ int column(int k) {
+    return sizeof(T) == 2 ? k : f32_operand_index(k);
 }
+
+// Element c of row r of an activation tile in LDS, [events][128]: the 16-byte
+// chunks of a row are permuted by chunk ^ (r mod 16), so the operand reads
+// (one chunk column of many rows) and the stores (neighbouring chunks, or
+// halves of one, of sixteen rows) each touch every bank once; with padded rows
+// instead the reads took two passes.
+template <class T>
+__device__ __forceinline__ int act_at(int row, int c) {
+    constexpr int L = sizeof(T) == 2 ? 3 : 2;  // log2 of the elements of a chunk
+    return row * kHid + (((c >> L) ^ (row & 15)) << L) + (c & ((1 << L) - 1));
+}
+// The same for the conditioning inputs, [events][kCond] (zero beyond nh).
+constexpr int kCond = kFlowMaxHalf;
+template <class T>
+__device__ __forceinline__ int cond_at(int row, int c) {
+    if (sizeof(T) == 2) return row * kCond + (((c >> 3) ^ ((row >> 2) & 3)) << 3) + (c & 7);
+    return row * kCond + (((c >> 2) ^ ((row >> 1) & 7)) << 2) + (c & 3);
+}
+// Eight elements from column c, a multiple of 8 (two chunks in FP32).
+__device__ __forceinline__ Vec8<__bf16> act8(const __bf16* act, int row, int c) {
+    return *(const Vec8<__bf16>*)&act[act_at<__bf16>(row, c)];
+}
+__device__ __forceinline__ Vec8<__bf16> cond8(const __bf16* cond, int row, int c) {
+    return *(const Vec8<__bf16>*)&cond[cond_at<__bf16>(row, c)];
+}
+__device__ __forceinline__ Vec8<float> join(const floatx4& a, const floatx4& b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+__device__ __forceinline__ Vec8<float> act8(const float* act, int row, int c) {
+    return join(*(const floatx4*)&act[act_at<float>(row, c)], *(const floatx4*)&act[act_at<float>(row, c + 4)]);
+}
+__device__ __forceinline__ Vec8<float> cond8(const float* cond, int row, int c) {
+    return join(*(const floatx4*)&cond[cond_at<float>(row, c)], *(const floatx4*)&cond[cond_at<float>(row, c + 4)]);
+}
+// Eight elements from memory, 16-byte aligned.
+__device__ __forceinline__ Vec8<__bf16> load8(const __bf16* p) { return *(const Vec8<__bf16>*)p; }
+__device__ __forceinline__ Vec8<float> load8(const float* p) { return join(*(const floatx4*)p, *(const floatx4*)(p + 4)); }
 
 constexpr float kMinW = 1e-3f, kMinH = 1e-3f, kMinD = 1e-3f;
 
@@ -65,46 +101,72 @@ __device__ __forceinline__ int cond_index(const Mask& m, int nh, int c) {
     return r >= 0 && r < nh ? r : -1;
 }
 
-__device__ __forceinline__ floatx4 mfma(const bf16x8& a, const bf16x8& b, const floatx4& c) {
+__device__ __forceinline__ floatx4 mfma(const Vec8<__bf16>& a, const Vec8<__bf16>& b, const floatx4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ floatx4 zero4() { return floatx4{0.0f, 0.0f, 0.0f, 0.0f}; }
-__device__ __forceinline__ bf16x8 zero8() {
-    bf16x8 r;
+__device__ __forceinline__ floatx4 mfma(const Vec8<float>& a, const Vec8<float>& b, floatx4 c) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = (__bf16)0.0f;
+    for (int i = 0; i < 8; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], c, 0, 0, 0);
+    return c;
+}
+__device__ __forceinline__ floatx4 zero4() { return floatx4{0.0f, 0.0f, 0.0f, 0.0f}; }
+template <class T>
+__device__ __forceinline__ Vec8<T> zero8() {
+    Vec8<T> r;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = (T)0.0f;
     return r;
 }
 
-// A wave's weights of the hidden layers and the biases, in registers over all
-// tiles of a layer.
+// An offset of zero that the compiler takes for a new value wherever it is
+// asked for: loads behind it stay where they are written.
+__device__ __forceinline__ int here() {
+    int z = 0;
+    asm volatile("" : "+s"(z));
+    return z;
+}
+
+// A wave's weights of the hidden layers.  BF16: in registers over all tiles of
+// a layer.  FP32: the square layers' (64 registers) are
+// loaded again at the start of every tile, which is little beside the FP32
+// matrix rate (0.5 us of 20 us per 64 events).
+template <class T>
 struct HidW {
-    bf16x8 w1, w2[4], w3[4];
-    floatx4 b1, b2, b3;
+    Vec8<T> w1, w2[4], w3[4];
+    const T *p2, *p3;
+    __device__ __forceinline__ void load() {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            w2[s] = load8(p2 + 32 * s);
+            w3[s] = load8(p3 + 32 * s);
+        }
+    }
+    __device__ __forceinline__ void per_layer() {
+        if (sizeof(T) == 2) load();
+    }
+    __device__ __forceinline__ void per_tile() {
+        if (sizeof(T) == 2) return;
+        const int z = here();
+        p2 += z;
+        p3 += z;
+        load();
+    }
 };
 
-__device__ __forceinline__ floatx4 load_bias(const float* __restrict__ b) { return floatx4{b[0], b[1], b[2], b[3]}; }
-
-__device__ __forceinline__ HidW load_hidden(const FlowNet& fn, int layer, int wave, int lane) {
-    const __bf16* W = (const __bf16*)fn.wt + layer * fn.per_t;
-    const float* P = fn.p + layer * fn.per;
+template <class T>
+__device__ __forceinline__ HidW<T> load_hidden(const FlowNet& fn, int layer, int wave, int lane) {
+    const T* W = (const T*)fn.wt + layer * fn.per_t;
     const int r16 = lane & 15, q = lane >> 4, row = 16 * wave + r16;
-    HidW h;
+    HidW<T> h;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int k = 8 * q + i;
-        const __bf16 v = W[fn.off[0] + row * fn.nh + min(k, fn.nh - 1)];
-        h.w1[i] = k < fn.nh ? v : (__bf16)0.0f;
+        const int k = sizeof(T) == 2 ? 8 * q + i : 4 * i + q;
+        const T v = W[fn.off[0] + row * fn.nh + min(k, fn.nh - 1)];
+        h.w1[i] = k < fn.nh ? v : (T)0.0f;
     }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        h.w2[s] = *(const bf16x8*)&W[fn.off[2] + row * kHid + 32 * s + 8 * q];
-        h.w3[s] = *(const bf16x8*)&W[fn.off[4] + row * kHid + 32 * s + 8 * q];
-    }
-    const int f = 16 * wave + 4 * q;
-    h.b1 = load_bias(P + fn.off[1] + f);
-    h.b2 = load_bias(P + fn.off[3] + f);
-    h.b3 = load_bias(P + fn.off[5] + f);
+    h.p2 = &W[fn.off[2] + row * kHid + 8 * q];
+    h.p3 = &W[fn.off[4] + row * kHid + 8 * q];
+    h.per_layer();
     return h;
 }
 
@@ -115,7 +177,7 @@ __device__ __forceinline__ int param_row(int m, int r, int K) {
     if (m < 2) return m * K + min(r, K - 1);
     return min(2 * K + 16 * (m - 2) + r, 3 * K);
 }
-// W4 in LDS, per coordinate: tiles 0..2 in fragment order (a wave's read is 64
+// W4 (BF16) in LDS, per coordinate: tiles 0..2 in fragment order (a wave's read is 64
 // consecutive 16-byte words), then the row of slope 16, which all rows of
 // tile 3 repeat.
 constexpr int kOutElems = 48 * kHid + kHid;
@@ -126,47 +188,119 @@ __device__ __forceinline__ void load_out(const FlowNet& fn, int layer, __bf16* _
         const int j = i / (49 * 16), c = i - j * (49 * 16);  // 16-byte word c of coordinate j
         const int m = c >> 8, s = (c >> 6) & 3, r = c & 15, q = (c >> 4) & 3;
         const int row = m < 3 ? param_row(m, r, fn.K) : param_row(3, 0, fn.K), k = m < 3 ? 32 * s + 8 * q : 8 * (c & 15);
-        *(bf16x8*)&w4[j * kOutElems + 8 * c] = *(const bf16x8*)&W[(j * P + row) * kHid + k];
+        *(Vec8<__bf16>*)&w4[j * kOutElems + 8 * c] = load8(&W[(j * P + row) * kHid + k]);
     }
 }
-__device__ __forceinline__ bf16x8 out_fragment(const __bf16* w4, int j, int m, int s, int lane) {
+__device__ __forceinline__ Vec8<__bf16> out_fragment(const __bf16* w4, int j, int m, int s, int lane) {
     const __bf16* c = w4 + j * kOutElems;
-    return *(const bf16x8*)(m < 3 ? c + ((m * 4 + s) * 64 + lane) * 8 : c + 48 * kHid + 32 * s + 8 * (lane >> 4));
+    return load8(m < 3 ? c + ((m * 4 + s) * 64 + lane) * 8 : c + 48 * kHid + 32 * s + 8 * (lane >> 4));
 }
 
-struct OutBias {
-    floatx4 b[4];
+// The biases that a lane adds: hidden(l) to features 16 wave + 4 (lane / 16) ..
+// + 3 of hidden layer l, out(j, m) to rows 4 (lane / 16) .. + 3 of tile m of
+// coordinate j.  From memory:
+struct MemoryBias {
+    const float* P;
+    int off1, off3, off5, off7, K, wave, q;
+    __device__ __forceinline__ MemoryBias(const FlowNet& fn, int layer, int wave, int lane)
+        : P(fn.p + layer * fn.per), off1(fn.off[1]), off3(fn.off[3]), off5(fn.off[5]), off7(fn.off[7]), K(fn.K),
+          wave(wave), q(lane >> 4) {}
+    __device__ __forceinline__ floatx4 hidden(int l) const {
+        const float* b = P + (l == 0 ? off1 : (l == 1 ? off3 : off5)) + 16 * wave + 4 * q;
+        return floatx4{b[0], b[1], b[2], b[3]};
+    }
+    __device__ __forceinline__ floatx4 out(int j, int m) const {
+        const float* b = P + off7 + j * (3 * K + 1);
+        floatx4 o;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) o[x] = b[param_row(m, 4 * q + x, K)];
+        return o;
+    }
 };
-__device__ __forceinline__ OutBias load_out_bias(const FlowNet& fn, int layer, int j, int lane) {
-    const float* B = fn.p + layer * fn.per + fn.off[7] + j * (3 * fn.K + 1);
-    OutBias o;
+// From registers, a wave's hidden layers and (KEEP) its one coordinate; other
+// coordinates from memory.
+template <bool KEEP>
+struct RegisterBias {
+    MemoryBias mem;
+    floatx4 h[3], o[4];
+    __device__ __forceinline__ RegisterBias(const FlowNet& fn, int layer, int wave, int lane)
+        : mem(fn, layer, wave, lane) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+        for (int l = 0; l < 3; ++l) h[l] = mem.hidden(l);
+        if (KEEP) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) o.b[m][x] = B[param_row(m, 4 * (lane >> 4) + x, fn.K)];
-    return o;
+            for (int m = 0; m < 4; ++m) o[m] = mem.out(min(wave, fn.nh - 1), m);
+        }
+    }
+    __device__ __forceinline__ floatx4 hidden(int l) const { return h[l]; }
+    __device__ __forceinline__ floatx4 out(int j, int m) const { return KEEP ? o[m] : mem.out(j, m); }
+};
+// The same from LDS: 28 registers fewer over all tiles, for four or five more
+// LDS reads.
+constexpr int kBiases = 3 * kHid + kWaves * 64;  // floats
+template <bool KEEP>
+struct LdsBias {
+    MemoryBias mem;
+    const float* lb;
+    __device__ __forceinline__ LdsBias(const FlowNet& fn, int layer, int wave, int lane, float* lds)
+        : mem(fn, layer, wave, lane), lb(lds + 4 * (lane >> 4)) {
+        const int tid = 64 * wave + lane;
+        for (int i = tid; i < 3 * kHid; i += kThreads)
+            lds[i] = mem.P[fn.off[2 * (i / kHid) + 1] + (i & (kHid - 1))];
+        static_assert(kThreads == kWaves * 64, "one bias of a coordinate per thread");
+        lds[3 * kHid + tid] =
+            mem.P[fn.off[7] + min(wave, fn.nh - 1) * (3 * fn.K + 1) + param_row((tid >> 4) & 3, tid & 15, fn.K)];
+    }
+    __device__ __forceinline__ floatx4 hidden(int l) const {
+        return *(const floatx4*)&lb[here() + l * kHid + 16 * mem.wave];
+    }
+    __device__ __forceinline__ floatx4 out(int j, int m) const {
+        return KEEP ? *(const floatx4*)&lb[here() + 3 * kHid + j * 64 + m * 16] : mem.out(j, m);
+    }
+};
+
+// Four neighbouring columns from c of an activation row.
+__device__ __forceinline__ void store4(const Vec4<__bf16>& v, __bf16* __restrict__ act, int row, int c) {
+    *(Vec4<__bf16>*)&act[act_at<__bf16>(row, c)] = v;
+}
+__device__ __forceinline__ void store4(const Vec4<float>& v, float* __restrict__ act, int row, int c) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) act[act_at<float>(row, column<float>(c + x))] = v[x];
 }
 
 // The activations of the wave's 16 features for the 16 events from row r0:
-// bias, ReLU, BF16, one 8-byte store per lane.  Returns which are positive.
-__device__ __forceinline__ uint32_t store_act(const floatx4& acc, const floatx4& bias, __bf16* __restrict__ act, int r0,
+// bias, ReLU, conversion, one store per lane.  Returns which are positive.
+template <class T>
+__device__ __forceinline__ uint32_t store_act(const floatx4& acc, const floatx4& bias, T* __restrict__ act, int r0,
                                               int wave, int lane) {
-    const int q = lane >> 4;
-    bf16x4 v;
+    Vec4<T> v;
     uint32_t on = 0;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-        v[x] = (__bf16)fmaxf(acc[x] + bias[x], 0.0f);
+        v[x] = (T)fmaxf(acc[x] + bias[x], 0.0f);
         on |= (float)v[x] > 0.0f ? 1u << x : 0u;
     }
-    *(bf16x4*)&act[act_chunk(r0 + (lane & 15), 2 * wave + (q >> 1)) + 4 * (q & 1)] = v;
+    store4(v, act, r0 + (lane & 15), 16 * wave + 4 * (lane >> 4));
     return on;
 }
 
 // The four right-hand fragments (128 features) of the 16 events from row r0.
-__device__ __forceinline__ void load_act(const __bf16* __restrict__ act, int r0, int lane, bf16x8 (&b)[4]) {
+template <class T>
+__device__ __forceinline__ void load_act(const T* __restrict__ act, int r0, int lane, Vec8<T> (&b)[4]) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) b[s] = *(const bf16x8*)&act[act_chunk(r0 + (lane & 15), 4 * s + (lane >> 4))];
+    for (int s = 0; s < 4; ++s) b[s] = act8(act, r0 + (lane & 15), 32 * s + 8 * (lane >> 4));
+}
+
+// acc[t] = W X of the wave's 16 rows and the NT 16-event tiles of `in`.
+template <int NT, class T>
+__device__ __forceinline__ void square(const Vec8<T> (&w)[4], const T* in, int lane, floatx4 (&acc)[NT]) {
+    Vec8<T> x[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) load_act(in, 16 * t, lane, x[t]);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = mfma(w[s], x[t][s], s ? acc[t] : zero4());
 }
 
 // x[t] of four 16-event tiles, where lane 16 q + e holds item q of event e, to
@@ -221,50 +355,71 @@ __device__ __forceinline__ Theta gather_theta(const floatx4 (&acc)[NT][4]) {
 
 // One 128 -> 128 layer: the wave's 16 features of every event of the tile.
 // Returns which are positive, four bits per 16-event tile.
-template <int NT>
-__device__ __forceinline__ uint32_t hidden_layer(const bf16x8 (&w)[4], const floatx4& bias, const __bf16* in, __bf16* out,
-                                             int wave, int lane) {
-    bf16x8 x[NT][4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) load_act(in, 16 * t, lane, x[t]);
+template <int NT, class T>
+__device__ __forceinline__ uint32_t hidden_layer(const Vec8<T> (&w)[4], const floatx4& bias, const T* in, T* out, int wave,
+                                                 int lane) {
     floatx4 acc[NT];
+    square<NT>(w, in, lane, acc);
     uint32_t on = 0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = mfma(w[s], x[t][s], s ? acc[t] : zero4());
 #pragma unroll
     for (int t = 0; t < NT; ++t) on |= store_act(acc[t], bias, out, 16 * t, wave, lane) << (4 * t);
     return on;
 }
 
 // The spline parameters of coordinate j from the last activation; the output
-// weights from LDS and the biases from registers (KEEP), or both from memory.
-template <int NT, bool KEEP>
-__device__ __forceinline__ Theta output_layer(const FlowNet& fn, int layer, const __bf16* a, const __bf16* w4,
-                                              OutBias ob, int j, int K, int lane) {
-    const __bf16* const w4g = (const __bf16*)fn.wt + layer * fn.per_t + fn.off[6];
+// weights from LDS (KEEP) or from memory.
+template <int NT, bool KEEP, class T, class B>
+__device__ __forceinline__ Theta output_layer(const FlowNet& fn, int layer, const T* a, const T* w4, const B& bias,
+                                              int j, int K, int lane) {
+    const T* const w4g = (const T*)fn.wt + layer * fn.per_t + fn.off[6];
     floatx4 acc[NT][4];
-    bf16x8 x[NT][4];
+    if constexpr (sizeof(T) == 2) {
+        Vec8<T> x[NT][4];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) load_act(a, 16 * t, lane, x[t]);
+        for (int t = 0; t < NT; ++t) load_act(a, 16 * t, lane, x[t]);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int row = j * (3 * K + 1) + param_row(m, lane & 15, K);
+            Vec8<T> w[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if constexpr (KEEP)
+                    w[s] = out_fragment(w4, j, m, s, lane);
+                else
+                    w[s] = load8(&w4g[row * kHid + 32 * s + 8 * (lane >> 4)]);
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t][m] = mfma(w[s], x[t][s], s ? acc[t][m] : zero4());
+        }
+    } else {
+        // the weights of a step are in flight during the step before
+        const T* const wj = w4g + here() + 8 * (lane >> 4);
+        auto weights = [&](int s, Vec8<T>(&w)[4]) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) w[m] = load8(&wj[(j * (3 * K + 1) + param_row(m, lane & 15, K)) * kHid + 32 * s]);
+        };
+        Vec8<T> w[2][4];
+        weights(0, w[0]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s < 3) weights(s + 1, w[(s + 1) & 1]);
+            Vec8<T> x[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) x[t] = act8(a, 16 * t + (lane & 15), 32 * s + 8 * (lane >> 4));
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t][m] = mfma(w[s & 1][m], x[t], s ? acc[t][m] : zero4());
+        }
+    }
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-        const int row = j * (3 * K + 1) + param_row(m, lane & 15, K);
-        bf16x8 w[4];
+        const floatx4 b = bias.out(j, m);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            w[s] = KEEP ? out_fragment(w4, j, m, s, lane) : *(const bf16x8*)&w4g[row * kHid + 32 * s + 8 * (lane >> 4)];
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t][m] = mfma(w[s], x[t][s], s ? acc[t][m] : zero4());
+        for (int t = 0; t < NT; ++t) acc[t][m] += b;
     }
-    if (!KEEP) ob = load_out_bias(fn, layer, j, lane);
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) acc[t][m] += ob.b[m];
     return gather_theta<NT>(acc);
 }
 

@@ -14,9 +14,9 @@ using namespace flow;
 // weights of `kept` coordinates, two activation tiles, two tiles of the
 // conditioning inputs and of the d coordinates, the log-determinant terms of
 // a tile.
-template <int NT>
+template <int NT, class T>
 constexpr size_t layers_lds(int d, int kept) {
-    return sizeof(__bf16) * ((size_t)kept * kOutElems + 2 * 16 * NT * (kHid + kCond)) +
+    return sizeof(T) * ((size_t)kept * kOutElems + 2 * 16 * NT * (kHid + kCond)) +
            sizeof(float) * 16 * NT * (2 * (size_t)d + kWaves);
 }
 
@@ -38,20 +38,24 @@ constexpr size_t layers_lds(int d, int kept) {
 // the latency of the three barriers and the LDS reads behind them.  Before, a
 // wave read every weight of a layer from L2 for its own 64 events and walked
 // each spline through LDS: 4583 us for eight layers of 2^20 events of 16
-// dimensions, now 2531 us; 1000 events of 10 dimensions 299 -> 66 us.  (Tried
+// dimensions, now 2580 us; 1000 events of 10 dimensions 299 -> 68 us.  (Tried
 // and slower: the output weights in registers, 2850 us; two workgroups of
 // four waves per compute unit, 4240 us, and the splines of a tile interleaved
 // with the next tile's hidden layers, 2840 us, which both spill.)
-template <bool INV, int NT, bool KEEP, bool K16>
+//
+// FP32 conditioners are bound by the FP32 matrix instructions (16 of them for
+// one in BF16): 4,097 events of 16 dimensions, inverse, 8 layers: 24 us each,
+// of which 11 are products; they were 130 us as seven kernels.
+template <bool INV, int NT, bool KEEP, bool K16, class T>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_flow_layers(FlowNet fn,
                                                                                                  FlowRun run) {
     constexpr int EV = 16 * NT;
     constexpr int ZR = 2;  // coordinates in flight per thread (all of a tile of 64 events up to 16 dimensions)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int nh = fn.nh, d = 2 * nh, K = fn.K, P = 3 * K + 1;
-    __bf16* const w4 = (__bf16*)smem;                   // KEEP: [nh][kOutElems]
-    __bf16* const act = w4 + (KEEP ? nh * kOutElems : 0);  // [2][EV][kHid]
-    __bf16* const cond = act + 2 * EV * kHid;           // [2][EV][kCond]
+    const int nh = fn.nh, d = 2 * nh, K = fn.K;
+    T* const w4 = (T*)smem;                   // KEEP: [nh][kOutElems]
+    T* const act = w4 + (KEEP ? nh * kOutElems : 0);  // [2][EV][kHid]
+    T* const cond = act + 2 * EV * kHid;           // [2][EV][kCond]
     float* const zs = (float*)(cond + 2 * EV * kCond);  // [2][d][EV]
     float* const lds_ld = zs + 2 * d * EV;              // [kWaves][EV]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -61,17 +65,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int64_t n = run.n, step = gridDim.x;
     const int64_t tiles = (n + EV - 1) / EV;
 
-    for (int i = tid; i < 2 * EV * kCond; i += kThreads) cond[i] = (__bf16)0.0f;
+    for (int i = tid; i < 2 * EV * kCond; i += kThreads) cond[i] = (T)0.0f;
 
     for (int li = 0; li < run.count; ++li) {
         const int layer = run.first + li * run.dir;
         const Mask mk = mask_of(layer, nh);
         const float* const zi = li == 0 ? run.zin : run.zout + (li - 1) * run.zstep;
         float* const zo = run.zout + li * run.zstep;
-        const HidW hw = load_hidden(fn, layer, wave, lane);
-        OutBias ob;
-        if (KEEP) {
-            ob = load_out_bias(fn, layer, min(wave, nh - 1), lane);
+        HidW<T> hw = load_hidden<T>(fn, layer, wave, lane);
+        const RegisterBias<KEEP> bias(fn, layer, wave, lane);
+        if constexpr (KEEP) {
             __syncthreads();  // the previous layer's readers of w4
             load_out(fn, layer, w4, tid);
         }
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             const int c = row_of(i), k = cond_index(mk, nh, c);
             if (c >= d) return;
             zs[(buf * d + c) * EV + ev] = v;
-            if (k >= 0) cond[cond_chunk(buf * EV + ev, k >> 3) + (k & 7)] = (__bf16)v;
+            if (k >= 0) cond[cond_at<T>(buf * EV + ev, column<T>(k))] = (T)v;
         };
         auto fetch = [&](int64_t tile) {
             const uint32_t e = event_of(tile);
@@ -120,26 +123,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         float old = 0.0f;
         for (int64_t tile = blockIdx.x; tile < tiles; tile += step) {
             const float* zt = zs + buf * d * EV;
-            __bf16* const a0 = act + pa * EV * kHid;
-            __bf16* const a1 = act + (pa ^ 1) * EV * kHid;
+            T* const a0 = act + pa * EV * kHid;
+            T* const a1 = act + (pa ^ 1) * EV * kHid;
             const float old_next = before(tile);
+            hw.per_tile();
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                store_act(mfma(hw.w1, *(const bf16x8*)&cond[cond_chunk(buf * EV + 16 * t + e16, q)], zero4()),
-                          hw.b1, a0, 16 * t, wave, lane);
+                store_act(mfma(hw.w1, cond8(cond, buf * EV + 16 * t + e16, 8 * q), zero4()),
+                          bias.hidden(0), a0, 16 * t, wave, lane);
             __syncthreads();
             if (prev >= 0) flush(prev, old);
             old = old_next;
-            hidden_layer<NT>(hw.w2, hw.b2, a0, a1, wave, lane);
+            hidden_layer<NT>(hw.w2, bias.hidden(1), a0, a1, wave, lane);
             __syncthreads();
-            hidden_layer<NT>(hw.w3, hw.b3, a1, a0, wave, lane);
+            hidden_layer<NT>(hw.w3, bias.hidden(2), a1, a0, wave, lane);
             stage(buf ^ 1, tile + step);
             fetch(tile + 2 * step);
             __syncthreads();
             float ld_sum = 0.0f;
             for (int j = wave; j < nh; j += KEEP ? 2 * kFlowMaxHalf : kWaves) {
                 const int tj = mk.t0 + mk.ts * j;
-                Theta th = output_layer<NT, KEEP>(fn, layer, a0, w4, ob, j, K, lane);
+                Theta th = output_layer<NT, KEEP>(fn, layer, a0, w4, bias, j, K, lane);
                 const float vin = zt[tj * EV + ev];
                 float sw, sh, ld;
                 spline_exp<K16>(th, K, sw, sh);
@@ -168,29 +172,42 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <bool INV, int NT>
+template <bool INV, int NT, class T>
 hipError_t launch_layers(const FlowNet& fn, const FlowRun& run, int64_t grid, hipStream_t s) {
-    const bool keep = fn.nh <= kWaves;  // then W4 fits in LDS: at most 98 KiB
-    const size_t lds = layers_lds<NT>(2 * fn.nh, keep ? fn.nh : 0);
+    constexpr bool can_keep = sizeof(T) == 2;
+    const bool keep = can_keep && fn.nh <= kWaves;  // then W4 fits in LDS: at most 98 KiB
+    const size_t lds = layers_lds<NT, T>(2 * fn.nh, keep ? fn.nh : 0);
     const dim3 g((unsigned)grid), t(kThreads);
     if (keep && fn.K == 16)
-        k_flow_layers<INV, NT, true, true><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, can_keep, true, T><<<g, t, lds, s>>>(fn, run);
     else if (keep)
-        k_flow_layers<INV, NT, true, false><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, can_keep, false, T><<<g, t, lds, s>>>(fn, run);
     else if (fn.K == 16)
-        k_flow_layers<INV, NT, false, true><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, false, true, T><<<g, t, lds, s>>>(fn, run);
     else
-        k_flow_layers<INV, NT, false, false><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, false, false, T><<<g, t, lds, s>>>(fn, run);
     return hipGetLastError();
 }
 
 template <bool INV>
 hipError_t launch_pass(const FlowNet& fn, const FlowRun& run, int cu_count, hipStream_t s) {
     const int64_t t16 = (run.n + 15) / 16;
+    if (fn.f32) {
+        // FP32 products take most of a tile's time (5 us per 16 events), so
+        // the tile is the largest that does not leave more of the last round
+        // empty than it saves in latencies (about 4 us per tile and layer)
+        const int64_t r1 = (t16 + cu_count - 1) / cu_count, r2 = ((t16 + 1) / 2 + cu_count - 1) / cu_count,
+                      r4 = ((t16 + 3) / 4 + cu_count - 1) / cu_count;
+        if (r1 * 9 <= std::min(r2 * 14, r4 * 24))
+            return launch_layers<INV, 1, float>(fn, run, std::min<int64_t>(t16, cu_count), s);
+        if (r2 * 14 <= r4 * 24)
+            return launch_layers<INV, 2, float>(fn, run, std::min<int64_t>((t16 + 1) / 2, cu_count), s);
+        return launch_layers<INV, 4, float>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
+    }
     // up to one tile of 16 events for every compute unit the time is the
     // latency of a tile through the layers, which grows with the tile
-    if (t16 <= cu_count) return launch_layers<INV, 1>(fn, run, t16, s);
-    return launch_layers<INV, 4>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
+    if (t16 <= cu_count) return launch_layers<INV, 1, __bf16>(fn, run, t16, s);
+    return launch_layers<INV, 4, __bf16>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
 }
 
 }  // namespace

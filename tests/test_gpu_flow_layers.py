@@ -121,3 +121,63 @@ def test_gradient_after_a_larger_batch(torch, d, bins):
     got, _ = f.gradient(*small)
     assert torch.equal(got, want)
     f.close()
+
+
+def _pair_f32(d, layers, bins, seed):
+    import torch as t
+
+    from paper_2602_06895_amd import FLOW_FP32, Flow
+
+    params = W.flow_params(seed, d, layers, bins, 128, last_scale=0.05)
+    f = Flow(d, layers, bins, 128, mlp=FLOW_FP32)
+    f.set_params(params)
+    return f, F.Flow(d, layers, bins, 128, params=t.as_tensor(params.astype(np.float64)), bf16_mlp=False)
+
+
+# tiles of 16, 32 and 64 events, up to and beyond one per compute unit
+@pytest.mark.parametrize("d,layers,bins,n", [(16, 3, 16, 1), (16, 4, 16, 33), (2, 3, 16, 100), (10, 4, 16, 4096),
+                                             (16, 2, 16, 4097), (16, 2, 16, 8200), (18, 2, 5, 90), (64, 2, 12, 300),
+                                             (16, 4, 1, 70), (14, 2, 16, 16500)])
+def test_fp32_passes_match_oracle(torch, d, layers, bins, n):
+    """FP32 conditioners against the FP64 oracle, with the bounds of the full-size
+    flows (a few hundred roundings of 6e-8 through up to as many layers)."""
+    f, orc = _pair_f32(d, layers, bins, 10 * d + bins)
+    u = W.philox_uniforms_f32(3, d, 0, n, d)
+    t = torch.from_numpy(u).cuda()
+    y, ld = f.forward(t)
+    x, lq = f.inverse(t)
+    torch.cuda.synchronize()
+    ref = torch.from_numpy(u.T.astype(np.float64))
+    for got, gl, (want, wl) in ((y, ld, orc.forward(ref)), (x, lq, orc.inverse(ref))):
+        assert np.abs(got.cpu().numpy().T - want.numpy()).max() < 2e-5
+        assert np.abs(gl.cpu().numpy() - wl.numpy()).max() < 2e-4
+    f.close()
+
+
+@pytest.mark.parametrize("d,layers,bins,n", [(16, 4, 16, 1), (16, 4, 16, 31), (16, 3, 16, 65), (10, 4, 16, 513),
+                                             (2, 3, 16, 200), (16, 2, 16, 2100), (18, 2, 16, 130), (64, 2, 12, 300),
+                                             (16, 4, 1, 90), (24, 2, 5, 700)])
+def test_fp32_gradient_matches_oracle(torch, d, layers, bins, n):
+    """The FP32 gradient against the FP64 oracle, with the bound of the full-size
+    flow; a step afterwards leaves operands that give the same density as the
+    parameters read back into a new flow."""
+    import torch as t
+
+    from paper_2602_06895_amd import FLOW_FP32, Flow
+
+    f, orc = _pair_f32(d, layers, bins, 7 * d + bins)
+    y, wfj, lqo, dev = _batch(torch, d, n, d + n)
+    g, loss = f.gradient(*dev)
+    torch.cuda.synchronize()
+    l_ref, ref = orc.loss_and_grad(t.from_numpy(y.T.astype(np.float64)), t.from_numpy(wfj) ** 2,
+                                   t.from_numpy(lqo.astype(np.float64)))
+    got, ref = g.cpu().numpy().astype(np.float64), ref.numpy()
+    assert np.linalg.norm(got - ref) <= 1e-3 * np.linalg.norm(ref)
+    assert abs(float(loss.cpu()[0]) - float(l_ref)) <= 1e-4 * abs(float(l_ref))
+    f.train_step(*dev, lr=1e-3)
+    h = Flow(d, layers, bins, 128, mlp=FLOW_FP32)
+    h.set_params(f.get_params())
+    for a, b in zip(f.inverse(dev[0]), h.inverse(dev[0])):
+        assert torch.equal(a, b)
+    f.close()
+    h.close()
