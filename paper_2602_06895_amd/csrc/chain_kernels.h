@@ -128,8 +128,21 @@ __device__ __forceinline__ double finish_event(const ChannelTab* __restrict__ ct
     return w;
 }
 
+// Waves per SIMD that a class kernel is compiled for.  These kernels walk the
+// channel's tables, so a wave issues a vector instruction every 18 cycles and
+// the time goes down with the waves in flight.  A class is held to the next
+// register limit (512 / waves) where it exceeds it by a few registers; the
+// others (1 -> 3 decays, Chili, the largest slots in FP64) would spill
+// hundreds.
+constexpr bool tree_kinds(int kinds) { return (kinds & (KIND_CHILI | KIND_DEC3 | KIND_ST)) == 0; }
+constexpr int map_waves(int ns, int kinds) { return tree_kinds(kinds) ? (ns == 6 ? 3 : (ns == 10 ? 2 : 1)) : 1; }
+constexpr int sample_waves(int ns, int kinds, bool mix) {
+    return mix && ns == 14 && tree_kinds(kinds) ? 2 : map_waves(ns, kinds);
+}
+constexpr int inverse_waves(int ns, int kinds) { return ns == 6 && !(kinds & KIND_DEC3) ? 4 : 1; }
+
 template <int NS, int NI, int KINDS, bool MIX>
-__global__ __launch_bounds__(kBlock) void k_map(const ChannelTab* __restrict__ ct, const ProcessTab* __restrict__ pt,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(map_waves(NS, KINDS)))) void k_map(const ChannelTab* __restrict__ ct, const ProcessTab* __restrict__ pt,
                                                 const double* __restrict__ grid, int nb, double s_lab, int np,
                                                 int64_t n, const double* __restrict__ y, double* __restrict__ p,
                                                 double* __restrict__ x1x2, double* __restrict__ jac,
@@ -285,10 +298,14 @@ __device__ __forceinline__ void sample_loop(const ChannelTab* __restrict__ cts, 
     if (vpart) {
         for (int i = threadIdx.x; i < kWaves * vstride; i += kBlock) vh[i] = 0.0;
     }
+    // this block's next tile: the tiles of consecutive channels follow each
+    // other, so a remainder is needed only for the first channel of a launch and
+    // after a channel that was left out (one for each of 24 channels took a
+    // tenth of the time of a block with two tiles)
+    int64_t tl = -1;
     auto run = [&](int c, auto&& tile) {
         const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
-        // this block's first tile of the channel
-        int64_t tl = t0 + ((((int64_t)blockIdx.x - t0) % G) + G) % G;
+        if (tl < t0) tl = t0 + ((((int64_t)blockIdx.x - t0) % G) + G) % G;
         if (tl >= t1) return;
         const int nb = chan_nb[c];
         const int dims = cts[c].dims;
@@ -358,7 +375,7 @@ __device__ __forceinline__ void sample_loop(const ChannelTab* __restrict__ cts, 
 // The fused multichannel sample with the channel tables read from device
 // memory (every channel of a context through one register and kind class).
 template <int NS, int NI, int KINDS, bool MIX>
-__global__ __launch_bounds__(kBlock) void k_sample(const ChannelTab* __restrict__ cts, const ProcessTab* __restrict__ pts,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sample_waves(NS, KINDS, MIX)))) void k_sample(const ChannelTab* __restrict__ cts, const ProcessTab* __restrict__ pts,
                                                    const double* __restrict__ grids, const int64_t* __restrict__ grid_off,
                                                    const int32_t* __restrict__ chan_nb,
                                                    const SampleCall* __restrict__ call, uint64_t seed, uint64_t sid,
@@ -435,7 +452,7 @@ __device__ __forceinline__ void chili_unmap(const ChannelTab* __restrict__ ct, d
 // P = p_A + p_B, per decay the angles of the first child in its parent's
 // rest frame, then the inverse VEGAS map.  FP64.
 template <int NS, int NI, int KINDS>
-__global__ __launch_bounds__(kBlock) void k_inverse(const ChannelTab* __restrict__ ct, const double* __restrict__ grid,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(inverse_waves(NS, KINDS)))) void k_inverse(const ChannelTab* __restrict__ ct, const double* __restrict__ grid,
                                                     int nb, double s_lab, int np, int64_t n,
                                                     const double* __restrict__ p, const double* __restrict__ x1x2,
                                                     double* __restrict__ y) {
