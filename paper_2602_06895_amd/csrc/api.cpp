@@ -47,7 +47,7 @@ struct msx_ctx {
     int64_t obs_hist_cap = 0;
     int64_t* d_ublk = nullptr;  // unweighting block offsets
     int64_t ublk_cap = 0;
-    double* d_inv = nullptr;  // multichannel density scratch: y [max dims][n] then jac [n]
+    double* d_inv = nullptr;  // multichannel density scratch: y [channels][max dims][n] then jac [channels][n]
     int64_t inv_cap = 0;      // doubles
     int64_t vpart_cap = 0;
     double* d_unw = nullptr;  // 3 * 4096 bucket words + 2 * 1024 partials + 2 + the search state (3)
@@ -154,6 +154,17 @@ msx_status ensure_tiles(msx_ctx* ctx, int64_t tiles) {
     MSX_HIP(ctx, dmalloc(&ctx->d_tile, 4 * tiles), "tile scratch");
     ctx->tile_cap = tiles;
     return MSX_OK;
+}
+
+// One channel of a map or inverse launch.
+LaunchChans chans_of(const msx_ctx* ctx, int channel) {
+    LaunchChans lc{};
+    lc.cts = ctx->d_chans;
+    lc.grids = ctx->d_grids;
+    lc.grid_off = ctx->d_grid_off;
+    lc.nb = ctx->d_chan_nb;
+    lc.c[0] = channel;
+    return lc;
 }
 
 int sample_grid(const msx_ctx* ctx) { return ctx->grid > 0 ? ctx->grid : ctx->cu_count * 8; }
@@ -399,8 +410,7 @@ msx_status msx_map(msx_ctx* ctx, int32_t channel, int64_t n, const double* y, do
     const ChannelTab& t = ctx->comp.chans[channel];
     const ProcessTab& pt = ctx->comp.procs[m.process];
     MSX_HIP(ctx,
-            launch_map(ctx->d_chans + channel, ctx->d_procs + m.process, ctx->d_grids + ctx->grid_off[channel], m.nbins,
-                       m.dims, t.n_slots, t.n_inv, t.kinds, ctx->mixed, pt.s_lab, m.n_momenta, n, y, p, x1x2, jac, w,
+            launch_map(chans_of(ctx, channel), ctx->d_procs + m.process, m.dims, m.nbins, t.n_slots, t.n_inv, t.kinds, ctx->mixed, pt.s_lab, m.n_momenta, n, y, p, x1x2, jac, w,
                        ctx->cu_count,
                        (hipStream_t)stream),
             "map launch");
@@ -421,8 +431,7 @@ msx_status msx_inverse_map(msx_ctx* ctx, int32_t channel, int64_t n, const doubl
     const ChannelTab& t = ctx->comp.chans[channel];
     const ProcessTab& pt = ctx->comp.procs[m.process];
     MSX_HIP(ctx,
-            launch_inverse(ctx->d_chans + channel, ctx->d_grids + ctx->grid_off[channel], m.nbins, m.dims, t.n_slots,
-                           t.n_inv, t.kinds, pt.s_lab, m.n_momenta, n, p, x1x2, y, jac, ctx->cu_count,
+            launch_inverse(chans_of(ctx, channel), 1, m.dims, m.nbins, t.n_slots, t.n_inv, t.kinds, pt.s_lab, m.n_momenta, n, p, x1x2, y, jac, ctx->cu_count,
                            (hipStream_t)stream),
             "inverse launch");
     return MSX_OK;
@@ -449,29 +458,70 @@ msx_status msx_multichannel_density(msx_ctx* ctx, int32_t process, int64_t n, co
         if (!(alpha[i] >= 0.0)) return fail(ctx, MSX_ERR_ARG, "alpha must be >= 0");
     if (n == 0) return MSX_OK;
     if (msx_status st = set_device(ctx)) return st;
-    const int64_t need = (int64_t)(dmax + 1) * n;
-    if (need > ctx->inv_cap) {
-        // the previous scratch may still be read by work in flight
-        MSX_HIP(ctx, hipDeviceSynchronize(), "synchronize");
-        if (ctx->d_inv) MSX_HIP(ctx, hipFree(ctx->d_inv), "hipFree");
-        ctx->d_inv = nullptr;
-        ctx->inv_cap = 0;
-        MSX_HIP(ctx, dmalloc(&ctx->d_inv, need), "density scratch");
-        ctx->inv_cap = need;
-    }
-    double* y = ctx->d_inv;
-    double* jac = ctx->d_inv + (int64_t)dmax * n;
     hipStream_t s = (hipStream_t)stream;
-    for (size_t i = 0; i < chans.size(); ++i) {
-        const int c = chans[i];
-        const ChannelMeta& m = ctx->comp.meta[c];
-        const ChannelTab& t = ctx->comp.chans[c];
-        const ProcessTab& pt = ctx->comp.procs[m.process];
+    // Runs of channels of one class go into one launch each of the inverse and
+    // of the Jacobian, whose waves wait for one another: eight channels of
+    // 200,000 events take 3 waves per SIMD each, where 4 (inverse) and 3 fit.
+    // Up to kDensityScratch of scratch; at least one channel at a time.
+    constexpr int64_t kDensityScratch = (int64_t)2 << 30;
+    const int64_t one = (int64_t)(dmax + 1) * n;  // doubles per channel
+    auto run_from = [&](size_t i, int64_t limit) {
+        const ChannelTab& a = ctx->comp.chans[chans[i]];
+        size_t k = i + 1;
+        for (; k < chans.size() && (int64_t)(k - i) < std::min<int64_t>(limit, kMaxLaunchChans); ++k) {
+            const ChannelTab& b = ctx->comp.chans[chans[k]];
+            if (!same_chain_class(a.n_slots, a.n_inv, a.kinds, b.n_slots, b.n_inv, b.kinds)) break;
+        }
+        return k;
+    };
+    int64_t limit = std::max<int64_t>(1, kDensityScratch / (int64_t)sizeof(double) / one), most = 1;
+    for (size_t i = 0; i < chans.size();) {
+        const size_t k = run_from(i, limit);
+        most = std::max<int64_t>(most, (int64_t)(k - i));
+        i = k;
+    }
+    if (most * one > ctx->inv_cap) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        MSX_HIP(ctx, hipStreamIsCapturing(s, &capture), "capture status");
+        if (capture != hipStreamCaptureStatusNone && one <= ctx->inv_cap) {
+            most = ctx->inv_cap / one;  // no allocation while capturing
+        } else {
+            // the previous scratch may still be read by work in flight
+            MSX_HIP(ctx, hipDeviceSynchronize(), "synchronize");
+            if (ctx->d_inv) MSX_HIP(ctx, hipFree(ctx->d_inv), "hipFree");
+            ctx->d_inv = nullptr;
+            ctx->inv_cap = 0;
+            if (most > 1 && dmalloc(&ctx->d_inv, most * one) != hipSuccess) {
+                (void)hipGetLastError();
+                ctx->d_inv = nullptr;
+                most = 1;
+            }
+            if (!ctx->d_inv) MSX_HIP(ctx, dmalloc(&ctx->d_inv, most * one), "density scratch");
+            ctx->inv_cap = most * one;
+        }
+        limit = std::min(limit, most);
+    }
+    for (size_t i = 0; i < chans.size();) {
+        const size_t k = run_from(i, limit);
+        LaunchChans lc = chans_of(ctx, chans[i]);
+        lc.y_step = (int64_t)dmax * n;
+        DensityAlpha da{};
+        int dims = 0, nb = 0;
+        for (size_t j = i; j < k; ++j) {
+            lc.c[j - i] = chans[j];
+            da.a[j - i] = alpha[j];
+            dims = std::max(dims, ctx->comp.meta[chans[j]].dims);
+            nb = std::max(nb, ctx->comp.meta[chans[j]].nbins);
+        }
+        const ChannelTab& t = ctx->comp.chans[chans[i]];
+        const int count = (int)(k - i);
+        double* jac = ctx->d_inv + count * lc.y_step;
         MSX_HIP(ctx,
-                launch_inverse(ctx->d_chans + c, ctx->d_grids + ctx->grid_off[c], m.nbins, m.dims, t.n_slots, t.n_inv,
-                               t.kinds, pt.s_lab, m.n_momenta, n, p, x1x2, y, jac, ctx->cu_count, s),
+                launch_inverse(lc, count, dims, nb, t.n_slots, t.n_inv, t.kinds, ctx->comp.procs[process].s_lab,
+                               m0.n_momenta, n, p, x1x2, ctx->d_inv, jac, ctx->cu_count, s),
                 "inverse launch");
-        MSX_HIP(ctx, launch_density_add(g, jac, alpha[i], n, i == 0, s), "density launch");
+        MSX_HIP(ctx, launch_density_add(g, jac, da, count, n, i == 0, s), "density launch");
+        i = k;
     }
     return MSX_OK;
 }
@@ -529,7 +579,7 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
     call.n_chan = C;
     call.ept = ctx->ept;
     const int64_t T = (int64_t)sample_block() * ctx->ept;
-    int64_t N = 0, tiles = 0;
+    int64_t N = 0, tiles = 0, chan_tiles = 0;  // chan_tiles: the most of a channel
     bool any_hadronic = false;
     int max_slots = 0, max_inv = 0, kinds = 0;
     for (int c = 0; c < C; ++c) {
@@ -539,6 +589,7 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
         if (counts[c] > INT64_MAX / 4 - N) return fail(ctx, MSX_ERR_ARG, "event count overflow");
         N += counts[c];
         tiles += (counts[c] + T - 1) / T;
+        chan_tiles = std::max(chan_tiles, (counts[c] + T - 1) / T);
         if (counts[c] > 0) {
             any_hadronic = any_hadronic || ctx->comp.meta[c].hadronic;
             max_slots = std::max(max_slots, ctx->comp.chans[c].n_slots);
@@ -571,7 +622,7 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
             launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, ctx->d_call, C,
                           max_slots, max_inv, kinds, ctx->mixed, ctx->lds_max, seed, stream_id, nullptr,
                           counter_offset, ctx->max_np, N, p, x1x2, w, chan, noalloc ? ctx->d_noalloc : ctx->d_tile,
-                          tiles, ctx->d_stats, grid, s, acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off,
+                          chan_tiles, ctx->d_stats, grid, s, acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off,
                           ctx->hist_total, ctx->d_hist, jit_of(ctx)),
             "sample launch");
     return MSX_OK;
@@ -1106,7 +1157,7 @@ msx_status sample_with_flows(msx_ctx* ctx, const int64_t* counts, uint64_t seed,
     call.n_chan = C;
     call.ept = ctx->ept;
     const int64_t T = (int64_t)sample_block() * ctx->ept;
-    int64_t N = 0, tiles = 0;
+    int64_t N = 0, tiles = 0, chan_tiles = 0;  // chan_tiles: the most of a channel
     bool any_hadronic = false;
     int max_slots = 0, max_inv = 0, kinds = 0;
     for (int c = 0; c < C; ++c) {
@@ -1121,6 +1172,7 @@ msx_status sample_with_flows(msx_ctx* ctx, const int64_t* counts, uint64_t seed,
             call.skip_mask |= 1ull << c;
         } else {
             tiles += (counts[c] + T - 1) / T;
+            chan_tiles = std::max(chan_tiles, (counts[c] + T - 1) / T);
             if (counts[c] > 0) {
                 max_slots = std::max(max_slots, ctx->comp.chans[c].n_slots);
                 max_inv = std::max(max_inv, ctx->comp.chans[c].n_inv);
@@ -1151,7 +1203,7 @@ msx_status sample_with_flows(msx_ctx* ctx, const int64_t* counts, uint64_t seed,
         MSX_HIP(ctx,
                 launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, ctx->d_call,
                               C, max_slots, max_inv, kinds, ctx->mixed, ctx->lds_max, seed, stream_id, nullptr,
-                              counter_offset, ctx->max_np, N, p, x1x2, w, chan, ctx->d_tile, tiles,
+                              counter_offset, ctx->max_np, N, p, x1x2, w, chan, ctx->d_tile, chan_tiles,
                               ctx->d_stats, grid, s, acc ? ctx->d_vtiles : nullptr, ctx->vstride, ctx->d_hist_off, ctx->hist_total,
                               ctx->d_hist, jit_of(ctx)),
                 "sample launch");

@@ -142,11 +142,15 @@ constexpr int sample_waves(int ns, int kinds, bool mix) {
 constexpr int inverse_waves(int ns, int kinds) { return ns == 6 && !(kinds & KIND_DEC3) ? 4 : 1; }
 
 template <int NS, int NI, int KINDS, bool MIX>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(map_waves(NS, KINDS)))) void k_map(const ChannelTab* __restrict__ ct, const ProcessTab* __restrict__ pt,
-                                                const double* __restrict__ grid, int nb, double s_lab, int np,
-                                                int64_t n, const double* __restrict__ y, double* __restrict__ p,
-                                                double* __restrict__ x1x2, double* __restrict__ jac,
-                                                double* __restrict__ w) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(map_waves(NS, KINDS)))) void k_map(
+    LaunchChans lc, const ProcessTab* __restrict__ pt, double s_lab, int np, int64_t n, const double* __restrict__ y,
+    double* __restrict__ p, double* __restrict__ x1x2, double* __restrict__ jac, double* __restrict__ w) {
+    const int c = lc.c[blockIdx.y];
+    const ChannelTab* __restrict__ ct = lc.cts + c;
+    const double* __restrict__ grid = lc.grids + lc.grid_off[c];
+    const int nb = lc.nb[c];
+    y += blockIdx.y * lc.y_step;
+    jac += blockIdx.y * n;  // more than one channel: Jacobians only
     extern __shared__ double lds[];
     double* lg = lds + kQRows * kBlock;
     const LdsQ q{lds + threadIdx.x};
@@ -375,15 +379,12 @@ __device__ __forceinline__ void sample_loop(const ChannelTab* __restrict__ cts, 
 // The fused multichannel sample with the channel tables read from device
 // memory (every channel of a context through one register and kind class).
 template <int NS, int NI, int KINDS, bool MIX>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sample_waves(NS, KINDS, MIX)))) void k_sample(const ChannelTab* __restrict__ cts, const ProcessTab* __restrict__ pts,
-                                                   const double* __restrict__ grids, const int64_t* __restrict__ grid_off,
-                                                   const int32_t* __restrict__ chan_nb,
-                                                   const SampleCall* __restrict__ call, uint64_t seed, uint64_t sid,
-                                                   const uint64_t* __restrict__ ctr_dev, uint64_t ctr_off, int np,
-                                                   int64_t ld, double* __restrict__ p, double* __restrict__ x1x2,
-                                                   double* __restrict__ w, int32_t* __restrict__ chan_out,
-                                                   double* __restrict__ tile_stats, int grid_doubles,
-                                                   double* __restrict__ vpart, int vstride) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sample_waves(NS, KINDS, MIX)))) void k_sample(
+    const ChannelTab* __restrict__ cts, const ProcessTab* __restrict__ pts, const double* __restrict__ grids,
+    const int64_t* __restrict__ grid_off, const int32_t* __restrict__ chan_nb, const SampleCall* __restrict__ call,
+    uint64_t seed, uint64_t sid, const uint64_t* __restrict__ ctr_dev, uint64_t ctr_off, int np, int64_t ld,
+    double* __restrict__ p, double* __restrict__ x1x2, double* __restrict__ w, int32_t* __restrict__ chan_out,
+    double* __restrict__ tile_stats, int grid_doubles, double* __restrict__ vpart, int vstride) {
     sample_loop<stage_rows<NS, NI>()>(
         cts, grids, grid_off, chan_nb, call, seed, sid, ctr_dev, ctr_off, np, ld, p, x1x2, w, chan_out, tile_stats,
         grid_doubles, vpart, vstride, [&](auto& run) {
@@ -452,10 +453,14 @@ __device__ __forceinline__ void chili_unmap(const ChannelTab* __restrict__ ct, d
 // P = p_A + p_B, per decay the angles of the first child in its parent's
 // rest frame, then the inverse VEGAS map.  FP64.
 template <int NS, int NI, int KINDS>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(inverse_waves(NS, KINDS)))) void k_inverse(const ChannelTab* __restrict__ ct, const double* __restrict__ grid,
-                                                    int nb, double s_lab, int np, int64_t n,
-                                                    const double* __restrict__ p, const double* __restrict__ x1x2,
-                                                    double* __restrict__ y) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(inverse_waves(NS, KINDS)))) void k_inverse(
+    LaunchChans lc, double s_lab, int np, int64_t n, const double* __restrict__ p, const double* __restrict__ x1x2,
+    double* __restrict__ y) {
+    const int c = lc.c[blockIdx.y];
+    const ChannelTab* __restrict__ ct = lc.cts + c;
+    const double* __restrict__ grid = lc.grids + lc.grid_off[c];
+    const int nb = lc.nb[c];
+    y += blockIdx.y * lc.y_step;
     constexpr int NF = NS / 2 + 1;
     constexpr int kRows = stage_rows<NS, NI>();
     extern __shared__ double lds[];

@@ -48,8 +48,8 @@ hipError_t launch_chain_class(int kc, const ChainLaunch& a) {
                 a.cts, a.pts, a.grids, a.grid_off, a.chan_nb, a.call, a.seed, a.sid, a.ctr_dev, a.ctr_off, a.np, a.n,
                 a.p, a.x1x2, a.w, a.chan, a.tile_stats, (int)(a.lds / sizeof(double)), a.vpart, a.vstride);
         else
-            k_map<NS, NI, K, MIX><<<a.grid, kBlock, lds, a.stream>>>(a.cts, a.pts, a.grids, a.nb, a.s_lab, a.np, a.n,
-                                                                         a.y, a.p, a.x1x2, a.jac, a.w);
+            k_map<NS, NI, K, MIX><<<dim3((unsigned)a.grid, (unsigned)a.n_chans), kBlock, lds, a.stream>>>(
+                a.chans, a.pts, a.s_lab, a.np, a.n, a.y, a.p, a.x1x2, a.jac, a.w);
     });
     if (err != hipSuccess) return err;
     return hipGetLastError();
@@ -69,8 +69,8 @@ hipError_t launch_inverse_class(int kc, const ChainLaunch& a) {
                                       (int)li);
             if (err != hipSuccess) return;
         }
-        k_inverse<NS, NI, K><<<a.grid, kBlock, li, a.stream>>>(a.cts, a.grids, a.nb, a.s_lab, a.np, a.n, a.p_in,
-                                                              a.x1x2_in, a.y_out);
+        k_inverse<NS, NI, K><<<dim3((unsigned)a.grid, (unsigned)a.n_chans), kBlock, li, a.stream>>>(
+            a.chans, a.s_lab, a.np, a.n, a.p_in, a.x1x2_in, a.y_out);
     });
     if (err != hipSuccess) return err;
     return hipGetLastError();

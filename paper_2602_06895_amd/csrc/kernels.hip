@@ -479,16 +479,19 @@ __global__ __launch_bounds__(64) void k_hist_reduce(const double* __restrict__ p
     if (threadIdx.x == 0) out[(int)(blockIdx.x & 1) * nb + (int)(blockIdx.x >> 1)] = s;
 }
 
-// Global multichannel density: g += alpha / J of one channel (g = alpha / J
-// for the first channel).  A channel whose chain cuts the event (J = 0)
+// Global multichannel density: g += alpha / J of a launch's channels, in order
+// (first: from zero).  A channel whose chain cuts the event (J = 0)
 // contributes nothing.
 __global__ __launch_bounds__(kBlock) void k_density_add(double* __restrict__ g, const double* __restrict__ jac,
-                                                        double alpha, int64_t n, int first) {
+                                                        DensityAlpha alpha, int n_chans, int64_t n, int first) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double j = jac[i];
-    const double t = j > 0.0 ? alpha / j : 0.0;
-    g[i] = first ? t : g[i] + t;
+    double sum = first ? 0.0 : g[i];
+    for (int c = 0; c < n_chans; ++c) {
+        const double j = jac[c * n + i];
+        sum += j > 0.0 ? alpha.a[c] / j : 0.0;
+    }
+    g[i] = sum;
 }
 
 __global__ void k_set_call(SampleCall call, SampleCall* __restrict__ dev) {
@@ -847,10 +850,11 @@ hipError_t launch_unweight(const double* w, int64_t n, double w_max, uint64_t se
     return hipGetLastError();
 }
 
-hipError_t launch_density_add(double* g, const double* jac, double alpha, int64_t n, bool first, hipStream_t s) {
+hipError_t launch_density_add(double* g, const double* jac, const DensityAlpha& alpha, int n_chans, int64_t n, bool first,
+                              hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t b = (n + kBlock - 1) / kBlock;
-    k_density_add<<<dim3((unsigned)b), dim3(kBlock), 0, s>>>(g, jac, alpha, n, first ? 1 : 0);
+    k_density_add<<<dim3((unsigned)b), dim3(kBlock), 0, s>>>(g, jac, alpha, n_chans, n, first ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -861,19 +865,18 @@ hipError_t launch_uniform(uint64_t seed, uint64_t sid, uint64_t e0, int64_t n, i
     return hipGetLastError();
 }
 
-hipError_t launch_map(const ChannelTab* ct, const ProcessTab* pt, const double* grid, int nb, int dims, int n_slots,
-                      int n_inv, int kinds, int mixed, double s_lab, int np, int64_t n, const double* y, double* p,
-                      double* x1x2, double* jac, double* w, int cu_count, hipStream_t s) {
+hipError_t launch_map(const LaunchChans& chans, const ProcessTab* pt, int dims, int nb, int n_slots, int n_inv, int kinds,
+                      int mixed, double s_lab, int np, int64_t n, const double* y, double* p, double* x1x2, double* jac,
+                      double* w, int cu_count, hipStream_t s) {
     if (n == 0) return hipSuccess;
     ChainLaunch a{};
     a.sample = false;
     a.lds = sizeof(double) * (size_t)dims * (nb + 1);
     a.grid = grid_for(n, cu_count * 8);
     a.stream = s;
-    a.cts = ct;
     a.pts = pt;
-    a.grids = grid;
-    a.nb = nb;
+    a.chans = chans;
+    a.n_chans = 1;
     a.s_lab = s_lab;
     a.np = np;
     a.n = n;
@@ -885,7 +888,11 @@ hipError_t launch_map(const ChannelTab* ct, const ProcessTab* pt, const double* 
     return launch_chain(reg_class(n_slots, n_inv), kind_class(kinds), mixed, a);
 }
 
-hipError_t launch_inverse(const ChannelTab* ct, const double* grid, int nb, int dims, int n_slots, int n_inv, int kinds,
+bool same_chain_class(int n_slots_a, int n_inv_a, int kinds_a, int n_slots_b, int n_inv_b, int kinds_b) {
+    return reg_class(n_slots_a, n_inv_a) == reg_class(n_slots_b, n_inv_b) && kind_class(kinds_a) == kind_class(kinds_b);
+}
+
+hipError_t launch_inverse(const LaunchChans& chans, int n_chans, int dims, int nb, int n_slots, int n_inv, int kinds,
                           double s_lab, int np, int64_t n, const double* p, const double* x1x2, double* y, double* jac,
                           int cu_count, hipStream_t s) {
     if (n == 0) return hipSuccess;
@@ -894,9 +901,8 @@ hipError_t launch_inverse(const ChannelTab* ct, const double* grid, int nb, int 
     a.lds = sizeof(double) * (size_t)dims * (nb + 1);
     a.grid = grid_for(n, cu_count * 8);
     a.stream = s;
-    a.cts = ct;
-    a.grids = grid;
-    a.nb = nb;
+    a.chans = chans;
+    a.n_chans = n_chans;
     a.s_lab = s_lab;
     a.np = np;
     a.n = n;
@@ -906,14 +912,13 @@ hipError_t launch_inverse(const ChannelTab* ct, const double* grid, int nb, int 
     // always the FP64 units
     hipError_t err = launch_chain(reg_class(n_slots, n_inv), kind_class(kinds), 0, a);
     if (err != hipSuccess || !jac) return err;
-    // the forward Jacobian at y: the map kernel without momentum stores
+    // the forward Jacobians at y: the map kernel without momentum stores
     ChainLaunch m{};
     m.lds = a.lds;
     m.grid = a.grid;
     m.stream = s;
-    m.cts = ct;
-    m.grids = grid;
-    m.nb = nb;
+    m.chans = chans;
+    m.n_chans = n_chans;
     m.s_lab = s_lab;
     m.np = np;
     m.n = n;

@@ -18,8 +18,9 @@ struct ChainLaunch {
     const ChannelTab* cts;
     const ProcessTab* pts;
     const double* grids;
-    // map
-    int nb;
+    // map, inverse
+    LaunchChans chans;
+    int n_chans;
     double s_lab;
     const double* y;
     double* jac;
@@ -55,11 +56,16 @@ hipError_t launch_inverse_class(int kind_class, const ChainLaunch& a);
 
 hipError_t launch_uniform(uint64_t seed, uint64_t sid, uint64_t e0, int64_t n, int d, double* y, hipStream_t s);
 
-hipError_t launch_map(const ChannelTab* ct, const ProcessTab* pt, const double* grid, int nb, int dims, int n_slots,
-                      int n_inv, int kinds, int mixed, double s_lab, int np, int64_t n, const double* y, double* p,
-                      double* x1x2, double* jac, double* w, int cu_count, hipStream_t s);
+// The events of one channel (chans.c[0]).
+hipError_t launch_map(const LaunchChans& chans, const ProcessTab* pt, int dims, int nb, int n_slots, int n_inv, int kinds,
+                      int mixed, double s_lab, int np, int64_t n, const double* y, double* p, double* x1x2, double* jac,
+                      double* w, int cu_count, hipStream_t s);
 
-hipError_t launch_inverse(const ChannelTab* ct, const double* grid, int nb, int dims, int n_slots, int n_inv, int kinds,
+// The inverse maps of n_chans channels of one register and kind class (dims,
+// nb: the largest dimension and bin count, n_slots, n_inv and kinds of any) for
+// the same events; jac: also their forward Jacobians [n_chans][n].
+bool same_chain_class(int n_slots_a, int n_inv_a, int kinds_a, int n_slots_b, int n_inv_b, int kinds_b);
+hipError_t launch_inverse(const LaunchChans& chans, int n_chans, int dims, int nb, int n_slots, int n_inv, int kinds,
                           double s_lab, int np, int64_t n, const double* p, const double* x1x2, double* y, double* jac,
                           int cu_count, hipStream_t s);
 
@@ -83,7 +89,13 @@ hipError_t launch_unweight(const double* w, int64_t n, double w_max, uint64_t se
                            int64_t* blk, int64_t* keep, double* uw, int64_t* count, hipStream_t s);
 
 // g = alpha / jac (first) or g += alpha / jac; jac = 0 adds nothing.
-hipError_t launch_density_add(double* g, const double* jac, double alpha, int64_t n, bool first, hipStream_t s);
+// g = (first ? 0 : g) + sum of alpha[i] / jac[i][e] over n_chans channels, in
+// order (jac <= 0: no term).
+struct DensityAlpha {
+    double a[kMaxLaunchChans];
+};
+hipError_t launch_density_add(double* g, const double* jac, const DensityAlpha& alpha, int n_chans, int64_t n, bool first,
+                              hipStream_t s);
 
 hipError_t launch_weight(const ChannelTab* ct, const ProcessTab* pt, int mixed, int np, int64_t n, const double* p,
                          const double* x1x2, const double* jac, double* w, double* alpha, hipStream_t s);
@@ -108,7 +120,7 @@ struct JitSampleSet {
 };
 
 // Fused multichannel sample.  `call` is the device copy of the call table;
-// `max_tiles` bounds its n_tiles (for the per-channel statistics pass);
+// `max_tiles` bounds the tiles of a channel (for the statistics pass);
 // `ld` is the row stride of the outputs (>= the events of the call).
 // With vpart != NULL the kernel also accumulates every channel's VEGAS
 // histogram (sum w^2 per bin of every dimension) into per-tile partials

@@ -181,4 +181,17 @@ struct SampleCall {
     int64_t ev_start[kMaxChannels + 1];    // first output position
 };
 
+// The channels of one map or inverse launch, blockIdx.y of them: channel
+// c[blockIdx.y] of the context's tables and VEGAS grids, its arrays y and jac
+// at blockIdx.y y_step and blockIdx.y n.
+constexpr int kMaxLaunchChans = 16;
+struct LaunchChans {
+    const ChannelTab* cts;
+    const double* grids;
+    const int64_t* grid_off;
+    const int32_t* nb;
+    int64_t y_step;
+    int32_t c[kMaxLaunchChans];
+};
+
 }  // namespace msx
