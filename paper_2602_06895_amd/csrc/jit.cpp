@@ -128,11 +128,9 @@ bool compile_load(const std::string& body, const std::string& arch, JitSample& j
     const std::string src = "#define MSX_JIT_NAME " + name + "\n" + body;
     // the library's own flags for the FP64 path (no contraction, no packed
     // FP32); no machine-level loop-invariant hoisting, which in this kernel
-    // only lengthens the live ranges of constants and table values, and
-    // instructions sunk to their uses
+    // only lengthens the live ranges of constants and table values
     const char* opts[] = {arch.c_str(), "-O3", "-std=c++17", "-ffp-contract=off", "-Xclang", "-target-feature",
-                          "-Xclang", "-packed-fp32-ops", "-mllvm", "-disable-machine-licm", "-mllvm",
-                          "-sink-insts-to-avoid-spills"};
+                          "-Xclang", "-packed-fp32-ops", "-mllvm", "-disable-machine-licm"};
     hiprtcProgram prog;
     hiprtcResult r = hiprtcCreateProgram(&prog, src.c_str(), "msx_jit_sample.hip", jit_src::kHeaderCount,
                                          jit_src::kHeaderTexts, jit_src::kHeaderNames);
@@ -179,16 +177,16 @@ bool compile_load(const std::string& body, const std::string& arch, JitSample& j
 }
 
 // One kernel for channels [c0, c1): first at three waves per SIMD (168
-// registers), which is faster than two waves where it needs little or no
-// scratch (t tbar: none, 5% faster; the eight pp -> 4 jets channels: 68 B/lane,
-// 130 instead of 148 us per million events); a three-wave build with more
-// scratch than kMaxScratch is dropped for the compiler's default occupancy
-// (120 B/lane in an earlier build of those channels cost 100 B/event of HBM
-// traffic and the gain).  Returns 0 with the kernel in j, 1 when the kernel
-// spills even at the default occupancy (not kept), -1 on error.
+// registers), which is faster than two waves with little scratch (t tbar: 12
+// B/lane, 5% faster) and still with some (the eight pp -> 4 jets channels: 148
+// B/lane, mostly of the three t-channel chains, 132 instead of 142 us per
+// million events); a three-wave build with more scratch than kMaxScratch is
+// dropped for the compiler's default occupancy.  Returns 0 with the kernel in
+// j, 1 when the kernel spills even at the default occupancy (not kept), -1 on
+// error.
 int build_group(const Compiled& comp, int mixed, const std::string& arch, int c0, int c1, JitSample& j,
                 int* scratch_out, std::string& err) {
-    constexpr int kMaxScratch = 80;
+    constexpr int kMaxScratch = 160;
     for (int waves : {3, 0}) {
         int rows = 0;
         const std::string src = sample_source(comp, mixed, waves, c0, c1, rows);
