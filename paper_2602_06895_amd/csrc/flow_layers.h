@@ -118,6 +118,14 @@ __device__ __forceinline__ Vec8<T> zero8() {
     return r;
 }
 
+// 16 bytes per lane from memory to consecutive words of LDS from dst (the same
+// for all lanes), without registers; there after landed().
+__device__ __forceinline__ void copy16_to_lds(const __bf16* src, __bf16* dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // An offset of zero that the compiler takes for a new value wherever it is
 // asked for: loads behind it stay where they are written.
 __device__ __forceinline__ int here() {
@@ -191,6 +199,33 @@ __device__ __forceinline__ void load_out(const FlowNet& fn, int layer, __bf16* _
         *(Vec8<__bf16>*)&w4[j * kOutElems + 8 * c] = load8(&W[(j * P + row) * kHid + k]);
     }
 }
+// The same copied straight to LDS, without registers and all words in flight at
+// once; this wave's are there after landed(), the workgroup's after a barrier.
+// The places that a lane copies from are the same in every layer.
+constexpr int kOutRounds = (kWaves * kOutElems / 8 + kThreads - 1) / kThreads;
+constexpr int kOutKept = kOutRounds * kThreads * 8;  // elements: up to eight coordinates, in whole rounds
+struct OutCopy {
+    int from[kOutRounds];
+    __device__ __forceinline__ OutCopy(const FlowNet& fn, int wave, int lane) {
+        const int words = fn.nh * (kOutElems / 8);
+#pragma unroll
+        for (int it = 0; it < kOutRounds; ++it) {
+            const int i = min((it * kWaves + wave) * 64 + lane, words - 1);
+            const int j = i / (kOutElems / 8), c = i - j * (kOutElems / 8);  // 16-byte word c of coordinate j
+            const int m = c >> 8, s = (c >> 6) & 3, r = c & 15, q = (c >> 4) & 3;
+            const int row = m < 3 ? param_row(m, r, fn.K) : param_row(3, 0, fn.K), k = m < 3 ? 32 * s + 8 * q : 8 * r;
+            from[it] = (j * (3 * fn.K + 1) + row) * kHid + k;
+        }
+    }
+    __device__ __forceinline__ void operator()(const FlowNet& fn, int layer, __bf16* w4, int wave) const {
+        const __bf16* W = (const __bf16*)fn.wt + layer * fn.per_t + fn.off[6];
+#pragma unroll
+        for (int it = 0; it < kOutRounds; ++it) {
+            const int base = (it * kWaves + wave) * 64;
+            if (base < fn.nh * (kOutElems / 8)) copy16_to_lds(W + from[it], &w4[base * 8]);
+        }
+    }
+};
 __device__ __forceinline__ Vec8<__bf16> out_fragment(const __bf16* w4, int j, int m, int s, int lane) {
     const __bf16* c = w4 + j * kOutElems;
     return load8(m < 3 ? c + ((m * 4 + s) * 64 + lane) * 8 : c + 48 * kHid + 32 * s + 8 * (lane >> 4));

@@ -38,7 +38,7 @@ constexpr size_t layers_lds(int d, int kept) {
 // the latency of the three barriers and the LDS reads behind them.  Before, a
 // wave read every weight of a layer from L2 for its own 64 events and walked
 // each spline through LDS: 4583 us for eight layers of 2^20 events of 16
-// dimensions, now 2580 us; 1000 events of 10 dimensions 299 -> 68 us.  (Tried
+// dimensions, now 2580 us.  (Tried
 // and slower: the output weights in registers, 2850 us; two workgroups of
 // four waves per compute unit, 4240 us, and the splines of a tile interleaved
 // with the next tile's hidden layers, 2840 us, which both spill.)
@@ -172,9 +172,92 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
+// A pass over 16 events per workgroup (BF16, at most eight transformed
+// coordinates): the coordinates stay in LDS over all layers, and a layer's
+// weights are on their way while the layer before evaluates its splines, the
+// hidden layers' to registers and the output layer's to LDS.
+//
+// What bounds it: a layer's 166 KB of weights come to the one compute unit at 28
+// B/ns, 6 of the 7.4 us per layer (without them it takes 3); fewer events per
+// tile would not change that, more take their splines' time.  1,000 events of 16
+// dimensions, 8 layers: 60 us; with the weights loaded when a layer begins and
+// the coordinates through memory (k_flow_layers with tiles of 16) 68.
+template <bool INV, bool K16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_flow_tile(FlowNet fn,
+                                                                                               FlowRun run) {
+    typedef __bf16 T;
+    constexpr int EV = 16;
+    __shared__ __attribute__((aligned(16))) T w4[kOutKept];  // [nh][kOutElems]
+    __shared__ __attribute__((aligned(16))) T act[2][EV * kHid];
+    __shared__ __attribute__((aligned(16))) T cond[EV * kCond];
+    __shared__ float zs[2 * kWaves][EV];
+    __shared__ float lds_ld[kWaves][EV];
+    if (K16) fn.K = 16;
+    const int nh = fn.nh, d = 2 * nh, K = fn.K;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ev = lane & 15, q = lane >> 4;
+    const int64_t n = run.n, e0 = (int64_t)blockIdx.x * EV;
+    const bool mine = tid < d * EV;  // thread tid moves coordinate tid / 16 of event tid % 16
+    const int64_t em = e0 + (tid & 15);
+    const float z0 = mine ? run.zin[(int64_t)(tid >> 4) * n + min(em, n - 1)] : 0.0f;
+    HidW<T> hw = load_hidden<T>(fn, run.first, wave, lane);
+    RegisterBias<true> bias(fn, run.first, wave, lane);
+    const OutCopy copy_out(fn, wave, lane);
+    copy_out(fn, run.first, w4, wave);
+    for (int i = tid; i < EV * kCond; i += kThreads) cond[i] = (T)0.0f;
+    if (mine) zs[tid >> 4][tid & 15] = z0;
+    __syncthreads();
+    float ld = 0.0f;
+    for (int li = 0; li < run.count; ++li) {
+        const int layer = run.first + li * run.dir, next = li + 1 < run.count ? layer + run.dir : layer;
+        const Mask mk = mask_of(layer, nh);
+        if (tid < nh * EV) {
+            const int k = tid >> 4;
+            cond[cond_at<T>(tid & 15, k)] = (T)zs[mk.c0 + mk.cs * k][tid & 15];
+        }
+        __syncthreads();
+        store_act(mfma(hw.w1, cond8(cond, ev, 8 * q), zero4()), bias.hidden(0), act[0], 0, wave, lane);
+        __syncthreads();
+        hidden_layer<1>(hw.w2, bias.hidden(1), act[0], act[1], wave, lane);
+        __syncthreads();
+        hidden_layer<1>(hw.w3, bias.hidden(2), act[1], act[0], wave, lane);
+        landed();  // this layer's w4
+        __syncthreads();
+        // the next layer's weights
+        hw = load_hidden<T>(fn, next, wave, lane);
+        Theta th;
+        if (wave < nh) th = output_layer<1, true>(fn, layer, act[0], w4, bias, wave, K, lane);
+        bias = RegisterBias<true>(fn, next, wave, lane);
+        __syncthreads();  // w4 is read
+        if (li + 1 < run.count) copy_out(fn, next, w4, wave);
+        if (wave < nh) {
+            const int tj = mk.t0 + mk.ts * wave;
+            const float vin = zs[tj][ev];
+            float sw, sh, l;
+            spline_exp<K16>(th, K, sw, sh);
+            Bin b = spline_find<INV, K16>(th, K, vin, sw, sh);
+            spline_slopes(b);
+            const float v = spline_value<INV>(b, vin, l);
+            if (lane < EV) {
+                zs[tj][ev] = v;
+                lds_ld[wave][ev] = 0.0f + l;
+            }
+        }
+        __syncthreads();
+        if (tid < EV) {
+            float s = 0.0f;
+            for (int w = 0; w < nh; ++w) s += lds_ld[w][tid];
+            ld = li > 0 ? ld + s : 0.0f + s;
+        }
+        if (mine && em < n && (run.zstep != 0 || li + 1 == run.count))
+            run.zout[li * run.zstep + (int64_t)(tid >> 4) * n + em] = zs[tid >> 4][tid & 15];
+    }
+    if (tid < EV && e0 + tid < n) run.logdet[e0 + tid] = ld;
+}
+
 template <bool INV, int NT, class T>
 hipError_t launch_layers(const FlowNet& fn, const FlowRun& run, int64_t grid, hipStream_t s) {
-    constexpr bool can_keep = sizeof(T) == 2;
+    constexpr bool can_keep = sizeof(T) == 2 && NT == 4;
     const bool keep = can_keep && fn.nh <= kWaves;  // then W4 fits in LDS: at most 98 KiB
     const size_t lds = layers_lds<NT, T>(2 * fn.nh, keep ? fn.nh : 0);
     const dim3 g((unsigned)grid), t(kThreads);
@@ -205,8 +288,17 @@ hipError_t launch_pass(const FlowNet& fn, const FlowRun& run, int cu_count, hipS
         return launch_layers<INV, 4, float>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
     }
     // up to one tile of 16 events for every compute unit the time is the
-    // latency of a tile through the layers, which grows with the tile
-    if (t16 <= cu_count) return launch_layers<INV, 1, __bf16>(fn, run, t16, s);
+    // latency of a tile through the layers, which grows with the tile (8 layers
+    // of 16 dimensions, 4,096 events: 60 us, one more 107; a second round of
+    // tiles of 16 would take 118)
+    if (t16 <= cu_count) {
+        if (fn.nh > kWaves) return launch_layers<INV, 1, __bf16>(fn, run, t16, s);
+        if (fn.K == 16)
+            k_flow_tile<INV, true><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
+        else
+            k_flow_tile<INV, false><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
+        return hipGetLastError();
+    }
     return launch_layers<INV, 4, __bf16>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
 }
 

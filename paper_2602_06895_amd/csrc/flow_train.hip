@@ -384,8 +384,7 @@ constexpr int kBlockElems = 2 * kBlockH + kBlockD + kBlockX;
 __device__ __forceinline__ void copy_to_lds(const __bf16* __restrict__ src, __bf16* __restrict__ dst, int chunks, int wave,
                                             int lane) {
     for (int c = wave; c < chunks; c += kWaves)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + c * 512 + lane * 8),
-                                         (__attribute__((address_space(3))) void*)(dst + c * 512), 16, 0, 0);
+        copy16_to_lds(src + c * 512 + lane * 8, dst + c * 512);
 }
 
 template <bool HIDDEN>
@@ -457,12 +456,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int64_t k0 = blockIdx.x * chunk, k1 = min(blocks, k0 + chunk);
     if (k0 < k1) stage(k0, smem);
     for (int64_t k = k0; k < k1; ++k) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        landed();
         __syncthreads();  // block k is in LDS, the other buffer's readers are done
         const int cur = (int)(k - k0) & 1;
         step(smem + cur * kBlockElems, smem + (cur ^ 1) * kBlockElems, min(k + 1, k1 - 1));
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    landed();
     auto over_q = [](float v) {
         v += __shfl_xor(v, 16, 64);
         return v + __shfl_xor(v, 32, 64);
