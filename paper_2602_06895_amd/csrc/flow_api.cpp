@@ -322,7 +322,7 @@ msx_status gradient_fused(msx_flow* f, int64_t n, const float* y, const double* 
         r.first = l == 0;
         FHIP(f, launch_flow_spline_reverse(fn, r, f->cu_count, s), "flow spline reverse");
         FHIP(f, launch_flow_mlp_reverse(fn, r, f->wt_t, f->cu_count, s), "flow conditioner reverse");
-        FHIP(f, launch_flow_wgrad(fn, r, splits, f->part, s), "flow weight gradients");
+        FHIP(f, launch_flow_wgrad(fn, r, splits, f->part, f->cu_count, s), "flow weight gradients");
         FHIP(f, launch_reduce_partials(f->part, splits, 1, (int)f->per_layer, grad + l * f->per_layer, f->per_layer, s),
              "flow reduce");
     }

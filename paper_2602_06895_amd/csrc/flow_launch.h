@@ -103,7 +103,8 @@ hipError_t launch_flow_mlp_reverse(const FlowNet& fn, const FlowRev& r, const vo
 // Weight and bias gradients of the layer from d, dh, h, x0: partial sums over
 // `splits` runs of events, part [splits][per], laid out as the parameters.
 int flow_wgrad_splits(const FlowNet& fn, int64_t n);
-hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, hipStream_t s);
+hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, int cu_count,
+                             hipStream_t s);
 
 // out[m][n] = sum_z part[z][m][n] in z order (out has leading dimension ldo).
 hipError_t launch_reduce_partials(const float* part, int splits, int M, int N, float* out, int64_t ldo,

@@ -583,17 +583,20 @@ hipError_t launch_mlp_reverse(const FlowNet& fn, const FlowRev& r, const void* w
     return hipGetLastError();
 }
 
-// 16-event tiles per workgroup of the reverse kernels.  FP32: 32 events, whose
-// 172 KiB of tiles LDS would not hold with 64.
-int reverse_tiles(const FlowNet& fn) { return fn.f32 ? 2 : 4; }
+// 16-event tiles per workgroup of the reverse kernels: 32 events in FP32 (of 64
+// the 172 KiB would not fit in LDS), and while every compute unit gets at most
+// one such tile (4,096 events of 16 dimensions: 569 us a gradient with tiles of
+// 64, 512 with 32).
+int reverse_tiles(const FlowNet& fn, int64_t n, int cu_count) { return fn.f32 || n <= 32 * (int64_t)cu_count ? 2 : 4; }
 
 }  // namespace
 
 int flow_grad_rows(int nh, int K) { return grad_rows(nh, K); }
 
 hipError_t launch_flow_spline_reverse(const FlowNet& fn, const FlowRev& r, int cu_count, hipStream_t s) {
-    return fn.f32 ? launch_spline_reverse<2, float>(fn, r, cu_count, s)
-                  : launch_spline_reverse<4, __bf16>(fn, r, cu_count, s);
+    if (fn.f32) return launch_spline_reverse<2, float>(fn, r, cu_count, s);
+    return reverse_tiles(fn, r.n, cu_count) == 2 ? launch_spline_reverse<2, __bf16>(fn, r, cu_count, s)
+                                                 : launch_spline_reverse<4, __bf16>(fn, r, cu_count, s);
 }
 
 int64_t flow_transposed_elems(int nh) { return transposed_elems(nh); }
@@ -609,19 +612,24 @@ hipError_t launch_flow_transpose(const FlowNet& fn, int layers, void* wt_t, hipS
 
 hipError_t launch_flow_mlp_reverse(const FlowNet& fn, const FlowRev& r, const void* wt_t, int cu_count,
                                    hipStream_t s) {
-    return fn.f32 ? launch_mlp_reverse<2, float>(fn, r, wt_t, cu_count, s)
-                  : launch_mlp_reverse<4, __bf16>(fn, r, wt_t, cu_count, s);
+    if (fn.f32) return launch_mlp_reverse<2, float>(fn, r, wt_t, cu_count, s);
+    return reverse_tiles(fn, r.n, cu_count) == 2 ? launch_mlp_reverse<2, __bf16>(fn, r, wt_t, cu_count, s)
+                                                 : launch_mlp_reverse<4, __bf16>(fn, r, wt_t, cu_count, s);
 }
 
-// BF16: up to 128 workgroups of at least 256 events.  FP32: blockIdx.y gives
-// seven workgroups per run of 16 coordinates' layers already, so up to 32 runs
-// of at least 64 events.
+// Runs of events of the weight gradients.  More of them fill more compute units,
+// but each writes, and the reduction reads, all partial sums (336 KB): runs of 64
+// events up to 64, from 8,192 events of 128, from 16,384 on 128 runs (1,000
+// events: 515 us a gradient with runs of 256, 429 with 64; 8,192: 600, 580 with
+// 64, 557 with 128).  FP32: blockIdx.y gives seven workgroups per run of eight
+// coordinates already, so up to 32 runs of at least 64.
 int flow_wgrad_splits(const FlowNet& fn, int64_t n) {
-    return (int)std::max<int64_t>(1, fn.f32 ? std::min<int64_t>(32, n / 64) : std::min<int64_t>(128, n / 256));
+    const int64_t runs = std::min<int64_t>(n / 64, fn.f32 ? 32 : 64);
+    return (int)std::max<int64_t>(1, fn.f32 ? runs : std::max(runs, std::min<int64_t>(128, n / 128)));
 }
 
-hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, hipStream_t s) {
-    const int64_t ev = 16 * reverse_tiles(fn), blocks = (r.n + ev - 1) / ev * ev / 32, chunk = (blocks + splits - 1) / splits;
+hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, int cu_count, hipStream_t s) {
+    const int64_t ev = 16 * reverse_tiles(fn, r.n, cu_count), blocks = (r.n + ev - 1) / ev * ev / 32, chunk = (blocks + splits - 1) / splits;
     if (fn.f32) {
         const int groups = (fn.nh * (3 * fn.K + 1) + kHid - 1) / kHid + 3;
         k_flow_wgrad_f32<<<dim3((unsigned)splits, (unsigned)groups), kThreads, 0, s>>>(fn, r, blocks, chunk, part);

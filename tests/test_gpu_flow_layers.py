@@ -81,8 +81,9 @@ def _batch(torch, d, n, seed):
     return y, wfj, lqo, [torch.from_numpy(a).cuda() for a in (y, wfj, lqo)]
 
 
-# one event, around one tile of 64, an odd number of 32-event blocks per run
-# of the weight gradients, a run per 256 events and beyond its largest number
+# one event, around a tile, an odd number of 32-event blocks per run of the
+# weight gradients, up to and beyond one tile of 32 per compute unit and the
+# largest number of runs
 GRAD_SHAPES = [(16, 4, 16, 1), (16, 4, 16, 63), (16, 3, 16, 65), (10, 4, 16, 513), (2, 3, 16, 200), (16, 2, 16, 2100),
                (18, 2, 16, 130), (64, 2, 16, 70), (64, 2, 12, 300), (16, 4, 1, 90), (14, 2, 7, 33000), (24, 2, 5, 700)]
 
