@@ -602,7 +602,7 @@ def summarize(d: str, events: int, steps: int = 10, kernel: str = "k_sample", by
 
 def summarize_flow(d: str):
     """Per-kernel summary of a rocprofv3 kernel trace of `bench.py --flow-only`
-    under d/flow (the coupling-flow kernels; GEMMs split by launch grid)."""
+    under d/flow (the coupling-flow kernels)."""
     import glob
     import sqlite3
 
@@ -613,11 +613,6 @@ def summarize_flow(d: str):
                                          "group by name order by sum(duration) desc"):
         short = name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
         out.append(f"  {short[:60]}: {cnt}, {avg / 1e3:.1f}, {tot / 1e6:.2f}")
-    out.append("k_gemm by grid (x work-items, y, z: dispatches, avg us, vgpr, agpr)")
-    for gx, gy, gz, cnt, avg, vg, ag in c.execute(
-            "select grid_x, grid_y, grid_z, count(*), avg(duration), max(vgpr_count), max(accum_vgpr_count) "
-            "from kernels where name like '%k_gemm%' group by grid_x, grid_y, grid_z order by sum(duration) desc"):
-        out.append(f"  {gx} x {gy} x {gz}: {cnt}, {avg / 1e3:.1f}, {vg}, {ag}")
     print("\n".join(out))
 
 
