@@ -217,9 +217,9 @@ msx_status sample_device(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uin
             launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, d_call, C,
                           ctx->all_slots, ctx->all_inv, ctx->all_kinds, ctx->mixed, ctx->lds_max, seed, stream_id,
                           counter_offset, 0, ctx->max_np, capacity, p, x1x2, w, chan, d_tile, max_tiles, ctx->d_stats,
-                          grid, s, d_vtiles, ctx->vstride, ctx->d_hist_off, ctx->hist_total, ctx->d_hist, jit_of(ctx)),
+                          grid, s, d_vtiles, ctx->vstride, ctx->d_hist_off, ctx->hist_total, ctx->d_hist, jit_of(ctx),
+                          advance ? const_cast<uint64_t*>(counter_offset) : nullptr),
             "sample launch");
-    if (advance) MSX_HIP(ctx, launch_advance_counter(d_call, const_cast<uint64_t*>(counter_offset), s), "counter");
     return MSX_OK;
 }
 
@@ -546,10 +546,11 @@ msx_status msx_weight(msx_ctx* ctx, int32_t channel, int64_t n, const double* p,
 namespace {
 
 // msx_sample and msx_sample_noalloc: with noalloc, the tile statistics go to
-// the library's fixed device scratch (no allocation; flags must be 0).
+// the library's fixed device scratch (no allocation; flags must be 0).  With
+// reset, the context's statistics start from zero with this call.
 msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint64_t stream_id,
                        uint64_t counter_offset, int32_t flags, double* p, double* x1x2, double* w, int32_t* chan,
-                       void* stream, bool noalloc) {
+                       void* stream, bool noalloc, bool reset = false) {
     if (bad_ctx(ctx)) return fail(nullptr, MSX_ERR_ARG, "ctx is NULL");
     if (!counts) return fail(ctx, MSX_ERR_ARG, "counts is NULL");
     if (noalloc && flags != 0) return fail(ctx, MSX_ERR_UNSUPPORTED, "msx_sample_noalloc takes no flags");
@@ -567,7 +568,8 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
         const uint64_t start = ctx->next_counter;
         if (start == MSX_COUNTER_AUTO || start > MSX_COUNTER_AUTO - 1 - (uint64_t)total)
             return fail(ctx, MSX_ERR_ARG, "the context's event counter is exhausted");
-        msx_status st = sample_host(ctx, counts, seed, stream_id, start, flags, p, x1x2, w, chan, stream, noalloc);
+        msx_status st =
+            sample_host(ctx, counts, seed, stream_id, start, flags, p, x1x2, w, chan, stream, noalloc, reset);
         if (st == MSX_OK) ctx->next_counter = start + (uint64_t)total;
         return st;
     }
@@ -616,7 +618,7 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
     if (acc)
         if (msx_status st = ensure_vtiles(ctx, tiles)) return st;
     hipStream_t s = (hipStream_t)stream;
-    MSX_HIP(ctx, launch_set_call(call, ctx->d_call, s), "sample call table");
+    MSX_HIP(ctx, launch_set_call(call, ctx->d_call, reset ? ctx->d_stats : nullptr, 5 * C, s), "sample call table");
     const int grid = (int)std::min<int64_t>(tiles, sample_grid(ctx));
     MSX_HIP(ctx,
             launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, ctx->d_call, C,
@@ -842,7 +844,7 @@ msx_status msx_reset_stats(msx_ctx* ctx, void* stream) {
     if (bad_ctx(ctx)) return fail(nullptr, MSX_ERR_ARG, "ctx is NULL");
     if (msx_status st = set_device(ctx)) return st;
     const int C = (int)ctx->comp.chans.size();
-    MSX_HIP(ctx, hipMemsetAsync(ctx->d_stats, 0, sizeof(double) * 5 * C, (hipStream_t)stream), "stats reset");
+    MSX_HIP(ctx, launch_clear(ctx->d_stats, 5 * C, (hipStream_t)stream), "stats reset");
     return MSX_OK;
 }
 
@@ -912,10 +914,10 @@ msx_status msx_vegas_adapt(msx_ctx* ctx, int64_t n_per_channel, int32_t iteratio
     std::vector<int64_t> counts(C, n_per_channel);
     msx_status st = MSX_OK;
     for (int it = 0; it < iterations && st == MSX_OK; ++it) {
-        st = msx_reset_stats(ctx, stream);
-        if (st == MSX_OK)
-            st = msx_sample(ctx, counts.data(), seed, stream_id, counter_offset + (uint64_t)it * (uint64_t)N,
-                            MSX_SAMPLE_ACCUMULATE_VEGAS, p, x1x2, w, nullptr, stream);
+        st = sample_host(ctx, counts.data(), seed, stream_id, counter_offset + (uint64_t)it * (uint64_t)N,
+                         MSX_SAMPLE_ACCUMULATE_VEGAS, p, x1x2, w, nullptr, stream, false, true);
+        // a call that is refused leaves the statistics empty as well
+        if (st != MSX_OK) (void)msx_reset_stats(ctx, stream);
         if (st == MSX_OK && stats_out && it == iterations - 1) st = msx_stats(ctx, stats_out, stream);
         if (st == MSX_OK) st = msx_vegas_update(ctx, alpha, stream);
     }
@@ -1198,7 +1200,7 @@ msx_status sample_with_flows(msx_ctx* ctx, const int64_t* counts, uint64_t seed,
         if (msx_status st = ensure_tiles(ctx, tiles)) return st;
         if (acc)
             if (msx_status st = ensure_vtiles(ctx, tiles)) return st;
-        MSX_HIP(ctx, launch_set_call(call, ctx->d_call, s), "sample call table");
+        MSX_HIP(ctx, launch_set_call(call, ctx->d_call, nullptr, 0, s), "sample call table");
         const int grid = (int)std::min<int64_t>(tiles, sample_grid(ctx));
         MSX_HIP(ctx,
                 launch_sample(ctx->d_chans, ctx->d_procs, ctx->d_grids, ctx->d_grid_off, ctx->d_chan_nb, ctx->d_call,

@@ -61,15 +61,16 @@ __global__ __launch_bounds__(kBlock) void k_weight(const ChannelTab* __restrict_
     if (alpha) alpha[e] = av;
 }
 
-// Sum of the statistics of tiles [t0, t1) over a workgroup, in a fixed order;
-// the result is valid in thread 0.
+// Sum of the statistics of tiles [t0, t1) over the first kBlock threads of a
+// workgroup, in a fixed order; the result is valid in thread 0.  Every thread
+// of the workgroup calls it.
 struct TileSum {
     double s1, s2, zeros, wmax;
 };
 __device__ __forceinline__ TileSum sum_tiles(const double* tile_stats, int64_t t0, int64_t t1,
                                              double (&red)[4][kWaves]) {
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x) {
+    for (int64_t t = threadIdx.x < kBlock ? t0 + threadIdx.x : t1; t < t1; t += kBlock) {
         a[0] += tile_stats[t * 4 + 0];
         a[1] += tile_stats[t * 4 + 1];
         a[2] += tile_stats[t * 4 + 2];
@@ -77,7 +78,7 @@ __device__ __forceinline__ TileSum sum_tiles(const double* tile_stats, int64_t t
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double r0 = wave_sum(a[0]), r1 = wave_sum(a[1]), r2 = wave_sum(a[2]), r3 = wave_max(a[3]);
-    if (lane == 0) {
+    if (lane == 0 && wave < kWaves) {
         red[0][wave] = r0;
         red[1][wave] = r1;
         red[2][wave] = r2;
@@ -121,13 +122,12 @@ __global__ __launch_bounds__(kBlock) void k_stats_slices(const SampleCall* __res
     }
 }
 
-// Reduce the tiles of each channel and add to the accumulators
-// stats[c] = (sum w, sum w^2, n, n(w == 0), max w).
-__global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __restrict__ call,
-                                                        const double* __restrict__ tile_stats,
-                                                        double* __restrict__ stats) {
-    const int c = blockIdx.x;
-    __shared__ double red[4][kWaves];
+// Reduce the tiles of channel c and add to its accumulators
+// stats[c] = (sum w, sum w^2, n, n(w == 0), max w); every thread of a workgroup
+// of at least kBlock calls it.
+__device__ __forceinline__ void channel_stats(int c, const SampleCall* __restrict__ call,
+                                              const double* __restrict__ tile_stats, double* __restrict__ stats,
+                                              double (&red)[4][kWaves]) {
     if (c >= call->n_chan || ((call->skip_mask >> c) & 1)) return;
     const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
     TileSum r;
@@ -154,6 +154,16 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __rest
         st[3] += r.zeros;
         st[4] = fmax(st[4], r.wmax);
     }
+}
+
+// The statistics of a call, a workgroup per channel.  After the sample has
+// read it the caller's event counter may move on (null: it stays).
+__global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __restrict__ call,
+                                                        const double* __restrict__ tile_stats,
+                                                        double* __restrict__ stats, uint64_t* __restrict__ advance) {
+    __shared__ double red[4][kWaves];
+    if (advance && threadIdx.x == 0 && blockIdx.x == 0) *advance += (uint64_t)call->ev_start[call->n_chan];
+    channel_stats(blockIdx.x, call, tile_stats, stats, red);
 }
 
 // Hit-or-miss unweighting (the paper's channel-wise unweighting against an
@@ -494,8 +504,23 @@ __global__ __launch_bounds__(kBlock) void k_density_add(double* __restrict__ g, 
     g[i] = sum;
 }
 
-__global__ void k_set_call(SampleCall call, SampleCall* __restrict__ dev) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dev = call;
+//
+// One workgroup, a word per thread; it also clears n_clear accumulators for a
+// caller whose statistics start with the call.  A launch of this size costs 4
+// us whatever it does; written by one thread the table took 5, and clearing
+// the accumulators by a memset 4 to 8 more (one fill kernel or two).
+constexpr int kSetThreads = 256;
+__global__ __launch_bounds__(kSetThreads) void k_set_call(SampleCall call, SampleCall* __restrict__ dev,
+                                                          double* __restrict__ clear, int n_clear) {
+    static_assert(sizeof(SampleCall) % 8 == 0 && sizeof(SampleCall) / 8 <= kSetThreads, "a word per thread");
+    const int i = threadIdx.x;
+    if (i < (int)(sizeof(SampleCall) / 8))
+        reinterpret_cast<uint64_t*>(dev)[i] = reinterpret_cast<const uint64_t*>(&call)[i];
+    for (int k = i; k < n_clear; k += kSetThreads) clear[k] = 0.0;
+}
+
+__global__ __launch_bounds__(kSetThreads) void k_clear(double* __restrict__ x, int n) {
+    for (int k = threadIdx.x; k < n; k += kSetThreads) x[k] = 0.0;
 }
 
 // VEGAS histograms of a fused sample: entry i of the context's histogram
@@ -505,12 +530,24 @@ __global__ void k_set_call(SampleCall call, SampleCall* __restrict__ dev) {
 // four loads in flight each, and the 64 sums of an entry are added in a fixed
 // order.  The kernel is bound by the latency of its loads: with one thread
 // per entry walking all 391 tiles of 1e5 events it took 93 us, this way 5.
+// The workgroups after those of the histograms do the call's statistics, which
+// saves their launch (4.6 us).
 constexpr int kVegasWaves = 16;
 __global__ __launch_bounds__(64 * kVegasWaves) void k_vegas_tiles(const SampleCall* __restrict__ call,
                                                                   const int64_t* __restrict__ hist_off,
                                                                   int64_t hist_total, int vstride,
                                                                   const double* __restrict__ vpart,
-                                                                  double* __restrict__ hist) {
+                                                                  double* __restrict__ hist, int hist_blocks,
+                                                                  const double* __restrict__ tile_stats,
+                                                                  double* __restrict__ stats,
+                                                                  uint64_t* __restrict__ advance) {
+    if ((int)blockIdx.x >= hist_blocks) {
+        __shared__ double stat_red[4][kWaves];
+        const int c = (int)blockIdx.x - hist_blocks;
+        if (advance && threadIdx.x == 0 && c == 0) *advance += (uint64_t)call->ev_start[call->n_chan];
+        channel_stats(c, call, tile_stats, stats, stat_red);
+        return;
+    }
     __shared__ double red[kVegasWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + lane;
@@ -540,38 +577,45 @@ __global__ __launch_bounds__(64 * kVegasWaves) void k_vegas_tiles(const SampleCa
     }
 }
 
-// Call table from device-resident counts (one thread: at most kMaxChannels).
-__global__ void k_plan(const int64_t* __restrict__ counts, int n_chan, int64_t capacity, int ept,
-                       SampleCall* __restrict__ dev, int32_t* __restrict__ status) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Call table from device-resident counts: lane c of one wave has channel c, the
+// starts are prefix sums over the lanes (one thread walking 24 channels took
+// 5.4 us, mostly its divisions).  A negative count or more events than the
+// buffers hold make an empty call.
+__global__ __launch_bounds__(64) void k_plan(const int64_t* __restrict__ counts, int n_chan, int64_t capacity, int ept,
+                                             SampleCall* __restrict__ dev, int32_t* __restrict__ status) {
+    static_assert(kMaxChannels <= 64, "one lane per channel");
+    const int c = threadIdx.x;
     const int64_t T = (int64_t)kBlock * ept;
-    int64_t N = 0, tiles = 0;
-    int bad = 0;
-    dev->n_chan = n_chan;
-    dev->ept = ept;
-    dev->skip_mask = 0;
-    for (int c = 0; c < n_chan; ++c) {
-        const int64_t k = counts[c];
-        dev->ev_start[c] = N;
-        dev->tile_start[c] = tiles;
-        if (k < 0 || k > capacity - N) {
-            bad = 1;
-        } else {
-            N += k;
-            tiles += (k + T - 1) / T;
+    const int64_t own = c < n_chan ? counts[c] : 0;
+    const bool refused = own < 0 || own > capacity;
+    const int64_t k = refused ? 0 : own;
+    // sums that stop at the largest count, which no capacity exceeds
+    constexpr uint64_t kMost = (uint64_t)INT64_MAX;
+    uint64_t ev = (uint64_t)k;
+    const int64_t mine = k / T + (k % T != 0);
+    int64_t tiles = mine;
+    for (int step = 1; step < 64; step *= 2) {
+        const uint64_t e = __shfl_up((unsigned long long)ev, step);
+        const int64_t t = __shfl_up((long long)tiles, step);
+        if (c >= step) {
+            ev = ev + e < kMost ? ev + e : kMost;
+            tiles += t;
         }
     }
-    dev->ev_start[n_chan] = N;
-    dev->tile_start[n_chan] = tiles;
-    dev->n_tiles = bad ? 0 : tiles;
-    if (bad) {
-        // no events: empty ranges everywhere
-        for (int c = 0; c <= n_chan; ++c) {
-            dev->ev_start[c] = 0;
-            dev->tile_start[c] = 0;
-        }
+    const bool bad = __any(refused || ev > (uint64_t)capacity);
+    if (c < n_chan) {
+        dev->ev_start[c] = bad ? 0 : (int64_t)ev - k;
+        dev->tile_start[c] = bad ? 0 : tiles - mine;
     }
-    if (status) *status = bad;
+    if (c == n_chan - 1) {
+        dev->ev_start[n_chan] = bad ? 0 : (int64_t)ev;
+        dev->tile_start[n_chan] = bad ? 0 : tiles;
+        dev->n_tiles = bad ? 0 : tiles;
+        dev->n_chan = n_chan;
+        dev->ept = ept;
+        dev->skip_mask = 0;
+        if (status) *status = bad;
+    }
 }
 
 // VEGAS histogram, pass 1: block (chunk, k) accumulates sum w^2 per bin of
@@ -943,7 +987,8 @@ hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const dou
                          int kinds, int mixed, size_t lds_bytes, uint64_t seed, uint64_t sid, const uint64_t* ctr_dev,
                          uint64_t ctr_off, int np, int64_t ld, double* p, double* x1x2, double* w, int32_t* chan,
                          double* tile_stats, int64_t max_tiles, double* stats, int grid, hipStream_t s,
-                         double* vpart, int vstride, const int64_t* hist_off, int64_t hist_total, double* hist, const JitSampleSet* jit) {
+                         double* vpart, int vstride, const int64_t* hist_off, int64_t hist_total, double* hist,
+                         const JitSampleSet* jit, uint64_t* advance) {
     if (jit && jit->n > 0) {
         int grid_doubles = (int)(lds_bytes / sizeof(double));
         void* args[] = {&cts, &pts, &grids, &grid_off, &chan_nb, &call, &seed, &sid, &ctr_dev, &ctr_off, &np, &ld,
@@ -985,11 +1030,12 @@ hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const dou
     }
     if (max_tiles > kStatTiles)
         k_stats_slices<<<dim3(kStatSlices, (unsigned)n_chan), kBlock, 0, s>>>(call, tile_stats);
-    k_stats_final<<<n_chan, kBlock, 0, s>>>(call, tile_stats, stats);
     if (vpart && hist_total > 0) {
         const int64_t g = (hist_total + 63) / 64;
-        k_vegas_tiles<<<dim3((unsigned)g), dim3(64 * kVegasWaves), 0, s>>>(call, hist_off, hist_total, vstride, vpart,
-                                                                           hist);
+        k_vegas_tiles<<<dim3((unsigned)(g + n_chan)), dim3(64 * kVegasWaves), 0, s>>>(
+            call, hist_off, hist_total, vstride, vpart, hist, (int)g, tile_stats, stats, advance);
+    } else {
+        k_stats_final<<<n_chan, kBlock, 0, s>>>(call, tile_stats, stats, advance);
     }
     return hipGetLastError();
 }
@@ -1006,8 +1052,14 @@ size_t sample_lds_bytes(int max_slots, int max_inv, size_t lds_bytes, int vstrid
     return lds_bytes + sizeof(double) * (size_t)rows * kBlock + (vstride > 0 ? vegas_acc_lds(vstride) : 0);
 }
 
-hipError_t launch_set_call(const SampleCall& host, SampleCall* dev, hipStream_t s) {
-    k_set_call<<<1, 64, 0, s>>>(host, dev);
+hipError_t launch_set_call(const SampleCall& host, SampleCall* dev, double* clear, int n_clear, hipStream_t s) {
+    k_set_call<<<1, kSetThreads, 0, s>>>(host, dev, clear, clear ? n_clear : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(double* x, int n, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    k_clear<<<1, kSetThreads, 0, s>>>(x, n);
     return hipGetLastError();
 }
 
@@ -1346,10 +1398,6 @@ __global__ void k_moments_final(int nblk, int64_t n, const double* __restrict__ 
     out[4] = fmax(out[4], m);
 }
 
-__global__ void k_advance_counter(const SampleCall* __restrict__ call, uint64_t* __restrict__ ctr) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *ctr += (uint64_t)call->ev_start[call->n_chan];
-}
-
 __global__ void k_fill_i32(int32_t* __restrict__ x, int64_t n, int32_t v) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] = v;
@@ -1366,11 +1414,6 @@ hipError_t launch_moments_add(const double* w, int64_t n, double* part, double* 
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     k_moments_final<<<1, 64, 0, s>>>(g, n, part, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_advance_counter(const SampleCall* call, uint64_t* ctr, hipStream_t s) {
-    k_advance_counter<<<1, 64, 0, s>>>(call, ctr);
     return hipGetLastError();
 }
 

@@ -128,21 +128,25 @@ struct JitSampleSet {
 // second kernel adds them, tiles in order, to hist at hist_off[c] (device
 // array, per channel).  With jit != NULL (and jit->n > 0) the launch runs
 // those kernels instead of the register / kind class kernel of
-// (max_slots, max_inv, kinds).
+// (max_slots, max_inv, kinds).  With advance != NULL, *advance += the events of
+// the call once they are drawn (launches that advance their counter offset).
 hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const double* grids, const int64_t* grid_off,
                          const int32_t* chan_nb, const SampleCall* call, int n_chan, int max_slots, int max_inv,
                          int kinds, int mixed, size_t lds_bytes, uint64_t seed, uint64_t sid, const uint64_t* ctr_dev,
                          uint64_t ctr_off, int np, int64_t ld, double* p, double* x1x2, double* w, int32_t* chan,
                          double* tile_stats, int64_t max_tiles, double* stats, int grid, hipStream_t s,
                          double* vpart = nullptr, int vstride = 0, const int64_t* hist_off = nullptr, int64_t hist_total = 0,
-                         double* hist = nullptr, const JitSampleSet* jit = nullptr);
+                         double* hist = nullptr, const JitSampleSet* jit = nullptr, uint64_t* advance = nullptr);
 // Dynamic LDS bytes of a sample launch with VEGAS accumulation (grid area
 // lds_bytes, vstride doubles per wave histogram) for the register class of
 // (max_slots, max_inv).
 size_t sample_lds_bytes(int max_slots, int max_inv, size_t lds_bytes, int vstride);
 
-// Device copy of a host-built call table (stream ordered).
-hipError_t launch_set_call(const SampleCall& host, SampleCall* dev, hipStream_t s);
+// Device copy of a host-built call table (stream ordered); with clear != NULL
+// the same launch zeroes clear[n_clear].
+hipError_t launch_set_call(const SampleCall& host, SampleCall* dev, double* clear, int n_clear, hipStream_t s);
+// x[n] = 0 for a few values, by a kernel (so that a caller may capture it).
+hipError_t launch_clear(double* x, int n, hipStream_t s);
 
 // Call table from device-resident counts: prefix sums over n_chan channels,
 // tiles of kBlock * ept events.  If a count is negative or the total exceeds
@@ -158,9 +162,6 @@ int sample_block();  // threads per workgroup of the sample kernel
 int64_t moments_blocks();
 hipError_t launch_moments_add(const double* w, int64_t n, double* part, double* out, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* x, int64_t n, int32_t v, hipStream_t s);
-// *ctr += the events of the call table (device-count launches that advance
-// their counter offset).
-hipError_t launch_advance_counter(const SampleCall* call, uint64_t* ctr, hipStream_t s);
 
 // The allocation-free sample entry point's fixed device scratch: room for the
 // tile statistics of kNoAllocTiles tiles, one copy per GPU (devices

@@ -195,3 +195,69 @@ def test_unweighting_of_many_blocks(torch, n):
     assert np.array_equal(out["keep"][:k].cpu().numpy(), ref["keep"])
     assert np.array_equal(out["uw"][:k].cpu().numpy(), ref["uw"])
     ctx.close()
+
+
+@pytest.mark.parametrize("n_chan", [1, 2, 63, 64])
+@pytest.mark.parametrize("counts", ["ragged", "full", "none", "over", "negative", "huge"])
+def test_call_table_of_device_counts(torch, n_chan, counts):
+    """The call table that one wave makes of device counts: the host call's
+    events and statistics, the counter moved on by their number; refused counts
+    (negative, over the capacity, sums beyond 64 bits) sample nothing.  Exact."""
+    from paper_2602_06895_amd import SAMPLE_ADVANCE_COUNTER, Context
+
+    cap = 20000
+    desc = W.c1_ee_mumu()
+    ctx = Context(dict(desc, channels=desc["channels"][:1] * n_chan))
+    k = np.array([(257 * c) % 300 + (c % 3 == 0) for c in range(n_chan)], dtype=np.int64)
+    if counts == "full":
+        k[-1] += cap - k.sum()
+    elif counts == "none":
+        k[:] = 0
+    elif counts == "over":
+        k[-1] += cap - k.sum() + 1
+    elif counts == "negative":
+        k[n_chan // 2] = -1
+    elif counts == "huge":
+        k[:] = 2 ** 63 - 1
+    buf = ctx.sample_buffers(cap)
+    buf["w"].fill_(-7.0)
+    off = torch.tensor([777], dtype=torch.int64, device="cuda")
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    ctx.sample_device(torch.from_numpy(k).cuda(), 9, 4, off, buf, status, flags=SAMPLE_ADVANCE_COUNTER)
+    got = ctx.stats()
+    refused = counts in ("over", "negative", "huge")
+    n = 0 if refused else int(k.sum())
+    assert int(status.cpu()[0]) == int(refused) and int(off.cpu()[0]) == 777 + n
+    assert bool((buf["w"][n:] == -7.0).all())
+    ctx.reset_stats()
+    assert not ctx.stats().any()
+    if n:
+        ref = ctx.sample(k, seed=9, stream_id=4, counter_offset=777)
+        assert np.array_equal(got, ctx.stats())
+        assert torch.equal(buf["w"][:n], ref["w"]) and torch.equal(buf["chan"][:n], ref["chan"])
+    else:
+        assert not got.any()
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 1000, 2049 * 256])
+@pytest.mark.parametrize("desc", [W.c3_ttbar6, W.c2_pp4j])
+def test_adaptation_is_its_steps(torch, n, desc):
+    """msx_vegas_adapt against its steps called one by one, with old statistics
+    in the context: the same statistics (one pass and two) and grids, exactly."""
+    from paper_2602_06895_amd import SAMPLE_ACCUMULATE_VEGAS, Context, adapt_vegas
+
+    a, b = Context(desc()), Context(desc())
+    a.sample([5] * a.n_channels, seed=1, stream_id=1, counter_offset=0)
+    got = adapt_vegas(a, n, 2, 0.5, 3, 2, 11)
+    for it in range(2):
+        b.reset_stats()
+        b.sample([n] * b.n_channels, seed=3, stream_id=2, counter_offset=11 + it * n * b.n_channels,
+                 flags=SAMPLE_ACCUMULATE_VEGAS)
+        want = b.stats()
+        b.vegas_update(0.5)
+    assert np.array_equal(got, want) and not a.stats().any()
+    for c in range(a.n_channels):
+        assert np.array_equal(a.get_grid(c), b.get_grid(c))
+    a.close()
+    b.close()
