@@ -399,12 +399,12 @@ __global__ __launch_bounds__(kBlock) void k_cut(const double* __restrict__ x, in
 
 // Weighted histogram, deterministic: bin = floor((x - lo) * scale), events
 // with x outside [lo, hi) or w = 0 skipped (they add nothing).  A workgroup
-// takes a contiguous run of events; each of its waves keeps a private
-// (sum w, sum w^2) histogram in LDS and adds its events 64 at a time: one
-// ballot per bit of the bin number gives every lane the lanes that share its
-// bin, and the lanes then add in rounds, the r-th lane of every bin in round
-// r, so no two lanes of a round write one entry and an entry's terms come in
-// event order.  The waves' histograms are added in wave order into the
+// takes a contiguous run of events; each group of lanes of its waves keeps a
+// private (sum w, sum w^2) histogram in LDS and a wave adds its events 64 at a
+// time: one ballot per bit of the bin number gives every lane the lanes of its
+// group that share its bin, and the lanes then add in rounds, the r-th lane of
+// every bin in round r, so no two lanes of a round write one entry and an
+// entry's terms come in event order.  The histograms are added in order into the
 // workgroup's partial, part[entry][workgroup], and k_hist_reduce sums every
 // entry over the workgroups in a fixed order.
 //
@@ -412,19 +412,26 @@ __global__ __launch_bounds__(kBlock) void k_cut(const double* __restrict__ x, in
 // fullest bin (a dozen for the p_T and mass spectra of pp -> 4 jets in 50
 // bins).  Before, every thread scanned the 2048 staged events of a workgroup
 // for each of its bins: 600 us for 1e7 events and 50 bins, and 103 us more to
-// add 4883 partials in two workgroups; now 62 us and 5.
+// add 4883 partials in two workgroups; with one histogram a wave 62 us and 5,
+// with four 50 (eight: 47 to 50).
 constexpr int kHistPer = 2048;    // events per workgroup at least
 constexpr int kHistBlocks = 2048; // workgroups at most
 constexpr int kHistSmall = 512;   // up to this many bins four waves share a workgroup (32 KiB of LDS), else one
 
+// Histograms of a wave: groups of neighbouring lanes have one each, as long as
+// 32 KiB hold them, which shortens the rounds to the fullest bin of a group.
+int hist_groups(int nb) { return nb <= kHistSmall / 4 ? 4 : nb <= kHistSmall / 2 ? 2 : 1; }
+
 __global__ __launch_bounds__(kBlock) void k_hist_block(const double* __restrict__ x, const double* __restrict__ w,
-                                                       int64_t n, int64_t chunk, int nb, int bits, double lo, double hi,
-                                                       double scale, double* __restrict__ part) {
-    extern __shared__ double hs[];  // [waves][nb][2]
+                                                       int64_t n, int64_t chunk, int nb, int bits, int groups, double lo,
+                                                       double hi, double scale, double* __restrict__ part) {
+    extern __shared__ double hs[];  // [waves][groups][nb][2]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    for (int i = threadIdx.x; i < waves * nb * 2; i += blockDim.x) hs[i] = 0.0;
+    for (int i = threadIdx.x; i < waves * groups * nb * 2; i += blockDim.x) hs[i] = 0.0;
     __syncthreads();
-    volatile double* mine = hs + (size_t)wave * nb * 2;
+    const int wide = 64 / groups, group = lane / wide;  // lanes of a group
+    volatile double* mine = hs + (size_t)(wave * groups + group) * nb * 2;
+    const uint64_t peers = (~uint64_t(0) >> (64 - wide)) << (group * wide);
     const int64_t e0 = blockIdx.x * chunk, e1 = min(n, e0 + chunk);
     const uint64_t below = (uint64_t(1) << lane) - 1;
     constexpr int kFlight = 4;
@@ -445,7 +452,7 @@ __global__ __launch_bounds__(kBlock) void k_hist_block(const double* __restrict_
                 b = b < 0 ? 0 : (b > nb - 1 ? nb - 1 : b);
             }
             uint64_t left = __ballot(in);
-            uint64_t same = left;
+            uint64_t same = left & peers;
             for (int q = 0; q < bits; ++q) {
                 const bool bit = (b >> q) & 1;
                 const uint64_t set = __ballot(bit);
@@ -466,7 +473,7 @@ __global__ __launch_bounds__(kBlock) void k_hist_block(const double* __restrict_
     __syncthreads();
     for (int i = threadIdx.x; i < nb * 2; i += blockDim.x) {
         double a = hs[i];
-        for (int v = 1; v < waves; ++v) a += hs[(size_t)v * nb * 2 + i];
+        for (int v = 1; v < waves * groups; ++v) a += hs[(size_t)v * nb * 2 + i];
         part[(int64_t)i * gridDim.x + blockIdx.x] = a;
     }
 }
@@ -865,9 +872,10 @@ hipError_t launch_histogram(const double* x, const double* w, int64_t n, int nb,
     int bits = 0;
     while ((1 << bits) < nb) ++bits;
     const int threads = nb <= kHistSmall ? kBlock : 64;
-    const size_t lds = sizeof(double) * 2 * (size_t)nb * (threads / 64);
-    k_hist_block<<<dim3((unsigned)nz), dim3(threads), lds, s>>>(x, w, n, (n + nz - 1) / nz, nb, bits, lo, hi, scale,
-                                                                part);
+    const int groups = hist_groups(nb);
+    const size_t lds = sizeof(double) * 2 * (size_t)nb * (threads / 64) * groups;
+    k_hist_block<<<dim3((unsigned)nz), dim3(threads), lds, s>>>(x, w, n, (n + nz - 1) / nz, nb, bits, groups, lo,
+                                                                hi, scale, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_hist_reduce<<<dim3((unsigned)(2 * nb)), dim3(64), 0, s>>>(part, (int)nz, nb, out);

@@ -126,10 +126,10 @@ def test_unweighting_efficiency_search(torch, kind, n):
     ctx.close()
 
 
-@pytest.mark.parametrize("bins", [1, 2, 63, 64, 65, 512, 513, 4096])
+@pytest.mark.parametrize("bins", [1, 2, 63, 64, 65, 128, 129, 256, 257, 512, 513, 4096])
 @pytest.mark.parametrize("n", [0, 1, 63, 2049, 2048 * 2048 + 77])
 def test_histogram_shapes(torch, bins, n):
-    """One and four waves per workgroup, one bin, more bins than events, all
+    """One and four waves per workgroup, one, two and four histograms a wave, one bin, more bins than events, all
     events in one bin, values on the ends of the range; the same bits on a
     second call.  Sums of non-negative terms: n times the unit roundoff."""
     from paper_2602_06895_amd import Context
