@@ -46,7 +46,7 @@ constexpr size_t layers_lds(int d, int kept) {
 // FP32 conditioners are bound by the FP32 matrix instructions (16 of them for
 // one in BF16): 4,097 events of 16 dimensions, inverse, 8 layers: 24 us each,
 // of which 11 are products; they were 130 us as seven kernels.
-template <bool INV, int NT, bool KEEP, bool K16, class T>
+template <bool INV, int NT, bool KEEP, int BINS, class T>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_flow_layers(FlowNet fn,
                                                                                                  FlowRun run) {
     constexpr int EV = 16 * NT;
@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 Theta th = output_layer<NT, KEEP>(fn, layer, a0, w4, bias, j, K, lane);
                 const float vin = zt[tj * EV + ev];
                 float sw, sh, ld;
-                spline_exp<K16>(th, K, sw, sh);
-                Bin b = spline_find<INV, K16>(th, K, vin, sw, sh);
+                spline_exp<BINS == 16>(th, BINS ? BINS : K, sw, sh);
+                Bin b = spline_find<INV, BINS == 16>(th, BINS ? BINS : K, vin, sw, sh);
                 spline_slopes(b);
                 const float v = spline_value<INV>(b, vin, ld);
                 const int64_t e = tile * EV + ev;
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // tile would not change that, more take their splines' time.  1,000 events of 16
 // dimensions, 8 layers: 60 us; with the weights loaded when a layer begins and
 // the coordinates through memory (k_flow_layers with tiles of 16) 68.
-template <bool INV, bool K16>
+template <bool INV, int BINS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_flow_tile(FlowNet fn,
                                                                                                FlowRun run) {
     typedef __bf16 T;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     __shared__ __attribute__((aligned(16))) T cond[EV * kCond];
     __shared__ float zs[2 * kWaves][EV];
     __shared__ float lds_ld[kWaves][EV];
-    if (K16) fn.K = 16;
+    if (BINS) fn.K = BINS;
     const int nh = fn.nh, d = 2 * nh, K = fn.K;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ev = lane & 15, q = lane >> 4;
@@ -234,8 +234,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             const int tj = mk.t0 + mk.ts * wave;
             const float vin = zs[tj][ev];
             float sw, sh, l;
-            spline_exp<K16>(th, K, sw, sh);
-            Bin b = spline_find<INV, K16>(th, K, vin, sw, sh);
+            spline_exp<BINS == 16>(th, K, sw, sh);
+            Bin b = spline_find<INV, BINS == 16>(th, K, vin, sw, sh);
             spline_slopes(b);
             const float v = spline_value<INV>(b, vin, l);
             if (lane < EV) {
@@ -255,6 +255,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (tid < EV && e0 + tid < n) run.logdet[e0 + tid] = ld;
 }
 
+// The bins are a constant of the kernels where they are 16 (the knots are then
+// searched by halves) or, in BF16, 8: with the number known at run time only,
+// each bin's exponentials stand behind a branch of their own and wait for
+// themselves (450,000 events of 10 dimensions, 6 layers, 8 bins, inverse: 1164
+// us, as a constant 805; the same bits).  Other numbers take the branches.
 template <bool INV, int NT, class T>
 hipError_t launch_layers(const FlowNet& fn, const FlowRun& run, int64_t grid, hipStream_t s) {
     constexpr bool can_keep = sizeof(T) == 2 && NT == 4;
@@ -262,13 +267,15 @@ hipError_t launch_layers(const FlowNet& fn, const FlowRun& run, int64_t grid, hi
     const size_t lds = layers_lds<NT, T>(2 * fn.nh, keep ? fn.nh : 0);
     const dim3 g((unsigned)grid), t(kThreads);
     if (keep && fn.K == 16)
-        k_flow_layers<INV, NT, can_keep, true, T><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, can_keep, 16, T><<<g, t, lds, s>>>(fn, run);
+    else if (keep && fn.K == 8)
+        k_flow_layers<INV, NT, can_keep, can_keep ? 8 : 0, T><<<g, t, lds, s>>>(fn, run);
     else if (keep)
-        k_flow_layers<INV, NT, can_keep, false, T><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, can_keep, 0, T><<<g, t, lds, s>>>(fn, run);
     else if (fn.K == 16)
-        k_flow_layers<INV, NT, false, true, T><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, false, 16, T><<<g, t, lds, s>>>(fn, run);
     else
-        k_flow_layers<INV, NT, false, false, T><<<g, t, lds, s>>>(fn, run);
+        k_flow_layers<INV, NT, false, 0, T><<<g, t, lds, s>>>(fn, run);
     return hipGetLastError();
 }
 
@@ -294,9 +301,11 @@ hipError_t launch_pass(const FlowNet& fn, const FlowRun& run, int cu_count, hipS
     if (t16 <= cu_count) {
         if (fn.nh > kWaves) return launch_layers<INV, 1, __bf16>(fn, run, t16, s);
         if (fn.K == 16)
-            k_flow_tile<INV, true><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
+            k_flow_tile<INV, 16><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
+        else if (fn.K == 8)
+            k_flow_tile<INV, 8><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
         else
-            k_flow_tile<INV, false><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
+            k_flow_tile<INV, 0><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
         return hipGetLastError();
     }
     return launch_layers<INV, 4, __bf16>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);
