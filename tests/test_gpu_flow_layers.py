@@ -34,7 +34,8 @@ def _pair(d, layers, bins, seed, scale=0.05):
 
 SHAPES = [(16, 5, 16, 1), (16, 4, 16, 15), (16, 4, 16, 16), (16, 4, 16, 17), (10, 4, 16, 1000), (16, 2, 16, 4096),
           (16, 2, 16, 4097), (14, 2, 16, 16385), (2, 3, 16, 100), (18, 2, 16, 4200), (64, 2, 16, 300),
-          (64, 2, 12, 4160), (16, 4, 1, 70), (16, 2, 2, 5000), (10, 2, 15, 70), (18, 2, 5, 90)]
+          (64, 2, 12, 4160), (16, 4, 1, 70), (16, 2, 2, 5000), (10, 2, 15, 70), (18, 2, 5, 90),
+          (10, 4, 8, 1000), (16, 2, 8, 4097), (64, 2, 8, 300)]
 
 
 @pytest.mark.parametrize("d,layers,bins,n", SHAPES)
