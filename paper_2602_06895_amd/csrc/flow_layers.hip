@@ -255,23 +255,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (tid < EV && e0 + tid < n) run.logdet[e0 + tid] = ld;
 }
 
-// The bins are a constant of the kernels where they are 16 (the knots are then
-// searched by halves) or, in BF16, 8: with the number known at run time only,
-// each bin's exponentials stand behind a branch of their own and wait for
-// themselves (450,000 events of 10 dimensions, 6 layers, 8 bins, inverse: 1164
-// us, as a constant 805; the same bits).  Other numbers take the branches.
+// The bins are a constant of the kernels of large BF16 passes: with their number
+// known at run time only, each bin's exponentials stand behind a branch of their
+// own and wait for themselves (450,000 events of 10 dimensions, 6 layers, 8
+// bins, inverse: 1164 us, as a constant 805; the same bits).  In the others,
+// bound by their weights or their products, only 16 bins are, whose knots are
+// searched by halves, and in tiles of 16 events 8.
+template <bool INV, int BINS>
+void launch_bins(const FlowNet& fn, const FlowRun& run, dim3 g, size_t lds, hipStream_t s) {
+    if constexpr (BINS > 0) {
+        if (fn.K == BINS)
+            k_flow_layers<INV, 4, true, BINS, __bf16><<<g, dim3(kThreads), lds, s>>>(fn, run);
+        else
+            launch_bins<INV, BINS - 1>(fn, run, g, lds, s);
+    }
+}
+
 template <bool INV, int NT, class T>
 hipError_t launch_layers(const FlowNet& fn, const FlowRun& run, int64_t grid, hipStream_t s) {
     constexpr bool can_keep = sizeof(T) == 2 && NT == 4;
     const bool keep = can_keep && fn.nh <= kWaves;  // then W4 fits in LDS: at most 98 KiB
     const size_t lds = layers_lds<NT, T>(2 * fn.nh, keep ? fn.nh : 0);
     const dim3 g((unsigned)grid), t(kThreads);
-    if (keep && fn.K == 16)
-        k_flow_layers<INV, NT, can_keep, 16, T><<<g, t, lds, s>>>(fn, run);
-    else if (keep && fn.K == 8)
-        k_flow_layers<INV, NT, can_keep, can_keep ? 8 : 0, T><<<g, t, lds, s>>>(fn, run);
-    else if (keep)
-        k_flow_layers<INV, NT, can_keep, 0, T><<<g, t, lds, s>>>(fn, run);
+    if (fn.K < 1 || fn.K > 16) return hipErrorInvalidValue;
+    if (keep)
+        launch_bins<INV, 16>(fn, run, g, lds, s);
     else if (fn.K == 16)
         k_flow_layers<INV, NT, false, 16, T><<<g, t, lds, s>>>(fn, run);
     else
