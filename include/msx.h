@@ -199,9 +199,17 @@ msx_status msx_inverse_map(msx_ctx* ctx, int32_t channel, int64_t n, const doubl
  * (host, one entry >= 0 per channel of the process) are the a-priori channel
  * weights.  An event that channel c's chain cuts contributes 0.  The
  * multichannel weight of an event is then f(p) / g(p).  p [4][np][n],
- * x1x2 [2][n] (hadronic) and g [n] are device arrays.  Uses a context-owned
- * scratch of (max dims + 1) n doubles (grown on demand: a call that grows it
- * synchronizes the device).  n = 0 is a no-op. */
+ * x1x2 [2][n] (hadronic) and g [n] are device arrays.  Channels that follow each
+ * other and share a kernel are evaluated together, up to 16 of them, in a
+ * context-owned scratch of (max dims + 1) n doubles for each; altogether it is
+ * at most 2 GiB, or one channel's if that is more.  It is sized for the context's
+ * longest such run, kept until msx_destroy and grown on demand: a call with more
+ * events than any before synchronizes the device and replaces it (so it is
+ * refused while its stream is captured, and work captured before must not be
+ * replayed after it); a call with as many events or fewer, of any process, does
+ * neither.  If the device cannot give that much, the context takes one channel at
+ * a time from then on, and the scratch is that of the process's (max dims + 1) n
+ * doubles.  n = 0 is a no-op. */
 msx_status msx_multichannel_density(msx_ctx* ctx, int32_t process, int64_t n, const double* p, const double* x1x2,
                                     const double* alpha, double* g, void* stream);
 

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "compiler.h"
+#include "density_scratch.h"
 #include "jit.h"
 #include "json.h"
 #include "launch.h"
@@ -49,6 +50,10 @@ struct msx_ctx {
     int64_t ublk_cap = 0;
     double* d_inv = nullptr;  // multichannel density scratch: y [channels][max dims][n] then jac [channels][n]
     int64_t inv_cap = 0;      // doubles
+    bool inv_single = false;  // one channel at a time: more could not be had
+    // the largest dimension of a channel and the most channels of a process that
+    // follow each other and share a class (up to kMaxLaunchChans)
+    int density_dims = 0, density_run = 1;
     int64_t vpart_cap = 0;
     double* d_unw = nullptr;  // 3 * 4096 bucket words + 2 * 1024 partials + 2 + the search state (3)
     // VEGAS accumulation inside the fused sample: per-channel histogram
@@ -291,6 +296,20 @@ msx_status msx_create_channels(const char* process_json, int32_t precision, int3
         c->all_kinds |= c->comp.chans[ch].kinds;
         c->any_hadronic = c->any_hadronic || m.hadronic;
     }
+    for (int pr = 0; pr < (int)c->comp.procs.size(); ++pr) {
+        const ChannelTab* first = nullptr;  // of the run
+        int run = 0;
+        for (int ch = 0; ch < C; ++ch) {
+            if (c->comp.meta[ch].process != pr) continue;
+            const ChannelTab& t = c->comp.chans[ch];
+            const bool same =
+                first && same_chain_class(first->n_slots, first->n_inv, first->kinds, t.n_slots, t.n_inv, t.kinds);
+            if (!same) first = &t;
+            run = same ? run + 1 : 1;
+            c->density_run = std::max(c->density_run, std::min(run, kMaxLaunchChans));
+            c->density_dims = std::max(c->density_dims, c->comp.meta[ch].dims);
+        }
+    }
     c->grid_total = (int64_t)grids.size();
     c->n_rows = (int)row_nb.size();
     for (int ch = 0; ch < C; ++ch)
@@ -462,10 +481,30 @@ msx_status msx_multichannel_density(msx_ctx* ctx, int32_t process, int64_t n, co
     // Runs of channels of one class go into one launch each of the inverse and
     // of the Jacobian, whose waves wait for one another: eight channels of
     // 200,000 events take 3 waves per SIMD each, where 4 (inverse) and 3 fit.
-    // Up to kDensityScratch of scratch; at least one channel at a time.
-    constexpr int64_t kDensityScratch = (int64_t)2 << 30;
     const int64_t one = (int64_t)(dmax + 1) * n;  // doubles per channel
-    auto run_from = [&](size_t i, int64_t limit) {
+    // the scratch grows with the largest n so far; a context whose full scratch
+    // could not be had takes one channel at a time from then on
+    const int64_t need = ctx->inv_single ? one : density_scratch(ctx->density_dims, ctx->density_run, n);
+    if (need > ctx->inv_cap) {
+        // the previous scratch may still be read by work in flight
+        MSX_HIP(ctx, hipDeviceSynchronize(), "synchronize");
+        if (ctx->d_inv) MSX_HIP(ctx, hipFree(ctx->d_inv), "hipFree");
+        ctx->d_inv = nullptr;
+        ctx->inv_cap = 0;
+        if (need > one && dmalloc(&ctx->d_inv, need) != hipSuccess) {
+            (void)hipGetLastError();
+            ctx->d_inv = nullptr;
+        }
+        if (ctx->d_inv) {
+            ctx->inv_cap = need;
+        } else {
+            MSX_HIP(ctx, dmalloc(&ctx->d_inv, one), "density scratch");
+            ctx->inv_cap = one;
+            ctx->inv_single = ctx->inv_single || need > one;
+        }
+    }
+    const int64_t limit = ctx->inv_cap / one;
+    auto run_from = [&](size_t i) {
         const ChannelTab& a = ctx->comp.chans[chans[i]];
         size_t k = i + 1;
         for (; k < chans.size() && (int64_t)(k - i) < std::min<int64_t>(limit, kMaxLaunchChans); ++k) {
@@ -474,35 +513,8 @@ msx_status msx_multichannel_density(msx_ctx* ctx, int32_t process, int64_t n, co
         }
         return k;
     };
-    int64_t limit = std::max<int64_t>(1, kDensityScratch / (int64_t)sizeof(double) / one), most = 1;
     for (size_t i = 0; i < chans.size();) {
-        const size_t k = run_from(i, limit);
-        most = std::max<int64_t>(most, (int64_t)(k - i));
-        i = k;
-    }
-    if (most * one > ctx->inv_cap) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        MSX_HIP(ctx, hipStreamIsCapturing(s, &capture), "capture status");
-        if (capture != hipStreamCaptureStatusNone && one <= ctx->inv_cap) {
-            most = ctx->inv_cap / one;  // no allocation while capturing
-        } else {
-            // the previous scratch may still be read by work in flight
-            MSX_HIP(ctx, hipDeviceSynchronize(), "synchronize");
-            if (ctx->d_inv) MSX_HIP(ctx, hipFree(ctx->d_inv), "hipFree");
-            ctx->d_inv = nullptr;
-            ctx->inv_cap = 0;
-            if (most > 1 && dmalloc(&ctx->d_inv, most * one) != hipSuccess) {
-                (void)hipGetLastError();
-                ctx->d_inv = nullptr;
-                most = 1;
-            }
-            if (!ctx->d_inv) MSX_HIP(ctx, dmalloc(&ctx->d_inv, most * one), "density scratch");
-            ctx->inv_cap = most * one;
-        }
-        limit = std::min(limit, most);
-    }
-    for (size_t i = 0; i < chans.size();) {
-        const size_t k = run_from(i, limit);
+        const size_t k = run_from(i);
         LaunchChans lc = chans_of(ctx, chans[i]);
         lc.y_step = (int64_t)dmax * n;
         DensityAlpha da{};
