@@ -377,7 +377,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // 65,536 events of 16 dimensions: 40 us, 157 MB at 3.9 TB/s (with every wave
 // loading its operands from the caches itself, eight times the traffic and no
 // load ahead of its use, 82 us).  The partial sums of 128 runs are 43 MB: more
-// runs would fill more compute units, but write and add up as much again.
+// runs would fill more compute units, but write and add up as much again
+// (flow_wgrad_splits).
 constexpr int kBlockH = 3 * kHid * 32, kBlockD = 16 * kGradTiles * 32, kBlockX = 32 * 32;  // elements
 constexpr int kBlockElems = 2 * kBlockH + kBlockD + kBlockX;
 
@@ -618,14 +619,27 @@ hipError_t launch_flow_mlp_reverse(const FlowNet& fn, const FlowRev& r, const vo
 }
 
 // Runs of events of the weight gradients.  More of them fill more compute units,
-// but each writes, and the reduction reads, all partial sums (336 KB): runs of 64
-// events up to 64, from 8,192 events of 128, from 16,384 on 128 runs (1,000
-// events: 515 us a gradient with runs of 256, 429 with 64; 8,192: 600, 580 with
-// 64, 557 with 128).  FP32: blockIdx.y gives seven workgroups per run of eight
-// coordinates already, so up to 32 runs of at least 64.
+// but each writes, and the reduction reads, all partial sums (336 KB for 8 + 8
+// coordinates and 16 bins).  Their length is also the number of terms that one
+// FP32 accumulator adds up, so the runs grow with n.
+//
+// BF16: runs of 64 events up to 64, from 8,192 events of 128, from 16,384 on 128
+// runs (1,000 events, 8 layers: 515 us a gradient with runs of 256, 429 with 64;
+// 8,192: 600, 580 with 64, 557 with 128), of 512 and more up to 256 runs (65,536
+// events: 1449 us with 128 runs, 1559 with 256; 2^20 events, 2 layers: 4689 with
+// 128, 4379 with 256, 4494 with 512).  The error against 64 bits is that of the
+// BF16 operands (3e-3 to 2e-2), the same to four digits for 64 to 8,192 events a
+// run.
+//
+// FP32: blockIdx.y gives seven workgroups per run of eight coordinates already, so
+// up to 32 runs of at least 64, and from 8,192 events on runs of 256 up to 512
+// runs.  With 32 runs whatever n is, the error of W4's gradient grew with n (2^18
+// events: 9.0e-7, now 8.6e-7; 10 dimensions, 8 bins, 65,536 events: 3.4e-7, now
+// 3.1e-7) and half of the chip waited (65,536 events, 4 layers: 3272 us, now 2943).
 int flow_wgrad_splits(const FlowNet& fn, int64_t n) {
-    const int64_t runs = std::min<int64_t>(n / 64, fn.f32 ? 32 : 64);
-    return (int)std::max<int64_t>(1, fn.f32 ? runs : std::max(runs, std::min<int64_t>(128, n / 128)));
+    if (fn.f32) return (int)std::max<int64_t>({1, std::min<int64_t>(n / 64, 32), std::min<int64_t>(n / 256, 512)});
+    return (int)std::max<int64_t>({1, std::min<int64_t>(n / 64, 64), std::min<int64_t>(n / 128, 128),
+                                   std::min<int64_t>(n / 512, 256)});
 }
 
 hipError_t launch_flow_wgrad(const FlowNet& fn, const FlowRev& r, int splits, float* part, int cu_count, hipStream_t s) {

@@ -183,3 +183,41 @@ def test_fp32_gradient_matches_oracle(torch, d, layers, bins, n):
         assert torch.equal(a, b)
     f.close()
     h.close()
+
+
+@pytest.mark.parametrize("d,bins,n", [(16, 16, 1 << 18), (10, 8, 1 << 16), (18, 5, 1 << 15)])
+def test_fp32_gradient_sums_stay_short(torch, d, bins, n):
+    """n equal events, n a power of two: every event adds the same term, the
+    one-event gradient divided by n exactly, so the sum should be that gradient.
+    An accumulator takes one run of at most max(256, n / 512) events, a rounding
+    each, and the partial sums of up to 512 runs are added in 16 chains: (run +
+    40) u relative, whatever n is."""
+    f, _ = _pair_f32(d, 2, bins, 3)
+    *_, one = _batch(torch, d, 1, 4)
+    want, _ = f.gradient(*one)
+    got, _ = f.gradient(one[0].expand(d, n).contiguous(), one[1].expand(n).contiguous(), one[2].expand(n).contiguous())
+    err = (got.double() - want.double()).abs()
+    assert bool((err <= (max(256, n // 512) + 40) * 2.0 ** -24 * want.double().abs() + 1e-30).all())
+    f.close()
+
+
+def test_fp32_gradient_blocks_of_a_large_batch(torch):
+    """Every weight and bias gradient of its own against the FP64 oracle, at more
+    events than the number of runs is limited by; the bound of the whole
+    gradient."""
+    import torch as t
+
+    d, layers, bins, n = 16, 2, 16, 40_001
+    f, orc = _pair_f32(d, layers, bins, 11)
+    y, wfj, lqo, dev = _batch(torch, d, n, 12)
+    g, _ = f.gradient(*dev)
+    _, ref = orc.loss_and_grad(t.from_numpy(y.T.astype(np.float64)), t.from_numpy(wfj) ** 2,
+                               t.from_numpy(lqo.astype(np.float64)))
+    got, ref = g.cpu().numpy().astype(np.float64), ref.numpy()
+    at = 0
+    for _ in range(layers):
+        for shape in orc.shapes:
+            k = int(np.prod(shape))
+            assert np.linalg.norm(got[at:at + k] - ref[at:at + k]) <= 1e-3 * np.linalg.norm(ref[at:at + k])
+            at += k
+    f.close()
