@@ -95,47 +95,49 @@ __device__ __forceinline__ TileSum sum_tiles(const double* tile_stats, int64_t t
     return r;
 }
 
-// A channel with more than kStatTiles tiles is reduced in two passes: first
+// A channel with more than kStatTiles tiles is reduced in two steps: first
 // kStatSlices workgroups sum a contiguous run of its tiles each, in place
-// (into the run's first entry), then k_stats_final adds the runs.  One
-// workgroup per channel walking all its tiles is bound by the latency of its
-// loads: 147 us for the 78125 tiles of 2e7 t tbar events, 11 us in two
-// passes; up to 2048 tiles (eight loads a thread) the second launch would
-// cost more than it saves.
+// (into the run's first entry), then the last of them to finish adds the runs.
+// One workgroup per channel walking all its tiles is bound by the latency of its
+// loads: 147 us for the 78125 tiles of 2e7 t tbar events, 11 us in two steps;
+// up to 2048 tiles (eight loads a thread) the slices would cost more than they
+// save.  A launch of its own for the slices, made whenever the buffers of a
+// device-count call hold that many tiles, took 2.2 us of the 16 of a thousand
+// two-dimensional events.
 constexpr int kStatTiles = 2048, kStatSlices = 64;
-
-__global__ __launch_bounds__(kBlock) void k_stats_slices(const SampleCall* __restrict__ call, double* tile_stats) {
-    const int c = blockIdx.y;
-    __shared__ double red[4][kWaves];
-    if (c >= call->n_chan || ((call->skip_mask >> c) & 1)) return;
-    const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
-    if (t1 - t0 <= kStatTiles) return;
-    const int64_t per = (t1 - t0 + kStatSlices - 1) / kStatSlices;
-    const int64_t b = t0 + blockIdx.x * per, e = min(t1, b + per);
-    if (b >= e) return;
-    const TileSum r = sum_tiles(tile_stats, b, e, red);
-    if (threadIdx.x == 0) {
-        tile_stats[b * 4 + 0] = r.s1;
-        tile_stats[b * 4 + 1] = r.s2;
-        tile_stats[b * 4 + 2] = r.zeros;
-        tile_stats[b * 4 + 3] = r.wmax;
-    }
-}
+int stat_slices(int64_t max_tiles) { return max_tiles > kStatTiles ? kStatSlices : 1; }
 
 // Reduce the tiles of channel c and add to its accumulators
 // stats[c] = (sum w, sum w^2, n, n(w == 0), max w); every thread of a workgroup
-// of at least kBlock calls it.
-__device__ __forceinline__ void channel_stats(int c, const SampleCall* __restrict__ call,
-                                              const double* __restrict__ tile_stats, double* __restrict__ stats,
-                                              double (&red)[4][kWaves]) {
+// of at least kBlock calls it, for every slice (kStatSlices of them if a channel
+// may have more than kStatTiles tiles, else one).
+__device__ __forceinline__ void channel_stats(int c, int slice, SampleCall* __restrict__ call, double* tile_stats,
+                                              double* __restrict__ stats, double (&red)[4][kWaves]) {
     if (c >= call->n_chan || ((call->skip_mask >> c) & 1)) return;
     const int64_t t0 = call->tile_start[c], t1 = call->tile_start[c + 1];
     TileSum r;
     if (t1 - t0 <= kStatTiles) {
+        if (slice) return;
         r = sum_tiles(tile_stats, t0, t1, red);
     } else {
-        // the runs' sums sit in the first entry of each run
         const int64_t per = (t1 - t0 + kStatSlices - 1) / kStatSlices;
+        const int64_t b = t0 + slice * per, e = min(t1, b + per);
+        if (b >= e) return;
+        const int slices = (int)((t1 - t0 + per - 1) / per);  // that have tiles
+        __shared__ int last;
+        const TileSum own = sum_tiles(tile_stats, b, e, red);
+        if (threadIdx.x == 0) {
+            tile_stats[b * 4 + 0] = own.s1;
+            tile_stats[b * 4 + 1] = own.s2;
+            tile_stats[b * 4 + 2] = own.zeros;
+            tile_stats[b * 4 + 3] = own.wmax;
+            __threadfence();
+            last = atomicAdd(&call->slices_done[c], 1u) == (unsigned)slices - 1;
+        }
+        __syncthreads();
+        if (!last) return;
+        __threadfence();
+        // the runs' sums sit in the first entry of each run
         const int64_t t = t0 + threadIdx.x * per;
         if (threadIdx.x < 64) {
             static_assert(kStatSlices == 64, "one lane per run");
@@ -156,14 +158,14 @@ __device__ __forceinline__ void channel_stats(int c, const SampleCall* __restric
     }
 }
 
-// The statistics of a call, a workgroup per channel.  After the sample has
-// read it the caller's event counter may move on (null: it stays).
-__global__ __launch_bounds__(kBlock) void k_stats_final(const SampleCall* __restrict__ call,
-                                                        const double* __restrict__ tile_stats,
+// The statistics of a call, a row of workgroups per channel.  After the sample
+// has read it the caller's event counter may move on (null: it stays).
+__global__ __launch_bounds__(kBlock) void k_stats_final(SampleCall* __restrict__ call, double* tile_stats,
                                                         double* __restrict__ stats, uint64_t* __restrict__ advance) {
     __shared__ double red[4][kWaves];
-    if (advance && threadIdx.x == 0 && blockIdx.x == 0) *advance += (uint64_t)call->ev_start[call->n_chan];
-    channel_stats(blockIdx.x, call, tile_stats, stats, red);
+    if (advance && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0)
+        *advance += (uint64_t)call->ev_start[call->n_chan];
+    channel_stats(blockIdx.y, blockIdx.x, call, tile_stats, stats, red);
 }
 
 // Hit-or-miss unweighting (the paper's channel-wise unweighting against an
@@ -540,19 +542,19 @@ __global__ __launch_bounds__(kSetThreads) void k_clear(double* __restrict__ x, i
 // The workgroups after those of the histograms do the call's statistics, which
 // saves their launch (4.6 us).
 constexpr int kVegasWaves = 16;
-__global__ __launch_bounds__(64 * kVegasWaves) void k_vegas_tiles(const SampleCall* __restrict__ call,
+__global__ __launch_bounds__(64 * kVegasWaves) void k_vegas_tiles(SampleCall* __restrict__ call,
                                                                   const int64_t* __restrict__ hist_off,
                                                                   int64_t hist_total, int vstride,
                                                                   const double* __restrict__ vpart,
                                                                   double* __restrict__ hist, int hist_blocks,
-                                                                  const double* __restrict__ tile_stats,
+                                                                  int slices, double* tile_stats,
                                                                   double* __restrict__ stats,
                                                                   uint64_t* __restrict__ advance) {
     if ((int)blockIdx.x >= hist_blocks) {
         __shared__ double stat_red[4][kWaves];
-        const int c = (int)blockIdx.x - hist_blocks;
-        if (advance && threadIdx.x == 0 && c == 0) *advance += (uint64_t)call->ev_start[call->n_chan];
-        channel_stats(c, call, tile_stats, stats, stat_red);
+        const int i = (int)blockIdx.x - hist_blocks;
+        if (advance && threadIdx.x == 0 && i == 0) *advance += (uint64_t)call->ev_start[call->n_chan];
+        channel_stats(i / slices, i % slices, call, tile_stats, stats, stat_red);
         return;
     }
     __shared__ double red[kVegasWaves][64];
@@ -601,7 +603,7 @@ __global__ __launch_bounds__(64) void k_plan(const int64_t* __restrict__ counts,
     uint64_t ev = (uint64_t)k;
     const int64_t mine = k / T + (k % T != 0);
     int64_t tiles = mine;
-    for (int step = 1; step < 64; step *= 2) {
+    for (int step = 1; step < n_chan; step *= 2) {
         const uint64_t e = __shfl_up((unsigned long long)ev, step);
         const int64_t t = __shfl_up((long long)tiles, step);
         if (c >= step) {
@@ -613,6 +615,7 @@ __global__ __launch_bounds__(64) void k_plan(const int64_t* __restrict__ counts,
     if (c < n_chan) {
         dev->ev_start[c] = bad ? 0 : (int64_t)ev - k;
         dev->tile_start[c] = bad ? 0 : tiles - mine;
+        dev->slices_done[c] = 0;
     }
     if (c == n_chan - 1) {
         dev->ev_start[n_chan] = bad ? 0 : (int64_t)ev;
@@ -991,7 +994,7 @@ hipError_t launch_weight(const ChannelTab* ct, const ProcessTab* pt, int mixed, 
 }
 
 hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const double* grids, const int64_t* grid_off,
-                         const int32_t* chan_nb, const SampleCall* call, int n_chan, int max_slots, int max_inv,
+                         const int32_t* chan_nb, SampleCall* call, int n_chan, int max_slots, int max_inv,
                          int kinds, int mixed, size_t lds_bytes, uint64_t seed, uint64_t sid, const uint64_t* ctr_dev,
                          uint64_t ctr_off, int np, int64_t ld, double* p, double* x1x2, double* w, int32_t* chan,
                          double* tile_stats, int64_t max_tiles, double* stats, int grid, hipStream_t s,
@@ -1036,14 +1039,13 @@ hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const dou
         hipError_t err = launch_chain(reg_class(max_slots, max_inv), kind_class(kinds), mixed, a);
         if (err != hipSuccess) return err;
     }
-    if (max_tiles > kStatTiles)
-        k_stats_slices<<<dim3(kStatSlices, (unsigned)n_chan), kBlock, 0, s>>>(call, tile_stats);
+    const int slices = stat_slices(max_tiles);
     if (vpart && hist_total > 0) {
         const int64_t g = (hist_total + 63) / 64;
-        k_vegas_tiles<<<dim3((unsigned)(g + n_chan)), dim3(64 * kVegasWaves), 0, s>>>(
-            call, hist_off, hist_total, vstride, vpart, hist, (int)g, tile_stats, stats, advance);
+        k_vegas_tiles<<<dim3((unsigned)(g + (int64_t)n_chan * slices)), dim3(64 * kVegasWaves), 0, s>>>(
+            call, hist_off, hist_total, vstride, vpart, hist, (int)g, slices, tile_stats, stats, advance);
     } else {
-        k_stats_final<<<n_chan, kBlock, 0, s>>>(call, tile_stats, stats, advance);
+        k_stats_final<<<dim3((unsigned)slices, (unsigned)n_chan), kBlock, 0, s>>>(call, tile_stats, stats, advance);
     }
     return hipGetLastError();
 }

@@ -131,7 +131,7 @@ struct JitSampleSet {
 // (max_slots, max_inv, kinds).  With advance != NULL, *advance += the events of
 // the call once they are drawn (launches that advance their counter offset).
 hipError_t launch_sample(const ChannelTab* cts, const ProcessTab* pts, const double* grids, const int64_t* grid_off,
-                         const int32_t* chan_nb, const SampleCall* call, int n_chan, int max_slots, int max_inv,
+                         const int32_t* chan_nb, SampleCall* call, int n_chan, int max_slots, int max_inv,
                          int kinds, int mixed, size_t lds_bytes, uint64_t seed, uint64_t sid, const uint64_t* ctr_dev,
                          uint64_t ctr_off, int np, int64_t ld, double* p, double* x1x2, double* w, int32_t* chan,
                          double* tile_stats, int64_t max_tiles, double* stats, int grid, hipStream_t s,

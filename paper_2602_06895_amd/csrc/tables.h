@@ -179,6 +179,7 @@ struct SampleCall {
     uint64_t skip_mask;                    // channels whose events another launch writes (no tiles, no statistics)
     int64_t tile_start[kMaxChannels + 1];  // first tile of each channel
     int64_t ev_start[kMaxChannels + 1];    // first output position
+    uint32_t slices_done[kMaxChannels];    // statistics in slices: those that are summed (zero before the call)
 };
 
 // The channels of one map or inverse launch, blockIdx.y of them: channel

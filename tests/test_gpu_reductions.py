@@ -261,3 +261,65 @@ def test_adaptation_is_its_steps(torch, n, desc):
         assert np.array_equal(a.get_grid(c), b.get_grid(c))
     a.close()
     b.close()
+
+
+def _nodes(torch, hip, call):
+    """The number of nodes of the graph that `call` is captured into (hip:
+    a library that is linked with the runtime)."""
+    import ctypes as C
+
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = C.c_size_t(0)
+    assert hip.hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("flags", [0, 1, 2])
+def test_device_count_sample_launches(torch, flags):
+    """A device-count sample takes the same launches (call table, sample,
+    statistics) whatever its buffers could hold."""
+    from paper_2602_06895_amd import SAMPLE_ACCUMULATE_VEGAS, SAMPLE_ADVANCE_COUNTER, Context
+
+    ctx = Context({"processes": [W.c1_ee_mumu(), W.c1_ee_mumu()]})
+    fl = (0, SAMPLE_ACCUMULATE_VEGAS, SAMPLE_ADVANCE_COUNTER)[flags]
+    counts = torch.tensor([700, 300], dtype=torch.int64, device="cuda")
+    off = torch.zeros(1, dtype=torch.int64, device="cuda")
+    nodes = []
+    for cap in (1 << 20, 4000):
+        buf = ctx.sample_buffers(cap)
+        ctx.sample_device(counts, 3, 1, off, buf, flags=fl)
+        torch.cuda.synchronize()
+        nodes.append(_nodes(torch, ctx.L, lambda: ctx.sample_device(counts, 3, 1, off, buf, flags=fl)))
+    assert nodes == [3, 3]
+    ctx.close()
+
+
+@pytest.mark.parametrize("vegas", [False, True])
+def test_statistics_of_device_counts(torch, vegas):
+    """The statistics of graph replays with many and few tiles in turn (slices and
+    one step, ragged slices, no events), with eager calls in between: those of
+    the host call of the same counts, exactly."""
+    from paper_2602_06895_amd import SAMPLE_ACCUMULATE_VEGAS, Context
+
+    a, b = (Context({"processes": [W.c1_ee_mumu()] * 3}) for _ in range(2))
+    cap, fl = 256 * 9000, SAMPLE_ACCUMULATE_VEGAS if vegas else 0
+    buf = a.sample_buffers(cap)
+    counts = torch.zeros(3, dtype=torch.int64, device="cuda")
+    off = torch.full((1,), 12, dtype=torch.int64, device="cuda")
+    g = a.sample_graph(counts, 9, 1, off, buf, flags=fl)
+    for k in ([256 * 2049, 5, 256 * 4000 + 1], [10, 256 * 2048, 0], [0, 0, 0], [256 * 2600 + 7, 256 * 3001, 256 * 2111],
+              [1, 0, 256 * 8000]):
+        counts.copy_(torch.tensor(k))
+        a.reset_stats()
+        b.reset_stats()
+        g.launch()
+        got = a.stats()
+        if sum(k):
+            b.sample(k, seed=9, stream_id=1, counter_offset=12, flags=fl)
+        want = b.stats()
+        assert np.array_equal(got, want) and list(got[:, 2]) == k
+    g.close()
+    a.close()
+    b.close()
