@@ -161,14 +161,15 @@ msx_status ensure_tiles(msx_ctx* ctx, int64_t tiles) {
     return MSX_OK;
 }
 
-// One channel of a map or inverse launch.
+// Channel c as the i-th of a map or inverse launch.
+void add_chan(const msx_ctx* ctx, LaunchChans& lc, int i, int c) {
+    lc.ct[i] = ctx->d_chans + c;
+    lc.grid[i] = ctx->d_grids + ctx->grid_off[c];
+    lc.nb[i] = ctx->comp.meta[c].nbins;
+}
 LaunchChans chans_of(const msx_ctx* ctx, int channel) {
     LaunchChans lc{};
-    lc.cts = ctx->d_chans;
-    lc.grids = ctx->d_grids;
-    lc.grid_off = ctx->d_grid_off;
-    lc.nb = ctx->d_chan_nb;
-    lc.c[0] = channel;
+    add_chan(ctx, lc, 0, channel);
     return lc;
 }
 
@@ -515,12 +516,12 @@ msx_status msx_multichannel_density(msx_ctx* ctx, int32_t process, int64_t n, co
     };
     for (size_t i = 0; i < chans.size();) {
         const size_t k = run_from(i);
-        LaunchChans lc = chans_of(ctx, chans[i]);
+        LaunchChans lc{};
         lc.y_step = (int64_t)dmax * n;
         DensityAlpha da{};
         int dims = 0, nb = 0;
         for (size_t j = i; j < k; ++j) {
-            lc.c[j - i] = chans[j];
+            add_chan(ctx, lc, (int)(j - i), chans[j]);
             da.a[j - i] = alpha[j];
             dims = std::max(dims, ctx->comp.meta[chans[j]].dims);
             nb = std::max(nb, ctx->comp.meta[chans[j]].nbins);

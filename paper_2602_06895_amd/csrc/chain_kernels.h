@@ -145,10 +145,9 @@ template <int NS, int NI, int KINDS, bool MIX>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(map_waves(NS, KINDS)))) void k_map(
     LaunchChans lc, const ProcessTab* __restrict__ pt, double s_lab, int np, int64_t n, const double* __restrict__ y,
     double* __restrict__ p, double* __restrict__ x1x2, double* __restrict__ jac, double* __restrict__ w) {
-    const int c = lc.c[blockIdx.y];
-    const ChannelTab* __restrict__ ct = lc.cts + c;
-    const double* __restrict__ grid = lc.grids + lc.grid_off[c];
-    const int nb = lc.nb[c];
+    const ChannelTab* __restrict__ ct = lc.ct[blockIdx.y];
+    const double* __restrict__ grid = lc.grid[blockIdx.y];
+    const int nb = lc.nb[blockIdx.y];
     y += blockIdx.y * lc.y_step;
     jac += blockIdx.y * n;  // more than one channel: Jacobians only
     extern __shared__ double lds[];
@@ -456,10 +455,9 @@ template <int NS, int NI, int KINDS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(inverse_waves(NS, KINDS)))) void k_inverse(
     LaunchChans lc, double s_lab, int np, int64_t n, const double* __restrict__ p, const double* __restrict__ x1x2,
     double* __restrict__ y) {
-    const int c = lc.c[blockIdx.y];
-    const ChannelTab* __restrict__ ct = lc.cts + c;
-    const double* __restrict__ grid = lc.grids + lc.grid_off[c];
-    const int nb = lc.nb[c];
+    const ChannelTab* __restrict__ ct = lc.ct[blockIdx.y];
+    const double* __restrict__ grid = lc.grid[blockIdx.y];
+    const int nb = lc.nb[blockIdx.y];
     y += blockIdx.y * lc.y_step;
     constexpr int NF = NS / 2 + 1;
     constexpr int kRows = stage_rows<NS, NI>();

@@ -56,7 +56,7 @@ hipError_t launch_inverse_class(int kind_class, const ChainLaunch& a);
 
 hipError_t launch_uniform(uint64_t seed, uint64_t sid, uint64_t e0, int64_t n, int d, double* y, hipStream_t s);
 
-// The events of one channel (chans.c[0]).
+// The events of one channel (the first of chans).
 hipError_t launch_map(const LaunchChans& chans, const ProcessTab* pt, int dims, int nb, int n_slots, int n_inv, int kinds,
                       int mixed, double s_lab, int np, int64_t n, const double* y, double* p, double* x1x2, double* jac,
                       double* w, int cu_count, hipStream_t s);

@@ -182,17 +182,16 @@ struct SampleCall {
     uint32_t slices_done[kMaxChannels];    // statistics in slices: those that are summed (zero before the call)
 };
 
-// The channels of one map or inverse launch, blockIdx.y of them: channel
-// c[blockIdx.y] of the context's tables and VEGAS grids, its arrays y and jac
-// at blockIdx.y y_step and blockIdx.y n.
+// The channels of one map or inverse launch, blockIdx.y of them: their table,
+// VEGAS grid and bins (in the kernel's arguments, so that a wave's first loads
+// wait for no others), and their arrays y and jac at blockIdx.y y_step and
+// blockIdx.y n.
 constexpr int kMaxLaunchChans = 16;
 struct LaunchChans {
-    const ChannelTab* cts;
-    const double* grids;
-    const int64_t* grid_off;
-    const int32_t* nb;
+    const ChannelTab* ct[kMaxLaunchChans];
+    const double* grid[kMaxLaunchChans];
+    int32_t nb[kMaxLaunchChans];
     int64_t y_step;
-    int32_t c[kMaxLaunchChans];
 };
 
 }  // namespace msx
