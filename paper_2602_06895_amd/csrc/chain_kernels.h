@@ -135,9 +135,9 @@ __device__ __forceinline__ double finish_event(const ChannelTab* __restrict__ ct
 // others (1 -> 3 decays, Chili, the largest slots in FP64) would spill
 // hundreds.
 constexpr bool tree_kinds(int kinds) { return (kinds & (KIND_CHILI | KIND_DEC3 | KIND_ST)) == 0; }
-constexpr int map_waves(int ns, int kinds) { return tree_kinds(kinds) ? (ns == 6 ? 3 : (ns == 10 ? 2 : 1)) : 1; }
+constexpr int map_waves(int ns, int kinds) { return tree_kinds(kinds) && ns == 10 ? 2 : 1; }
 constexpr int sample_waves(int ns, int kinds, bool mix) {
-    return mix && ns == 14 && tree_kinds(kinds) ? 2 : map_waves(ns, kinds);
+    return tree_kinds(kinds) ? (ns == 6 ? 3 : (ns == 10 || mix ? 2 : 1)) : 1;
 }
 constexpr int inverse_waves(int ns, int kinds) { return ns == 6 && !(kinds & KIND_DEC3) ? 4 : 1; }
 
