@@ -418,17 +418,23 @@ __global__ __launch_bounds__(kBlock) void k_cut(const double* __restrict__ x, in
 // with four 50 (eight: 47 to 50).
 constexpr int kHistPer = 2048;    // events per workgroup at least
 constexpr int kHistBlocks = 2048; // workgroups at most
-constexpr int kHistSmall = 512;   // up to this many bins four waves share a workgroup (32 KiB of LDS), else one
+constexpr int kHistSmall = 512;   // up to this many bins four waves have histograms (32 KiB of LDS), else one
+// Beyond this many bins a workgroup's LDS leaves room for five, and three waves
+// more clear and write out the one wave's histogram (4096 bins, one event: 18 us
+// with a wave alone, 12 so).  Below, they would take the place of workgroups (513
+// bins, 1e7 events in one of them: 1134 us without them, 1309 with).
+constexpr int kHistLarge = 1024;
 
 // Histograms of a wave: groups of neighbouring lanes have one each, as long as
 // 32 KiB hold them, which shortens the rounds to the fullest bin of a group.
 int hist_groups(int nb) { return nb <= kHistSmall / 4 ? 4 : nb <= kHistSmall / 2 ? 2 : 1; }
 
 __global__ __launch_bounds__(kBlock) void k_hist_block(const double* __restrict__ x, const double* __restrict__ w,
-                                                       int64_t n, int64_t chunk, int nb, int bits, int groups, double lo,
-                                                       double hi, double scale, double* __restrict__ part) {
+                                                       int64_t n, int64_t chunk, int nb, int bits, int waves,
+                                                       int groups, double lo, double hi, double scale,
+                                                       double* __restrict__ part) {
     extern __shared__ double hs[];  // [waves][groups][nb][2]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = 64 * waves;
     for (int i = threadIdx.x; i < waves * groups * nb * 2; i += blockDim.x) hs[i] = 0.0;
     __syncthreads();
     const int wide = 64 / groups, group = lane / wide;  // lanes of a group
@@ -437,11 +443,12 @@ __global__ __launch_bounds__(kBlock) void k_hist_block(const double* __restrict_
     const int64_t e0 = blockIdx.x * chunk, e1 = min(n, e0 + chunk);
     const uint64_t below = (uint64_t(1) << lane) - 1;
     constexpr int kFlight = 4;
-    for (int64_t e = e0 + wave * 64; e < e1; e += (int64_t)blockDim.x * kFlight) {
+    // waves without a histogram only clear and write out
+    for (int64_t e = wave < waves ? e0 + wave * 64 : e1; e < e1; e += (int64_t)step * kFlight) {
         double xv[kFlight], wv[kFlight];
 #pragma unroll
         for (int u = 0; u < kFlight; ++u) {
-            const int64_t i = e + (int64_t)u * blockDim.x + lane;
+            const int64_t i = e + (int64_t)u * step + lane;
             xv[u] = i < e1 ? x[i] : 0.0;
             wv[u] = i < e1 ? w[i] : 0.0;
         }
@@ -874,11 +881,11 @@ hipError_t launch_histogram(const double* x, const double* w, int64_t n, int nb,
     const double scale = nb / (hi - lo);
     int bits = 0;
     while ((1 << bits) < nb) ++bits;
-    const int threads = nb <= kHistSmall ? kBlock : 64;
-    const int groups = hist_groups(nb);
-    const size_t lds = sizeof(double) * 2 * (size_t)nb * (threads / 64) * groups;
-    k_hist_block<<<dim3((unsigned)nz), dim3(threads), lds, s>>>(x, w, n, (n + nz - 1) / nz, nb, bits, groups, lo,
-                                                                hi, scale, part);
+    const int waves = nb <= kHistSmall ? kWaves : 1, groups = hist_groups(nb);
+    const size_t lds = sizeof(double) * 2 * (size_t)nb * waves * groups;
+    const int threads = nb <= kHistLarge ? 64 * waves : kBlock;
+    k_hist_block<<<dim3((unsigned)nz), dim3(threads), lds, s>>>(x, w, n, (n + nz - 1) / nz, nb, bits, waves, groups, lo, hi,
+                                                                scale, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_hist_reduce<<<dim3((unsigned)(2 * nb)), dim3(64), 0, s>>>(part, (int)nz, nb, out);

@@ -323,3 +323,11 @@ def test_statistics_of_device_counts(torch, vegas):
     g.close()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("bins", [1023, 1024, 1025, 2048])
+@pytest.mark.parametrize("n", [1, 65, 2049, 300_007])
+def test_histogram_with_helping_waves(torch, bins, n):
+    """Around the number of bins from which three waves of a workgroup only clear
+    and write out: as for the other shapes."""
+    test_histogram_shapes(torch, bins, n)
