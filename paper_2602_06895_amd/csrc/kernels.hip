@@ -284,6 +284,17 @@ constexpr int kObsE = 0, kObsPt = 1, kObsEta = 2, kObsPhi = 3, kObsM = 4, kObsPt
 __device__ __forceinline__ double pt_of(double px, double py) { return sqrt(px * px + py * py); }
 __device__ __forceinline__ double eta_of(double px, double py, double pz) { return asinh(pz / pt_of(px, py)); }
 
+// The kinds of a summed momentum.
+__device__ __forceinline__ double of_sum(int kind, double E, double X, double Y, double Z) {
+    switch (kind) {
+        case kObsE: return E;
+        case kObsPt: return pt_of(X, Y);
+        case kObsEta: return eta_of(X, Y, Z);
+        case kObsPhi: return atan2(Y, X);
+        default: return sqrt(fmax(E * E - X * X - Y * Y - Z * Z, 0.0));
+    }
+}
+
 struct ObsList {
     ObsK o[8];
     uint32_t need_e, need_xy, need_z;  // final-state particles whose components any observable reads
@@ -370,15 +381,59 @@ __global__ __launch_bounds__(kBlock) void k_observables(const double* __restrict
                 Y += FY[i];
                 Z += FZ[i];
             }
-            switch (kind) {
-                case kObsE: v = E; break;
-                case kObsPt: v = pt_of(X, Y); break;
-                case kObsEta: v = eta_of(X, Y, Z); break;
-                case kObsPhi: v = atan2(Y, X); break;
-                default: v = sqrt(fmax(E * E - X * X - Y * Y - Z * Z, 0.0)); break;
-            }
+            v = of_sum(kind, E, X, Y, Z);
         }
         out[(int64_t)j * n + e] = v;
+    }
+}
+
+// The same for a list without ordered kinds, every observable straight from
+// memory, where the list reads no more particles than there are: the registers of
+// all particles (131 to 193) then only cost waves.  5e6 events of eight particles,
+// one p_T: 65 us through registers, 26 so (42 before); the mass of all 233 both
+// ways; energy and mass of all, 16 reads, 247 and 391.
+__global__ __launch_bounds__(kBlock) void k_observables_direct(const double* __restrict__ p, int np, int64_t n, ObsList ol,
+                                                               int k, double* __restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n) return;
+    for (int j = 0; j < k; ++j) {
+        const int kind = ol.o[j].kind;
+        double E = 0.0, X = 0.0, Y = 0.0, Z = 0.0;
+        // a loop per kind: the components of a particle are then in flight together
+        auto each = [&](auto&& add) {
+            for (uint32_t m = ol.o[j].set; m; m &= m - 1) {
+                const double* at = p + (int64_t)(__builtin_ctz(m) + 2) * n + e;
+                add([&](int c) { return at[(int64_t)c * np * n]; });
+            }
+        };
+        switch (kind) {
+            case kObsE: each([&](auto&& q) { E += q(0); }); break;
+            case kObsPt:
+            case kObsPhi:
+                each([&](auto&& q) {
+                    const double x = q(1), y = q(2);
+                    X += x;
+                    Y += y;
+                });
+                break;
+            case kObsEta:
+                each([&](auto&& q) {
+                    const double x = q(1), y = q(2), z = q(3);
+                    X += x;
+                    Y += y;
+                    Z += z;
+                });
+                break;
+            default:
+                each([&](auto&& q) {
+                    const double t = q(0), x = q(1), y = q(2), z = q(3);
+                    E += t;
+                    X += x;
+                    Y += y;
+                    Z += z;
+                });
+        }
+        out[(int64_t)j * n + e] = of_sum(kind, E, X, Y, Z);
     }
 }
 
@@ -832,6 +887,7 @@ hipError_t launch_observables(const double* p, int np, int64_t n, const int32_t*
                               hipStream_t s) {
     if (n == 0) return hipSuccess;
     ObsList ol{};
+    int reads = 0;  // particles of all sets
     for (int j = 0; j < k; ++j) {
         ol.o[j].kind = spec[4 * j];
         ol.o[j].set = (uint32_t)spec[4 * j + 1];
@@ -843,9 +899,14 @@ hipError_t launch_observables(const double* p, int np, int64_t n, const int32_t*
         if (kind != kObsE) ol.need_xy |= set;
         if (kind == kObsEta || kind == kObsM || kind == kObsDrHardest) ol.need_z |= set;
         if (ordered) ol.need_pt |= set;
+        reads += __builtin_popcount(set);
     }
     const dim3 b((unsigned)((n + kBlock - 1) / kBlock)), t(kBlock);
     static_assert(kMaxFinal == 8, "one instantiation per particle count");
+    if (!ol.need_pt && reads <= np - 2) {
+        k_observables_direct<<<b, t, 0, s>>>(p, np, n, ol, k, out);
+        return hipGetLastError();
+    }
     switch (np - 2) {
         case 2: k_observables<2><<<b, t, 0, s>>>(p, n, ol, k, out); break;
         case 3: k_observables<3><<<b, t, 0, s>>>(p, n, ol, k, out); break;

@@ -331,3 +331,34 @@ def test_histogram_with_helping_waves(torch, bins, n):
     """Around the number of bins from which three waves of a workgroup only clear
     and write out: as for the other shapes."""
     test_histogram_shapes(torch, bins, n)
+
+
+@pytest.mark.parametrize("nf", range(2, 9))
+def test_observables_of_short_and_long_lists(torch, nf):
+    """Lists without ordered kinds that read as many particles as there are, one
+    fewer and one more, which is where they change kernels: the bits of the
+    same observables beside a rank, and the oracle's values within the bound of
+    the test of all kinds."""
+    from paper_2602_06895_amd import OBS_E, OBS_ETA, OBS_M, OBS_PHI, OBS_PT, OBS_PT_RANK, Context
+
+    rng = np.random.default_rng(50 + nf)
+    n = 777
+    p = rng.normal(0.0, 50.0, (4, nf + 2, n))
+    p[0] = np.sqrt((p[1:] ** 2).sum(0))
+    dev = torch.from_numpy(p).cuda()
+    every = list(range(nf))
+    ctx = Context(W.volume_process(nf) if nf > 2 else W.c1_ee_mumu())
+    lists = [[(k, every, 0)] for k in (OBS_E, OBS_PT, OBS_ETA, OBS_PHI, OBS_M)]
+    lists += [[(OBS_M, every, 0), (OBS_PT, [nf - 1], 0)], [(OBS_ETA, every[1:], 0)],
+              [(OBS_PT, [i], 0) for i in every], [(OBS_M, every[:2], 0), (OBS_PHI, [0], 0), (OBS_E, every[1:], 0)]]
+    for spec in lists:
+        got = ctx.observables(0, dev, spec).cpu().numpy()
+        beside = ctx.observables(0, dev, spec[:7] + [(OBS_PT_RANK, every, 0)]).cpu().numpy()[:len(spec)]
+        assert np.array_equal(got[:7], beside[:7])
+        want = oracle.observables(p, spec)
+        scale = np.abs(want) + 1e-3
+        for j, (kind, s, _) in enumerate(spec):
+            if kind == OBS_M:
+                scale[j] += p[0, [2 + i for i in s]].sum(0) ** 2 / np.maximum(want[j], 1e-3) * 1e-2
+        assert np.all(np.abs(got - want) <= 1e-12 * scale)
+    ctx.close()
