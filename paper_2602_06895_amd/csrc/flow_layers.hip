@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     __shared__ __attribute__((aligned(16))) T cond[EV * kCond];
     __shared__ float zs[2 * kWaves][EV];
     __shared__ float lds_ld[kWaves][EV];
-    if (BINS) fn.K = BINS;
+    fn.K = BINS;
     const int nh = fn.nh, d = 2 * nh, K = fn.K;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ev = lane & 15, q = lane >> 4;
@@ -255,12 +255,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (tid < EV && e0 + tid < n) run.logdet[e0 + tid] = ld;
 }
 
-// The bins are a constant of the kernels of large BF16 passes: with their number
-// known at run time only, each bin's exponentials stand behind a branch of their
-// own and wait for themselves (450,000 events of 10 dimensions, 6 layers, 8
-// bins, inverse: 1164 us, as a constant 805; the same bits).  In the others,
-// bound by their weights or their products, only 16 bins are, whose knots are
-// searched by halves, and in tiles of 16 events 8.
+// The bins are a constant of the kernels of BF16 passes: with their number known
+// at run time only, each bin's exponentials stand behind a branch of their own and
+// wait for themselves (450,000 events of 10 dimensions, 6 layers, 8 bins, inverse:
+// 1164 us, as a constant 805; 1,000 events of 10 dimensions, 8 layers, 2 bins 51 and
+// 39, 5 bins 54 and 44, 12 bins 62 and 52), and small and large passes then do the
+// same operations (one bin at run time gave other bits in tiles of 16).  In the
+// others, bound by their weights or their products, only 16 bins are, whose knots
+// are searched by halves.
 template <bool INV, int BINS>
 void launch_bins(const FlowNet& fn, const FlowRun& run, dim3 g, size_t lds, hipStream_t s) {
     if constexpr (BINS > 0) {
@@ -268,6 +270,16 @@ void launch_bins(const FlowNet& fn, const FlowRun& run, dim3 g, size_t lds, hipS
             k_flow_layers<INV, 4, true, BINS, __bf16><<<g, dim3(kThreads), lds, s>>>(fn, run);
         else
             launch_bins<INV, BINS - 1>(fn, run, g, lds, s);
+    }
+}
+
+template <bool INV, int BINS>
+void launch_tile(const FlowNet& fn, const FlowRun& run, int64_t grid, hipStream_t s) {
+    if constexpr (BINS > 0) {
+        if (fn.K == BINS)
+            k_flow_tile<INV, BINS><<<(unsigned)grid, kThreads, 0, s>>>(fn, run);
+        else
+            launch_tile<INV, BINS - 1>(fn, run, grid, s);
     }
 }
 
@@ -308,12 +320,8 @@ hipError_t launch_pass(const FlowNet& fn, const FlowRun& run, int cu_count, hipS
     // tiles of 16 would take 118)
     if (t16 <= cu_count) {
         if (fn.nh > kWaves) return launch_layers<INV, 1, __bf16>(fn, run, t16, s);
-        if (fn.K == 16)
-            k_flow_tile<INV, 16><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
-        else if (fn.K == 8)
-            k_flow_tile<INV, 8><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
-        else
-            k_flow_tile<INV, 0><<<(unsigned)t16, kThreads, 0, s>>>(fn, run);
+        if (fn.K < 1 || fn.K > 16) return hipErrorInvalidValue;
+        launch_tile<INV, 16>(fn, run, t16, s);
         return hipGetLastError();
     }
     return launch_layers<INV, 4, __bf16>(fn, run, std::min<int64_t>((t16 + 3) / 4, cu_count), s);

@@ -221,3 +221,16 @@ def test_fp32_gradient_blocks_of_a_large_batch(torch):
             assert np.linalg.norm(got[at:at + k] - ref[at:at + k]) <= 1e-3 * np.linalg.norm(ref[at:at + k])
             at += k
     f.close()
+
+
+@pytest.mark.parametrize("d", [10, 16])
+@pytest.mark.parametrize("bins", range(1, 17))
+def test_small_and_large_passes_agree(torch, d, bins):
+    """A pass in tiles of 16 events and one in tiles of 64: the same bits for every
+    number of bins."""
+    f, _ = _pair(d, 4, bins, 3)
+    u = torch.from_numpy(W.philox_uniforms_f32(3, 1, 0, 5000, d)).cuda()
+    for name in ("inverse", "forward"):
+        large, small = getattr(f, name)(u), getattr(f, name)(u[:, :1000].contiguous())
+        assert torch.equal(small[0], large[0][:, :1000]) and torch.equal(small[1], large[1][:1000])
+    f.close()
