@@ -234,3 +234,36 @@ def test_small_and_large_passes_agree(torch, d, bins):
         large, small = getattr(f, name)(u), getattr(f, name)(u[:, :1000].contiguous())
         assert torch.equal(small[0], large[0][:, :1000]) and torch.equal(small[1], large[1][:1000])
     f.close()
+
+
+def _reverse_edge(torch):
+    """The largest batch whose reverse kernels take tiles of 32 events: one for
+    every compute unit."""
+    return 32 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+# up to the edge tiles of 32 events, beyond it of 64: 16 and fewer bins, one and
+# more chunks of eight coordinates, a partial last tile
+@pytest.mark.parametrize("d,layers,bins,beyond", [(16, 2, 16, 0), (16, 2, 16, 1), (16, 2, 16, 107), (18, 2, 16, 75),
+                                                  (24, 2, 5, 97), (64, 2, 12, 33), (64, 1, 16, 65), (10, 2, 8, 64),
+                                                  (2, 2, 16, 31)])
+def test_gradient_around_the_tile_edge(torch, d, layers, bins, beyond):
+    """The gradient of batches at and beyond the edge against the oracle, with the
+    bound of the other shapes."""
+    test_gradient_matches_oracle(torch, d, layers, bins, _reverse_edge(torch) + beyond)
+
+
+@pytest.mark.parametrize("d,bins", [(16, 16), (24, 9)])
+def test_gradient_across_the_tile_edge(torch, d, bins):
+    """Batches of both tile sizes in turn in the same buffers: the bits of a flow
+    that has seen nothing else."""
+    sizes = [_reverse_edge(torch) + 523, 77, _reverse_edge(torch) + 40, _reverse_edge(torch) - 1]
+    f, _ = _pair(d, 3, bins, 5)
+    for n in sizes:
+        *_, dev = _batch(torch, d, n, n)
+        got, _ = f.gradient(*dev)
+        h, _ = _pair(d, 3, bins, 5)
+        want, _ = h.gradient(*dev)
+        assert torch.equal(got, want)
+        h.close()
+    f.close()
