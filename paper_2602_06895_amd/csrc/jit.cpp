@@ -177,13 +177,23 @@ bool compile_load(const std::string& body, const std::string& arch, JitSample& j
 }
 
 // One kernel for channels [c0, c1): first at three waves per SIMD (168
-// registers), which is faster than two waves with little scratch (t tbar: 12
-// B/lane, 5% faster) and still with some (the eight pp -> 4 jets channels: 148
-// B/lane, mostly of the three t-channel chains, 132 instead of 142 us per
-// million events); a three-wave build with more scratch than kMaxScratch is
-// dropped for the compiler's default occupancy.  Returns 0 with the kernel in
-// j, 1 when the kernel spills even at the default occupancy (not kept), -1 on
-// error.
+// registers), kept with up to kMaxScratch of scratch, else at the compiler's
+// default occupancy.  Microseconds per million events at three waves (with that
+// scratch) and at the default without any:
+//   pp -> 4 jets, 1, 2, 3, 4 and 8 channels from the first (112 to 148 B)
+//     124 / 124, 128 / 132, 133 / 137, 127 / 135, 129 / 140;
+//     mixed precision (52 to 88 B) 122 / 126, 129 / 135, 131 / 139, 128 / 137, 129 / 140
+//   one (s~, t) chain (80, mixed 72 B) 126 / 127, 129 / 131
+//   2 -> 5 and 2 -> 6 flat (mixed 60 and 156 B) 156 / 165, 203 / 206, FP64 2 -> 5
+//     (144 B) 203 / 199
+//   pp -> 5, two channels (mixed 156, FP64 216 B) 162 / 164, 158 / 163
+//   2 -> 6 and 2 -> 8 flat (268, mixed 316 B) 264 / 248, 368 / 323
+// t tbar and the other programs tried need none.  So the limit lies where the
+// gains end and the losses are not yet seen.  A launch with scratch starts 2 us
+// later, which a call of 20,000 events does not win back (eight channels: 24.5 us,
+// 22.2 without); a second kernel for such calls would double the time to compile
+// (2 s for eight channels), so they pay.  Returns 0 with the kernel in j, 1 when
+// the kernel spills even at the default occupancy (not kept), -1 on error.
 int build_group(const Compiled& comp, int mixed, const std::string& arch, int c0, int c1, JitSample& j,
                 int* scratch_out, std::string& err) {
     constexpr int kMaxScratch = 160;
