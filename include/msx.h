@@ -329,19 +329,20 @@ msx_status msx_autotune(msx_ctx* ctx, const int64_t* counts, uint64_t seed, int3
  * them: msx_sample, msx_sample_device, msx_sample_noalloc and graphs
  * captured afterwards.  Channels are compiled in groups of at most eight
  * consecutive channels, one kernel each, launched one after the other in
- * the same stream (a group whose kernel would spill registers is split).
+ * the same stream (a group whose kernel spills registers is split; kernels of
+ * three waves per SIMD may spill up to 160 B per lane).
  * Results are bit-identical to the default kernel's in MSX_FP64 (same
  * source, no floating-point contraction in either) and differ by FP32
  * roundings in MSX_MIXED; the kernels run fewer instructions with fewer
  * registers.  The first call compiles on the host (0.5 s for one t tbar
- * channel, 4 s for eight pp -> 4 jets channels) and synchronises the device;
+ * channel, 2 s for eight pp -> 4 jets channels) and synchronises the device;
  * later calls only switch.  on == 0 switches launches back to the default
  * kernel; the compiled ones stay loaded until msx_destroy (graphs captured
  * with them keep working).  MSX_META_SPECIALIZED gives the number of
  * kernels in use (0: the default kernel).  Errors: MSX_ERR_DEVICE with the
  * compiler's log when the run-time compiler or a module load fails;
- * MSX_ERR_UNSUPPORTED when the kernel of a single channel would spill
- * registers to scratch (it would be slower than the default one).  In both
+ * MSX_ERR_UNSUPPORTED when the kernel of a single channel would spill more
+ * registers than that (it would be slower than the default one).  In both
  * cases the context keeps the default kernel. */
 msx_status msx_specialize(msx_ctx* ctx, int32_t on);
 
@@ -456,8 +457,8 @@ msx_status msx_cut(msx_ctx* ctx, int64_t n, const double* x, int32_t k, const do
  * (device) = (sum w, sum w^2) over the events in each of `bins` (1..4096)
  * equal bins of [lo, hi), bin = floor((x - lo) bins / (hi - lo)); events
  * outside [lo, hi) are not counted.  Deterministic (fixed summation order for
- * a given n).  Uses a context-owned scratch of 2 bins ceil(n / 2048) doubles
- * (grown on demand: a call that grows it synchronizes the device). */
+ * a given n).  Uses a context-owned scratch of 2 bins min(2048, ceil(n / 2048))
+ * doubles (grown on demand: a call that grows it synchronizes the device). */
 msx_status msx_histogram(msx_ctx* ctx, int64_t n, const double* x, const double* w, int32_t bins, double lo, double hi,
                          double* hist, void* stream);
 

@@ -86,7 +86,12 @@ __device__ __forceinline__ void vegas_wave_accumulate(double* __restrict__ hw, c
     const double w2 = wv * wv;
     const int lo = __double2loint(w2), hi = __double2hiint(w2);
     // the lane number, opaque: the masks below are then formed here and not
-    // kept in registers across the whole event loop
+    // kept in registers across the whole event loop.  An early form without this
+    // line had 14 registers more, and in that build the mixed-precision kernel of
+    // Chili channels (some 150 AGPRs) gave other weights from run to run, the low
+    // word of a double lost.  The cause is not known: nothing in the source explains
+    // it, and a later build that differs by this line only repeats its bits.  Repeat
+    // calls are tested bit for bit for every kind of channel.
     int own = lane;
     asm volatile("" : "+v"(own));
     for (int k = 0; k < dims; ++k) {

@@ -575,8 +575,8 @@ __global__ __launch_bounds__(kBlock) void k_density_add(double* __restrict__ g, 
     g[i] = sum;
 }
 
-//
-// One workgroup, a word per thread; it also clears n_clear accumulators for a
+// Device copy of a call table made on the host: one workgroup, a word per
+// thread; it also clears n_clear accumulators for a
 // caller whose statistics start with the call.  A launch of this size costs 4
 // us whatever it does; written by one thread the table took 5, and clearing
 // the accumulators by a memset 4 to 8 more (one fill kernel or two).

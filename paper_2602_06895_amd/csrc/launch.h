@@ -88,7 +88,6 @@ int64_t unweight_words(int64_t n);
 hipError_t launch_unweight(const double* w, int64_t n, double w_max, uint64_t seed, uint64_t sid, uint64_t e0,
                            int64_t* blk, int64_t* keep, double* uw, int64_t* count, hipStream_t s);
 
-// g = alpha / jac (first) or g += alpha / jac; jac = 0 adds nothing.
 // g = (first ? 0 : g) + sum of alpha[i] / jac[i][e] over n_chans channels, in
 // order (jac <= 0: no term).
 struct DensityAlpha {
