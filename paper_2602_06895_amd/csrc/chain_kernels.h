@@ -133,7 +133,9 @@ __device__ __forceinline__ double finish_event(const ChannelTab* __restrict__ ct
 // the time goes down with the waves in flight.  A class is held to the next
 // register limit (512 / waves) where it exceeds it by a few registers; the
 // others (1 -> 3 decays, Chili, the largest slots in FP64) would spill
-// hundreds.
+// hundreds.  The map kernels of six slots come to three waves by themselves (164
+// registers); held to three they were 10% slower (2e6 events of e+e- -> mu+mu-: 83
+// us, 75 without).
 constexpr bool tree_kinds(int kinds) { return (kinds & (KIND_CHILI | KIND_DEC3 | KIND_ST)) == 0; }
 constexpr int map_waves(int ns, int kinds) { return tree_kinds(kinds) && ns == 10 ? 2 : 1; }
 constexpr int sample_waves(int ns, int kinds, bool mix) {
