@@ -131,15 +131,19 @@ __device__ __forceinline__ double finish_event(const ChannelTab* __restrict__ ct
 // Waves per SIMD that a class kernel is compiled for.  These kernels walk the
 // channel's tables, so a wave issues a vector instruction every 18 cycles and
 // the time goes down with the waves in flight.  A class is held to the next
-// register limit (512 / waves) where it exceeds it by a few registers; the
-// others (1 -> 3 decays, Chili, the largest slots in FP64) would spill
-// hundreds.  The map kernels of six slots come to three waves by themselves (164
-// registers); held to three they were 10% slower (2e6 events of e+e- -> mu+mu-: 83
-// us, 75 without).
+// register limit (512 / waves) where it exceeds it by a few registers.  With Chili
+// channels or (s~, t) blocks the six-slot kernels come to 264 registers, one wave
+// and some in AGPRs; held to two waves they spill 20 values (the maps 3): 2e6 events
+// of pp -> 4 jets with a Chili channel 688 -> 401 us, with an (s~, t) chain 790 ->
+// 452.  The larger ones of those kinds would spill thousands (10 slots: 2442),
+// those with 1 -> 3 decays of 10 slots 1649, the largest slots in FP64 hundreds.
+// The map kernels of six slots come to three waves by themselves (164 registers);
+// held to three they were 10% slower (2e6 events of e+e- -> mu+mu-: 83 us, 75
+// without).
 constexpr bool tree_kinds(int kinds) { return (kinds & (KIND_CHILI | KIND_DEC3 | KIND_ST)) == 0; }
-constexpr int map_waves(int ns, int kinds) { return tree_kinds(kinds) && ns == 10 ? 2 : 1; }
+constexpr int map_waves(int ns, int kinds) { return tree_kinds(kinds) ? (ns == 10 ? 2 : 1) : (ns == 6 ? 2 : 1); }
 constexpr int sample_waves(int ns, int kinds, bool mix) {
-    return tree_kinds(kinds) ? (ns == 6 ? 3 : (ns == 10 || mix ? 2 : 1)) : 1;
+    return tree_kinds(kinds) ? (ns == 6 ? 3 : (ns == 10 || mix ? 2 : 1)) : (ns == 6 ? 2 : 1);
 }
 constexpr int inverse_waves(int ns, int kinds) { return ns == 6 && !(kinds & KIND_DEC3) ? 4 : 1; }
 
