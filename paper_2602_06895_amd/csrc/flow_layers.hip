@@ -31,10 +31,10 @@ constexpr size_t layers_lds(int d, int kept) {
 // its start.
 //
 // What bounds it: per 64 events and layer each of the two waves of a SIMD
-// issues 690 vector instructions, most of them in the splines (32
-// exponentials, sums and knots per event and coordinate), and 100 MFMAs, a
-// quarter of them for the padding of 49 parameters to 64 rows; the vector
-// units are busy 60% of the time, the matrix units 27%, and what is left is
+// issues 786 vector instructions, most of them in the splines (32
+// exponentials, sums and knots per event and coordinate), 100 of them MFMAs, a
+// quarter of those for the padding of 49 parameters to 64 rows; the vector
+// units are busy 58% of the time, the matrix units 26%, and what is left is
 // the latency of the three barriers and the LDS reads behind them.  Before, a
 // wave read every weight of a layer from L2 for its own 64 events and walked
 // each spline through LDS: 4583 us for eight layers of 2^20 events of 16

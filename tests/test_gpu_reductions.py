@@ -362,3 +362,44 @@ def test_observables_of_short_and_long_lists(torch, nf):
                 scale[j] += p[0, [2 + i for i in s]].sum(0) ** 2 / np.maximum(want[j], 1e-3) * 1e-2
         assert np.all(np.abs(got - want) <= 1e-12 * scale)
     ctx.close()
+
+
+def _large(case):
+    """Processes whose class kernels keep more than 256 registers."""
+    ttbar = W.c3_ttbar6()
+    three = {"s": {"d": [{"d": [1, 2, 3], "m": 173.0, "w": 1.5, "order": 1},
+                         {"d": [4, 5, 6], "m": 173.0, "w": 1.5, "order": 2}]}}
+    if case == "chili6":
+        return W.chili_process(6, 13000.0, pt_min=20.0, pdf=[-1.2, 3.0])
+    if case == "chili8":
+        return W.chili_process(8, 13000.0, pt_min=20.0)
+    if case == "vol8":
+        return W.volume_process(8)
+    if case == "ttbar6+chili":
+        return dict(ttbar, channels=ttbar["channels"] + [{"chili": True}])
+    if case == "ttbar6+dec3":
+        return dict(ttbar, channels=ttbar["channels"] + [three])
+    return dict(ttbar, channels=ttbar["channels"] + [three, {"chili": True}])
+
+
+@pytest.mark.parametrize("case", ["chili6", "chili8", "vol8", "ttbar6+chili", "ttbar6+dec3", "all"])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_sample_of_large_kernels_repeats_its_bits(torch, case, mixed):
+    """As above, for the kernels with more than 256 registers; the map kernel of
+    the last channel too."""
+    from paper_2602_06895_amd import FP64, MIXED, Context
+
+    ctx = Context(_large(case), precision=MIXED if mixed else FP64)
+    counts = np.full(ctx.n_channels, 20011)
+    c = ctx.n_channels - 1
+    y = ctx.uniform(3, 1, 5, 20011, ctx.dims[c])
+    for flags in (0, 1):
+        ref = None
+        for _ in range(3):
+            torch.randn(1 << 22, device="cuda").sin_()
+            out = ctx.sample(counts, seed=11, stream_id=4, counter_offset=123, flags=flags)
+            m = ctx.map(c, y, weight=True)
+            bits = [t.view(torch.int64).clone() for t in (out["w"], out["p"], m["p"], m["w"])]
+            ref = ref or bits
+            assert all(torch.equal(a, b) for a, b in zip(bits, ref))
+    ctx.close()
