@@ -589,7 +589,7 @@ msx_status sample_host(msx_ctx* ctx, const int64_t* counts, uint64_t seed, uint6
     if (flags & MSX_SAMPLE_USE_FLOW) return sample_with_flows(ctx, counts, seed, stream_id, counter_offset, flags, p,
                                                               x1x2, w, chan, stream);
     const int C = (int)ctx->comp.chans.size();
-    SampleCall call;
+    SampleRanges call;
     std::memset(&call, 0, sizeof call);
     call.n_chan = C;
     call.ept = ctx->ept;
@@ -1167,7 +1167,7 @@ msx_status sample_with_flows(msx_ctx* ctx, const int64_t* counts, uint64_t seed,
                              uint64_t counter_offset, int32_t flags, double* p, double* x1x2, double* w, int32_t* chan,
                              void* stream) {
     const int C = (int)ctx->comp.chans.size();
-    SampleCall call;
+    SampleRanges call;
     std::memset(&call, 0, sizeof call);
     call.n_chan = C;
     call.ept = ctx->ept;

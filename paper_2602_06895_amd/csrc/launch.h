@@ -143,7 +143,7 @@ size_t sample_lds_bytes(int max_slots, int max_inv, size_t lds_bytes, int vstrid
 
 // Device copy of a host-built call table (stream ordered); with clear != NULL
 // the same launch zeroes clear[n_clear].
-hipError_t launch_set_call(const SampleCall& host, SampleCall* dev, double* clear, int n_clear, hipStream_t s);
+hipError_t launch_set_call(const SampleRanges& host, SampleCall* dev, double* clear, int n_clear, hipStream_t s);
 // x[n] = 0 for a few values, by a kernel (so that a caller may capture it).
 hipError_t launch_clear(double* x, int n, hipStream_t s);
 

@@ -171,15 +171,18 @@ struct ProcessTab {
     double prior_share, tree_share;
 };
 
-// Per-call description of a multichannel launch (passed by value).
-struct SampleCall {
+// Per-call description of a multichannel launch.  The ranges come by value from
+// the host or are written on the device; the counters are cleared there.
+struct SampleRanges {
     int32_t n_chan;
     int32_t ept;                           // events per thread per tile
     int64_t n_tiles;
     uint64_t skip_mask;                    // channels whose events another launch writes (no tiles, no statistics)
     int64_t tile_start[kMaxChannels + 1];  // first tile of each channel
     int64_t ev_start[kMaxChannels + 1];    // first output position
-    uint32_t slices_done[kMaxChannels];    // statistics in slices: those that are summed (zero before the call)
+};
+struct SampleCall : SampleRanges {
+    uint32_t slices_done[kMaxChannels];  // statistics in slices: those that are summed
 };
 
 // The channels of one map or inverse launch, blockIdx.y of them: their table,
